@@ -110,10 +110,10 @@ msp_status msp_update_vacant_counts(msp_octree t, const int32_t* vac_dend_exc,
  *   elem_offset_out [n+1] int64: exclusive prefix sum of vac_axon (CSR by source).
  * Every search reads the octree as refreshed last (all requests are formed before
  * any is answered). The level-0 normaliser Z of a source (Sec. III-A) is added up in
- * float64 in the walk's depth-first order; a call with few sources (under 2^21) cuts
- * the walk into up to 8 consecutive pre-order ranges, searched in parallel, whose sums
- * are then added in order, so Z's last bits depend on the cut (the draw follows the
- * same sums). Errors: MSP_ERR_CAPACITY if S = sum(vac_axon) > capacity_S:
+ * float64 in the walk's depth-first order; a call with fewer than about 2^23 sources cuts
+ * the walk into up to 64 consecutive pre-order ranges, searched in parallel, whose sums
+ * are then added in order, so Z's last bits depend on the cuts (the draw follows the
+ * same sums; the cuts follow from the octree and the sources alone). Errors: MSP_ERR_CAPACITY if S = sum(vac_axon) > capacity_S:
  * then only elem_offset_out is written (elem_offset_out[n] = S sizes the buffer);
  * MSP_ERR_INVALID for sigma <= 0, theta < 0, a negative vac_axon or a type > 1
  * (the last two found on the device before the search: target_out is not written).

@@ -35,7 +35,7 @@ struct AttractArgs {
   double two_over_s2;           // 2 / sigma^2
   double two_over_s3;           // 2 / sigma^3
   int64_t N;
-  const int32_t* unit_count;    // device scalar: the sweep units (parts of tiles)
+  const int32_t* unit_count;    // device scalar: the units (runs of parts of tiles)
 };
 
 // The die (XCC) this wave runs on: bits 3:0 of hardware register XCC_ID (20). It only
@@ -116,10 +116,10 @@ __device__ __forceinline__ void wave_add3(double fx, double fy, double fz, doubl
   if (lane < 3) atomicAdd(dst + comp, v);
 }
 
-// Part `part` of the tile's 2^plog parts (the search's level-0 sweep cut into parts:
-// the lane states at the part's first node come from its ancestors).
-__device__ void attract_tile(const SearchArgs& A, const AttractArgs& O, int tile, int part,
-                             int plog, int lane) {
+// The parts of unit U of the tile (the search's level-0 sweep cut into parts: the lane
+// states at the unit's first node come from its ancestors).
+__device__ void attract_unit(const SearchArgs& A, const AttractArgs& O, int tile,
+                             const UnitParts& U, int lane) {
   const int64_t slot = (int64_t)tile * kWave + lane;
   const int32_t i = A.work[slot];
   const bool valid = i >= 0;
@@ -158,12 +158,11 @@ __device__ void attract_tile(const SearchArgs& A, const AttractArgs& O, int tile
   const NodeRec root = load_rec(R, 0);
   if (!(root.meta & kLeafBit)) {
     const int32_t root_end = (int32_t)(root.meta & kSkipMask);
-    int32_t x = 1, end = root_end;
+    const int32_t med = U.plog == 1 ? median_cut(li, valid, lane, root_end) : 0;
+    int32_t x = unit_begin(U, med);
+    const int32_t end = part_end(U, U.count - 1, med, root_end);
     int32_t me = valid ? 0 : 0x7FFFFFFF;
-    if (plog > 0) {
-      part_range(li, valid, lane, plog, part, root_end, x, end);
-      if (x > 1 && x < end) me = mask_at<true>(A, R, x, me, li, xi, yi, zi);
-    }
+    if (x > 1 && x < end) me = mask_at<true>(A.L2, A.theta2, A.acc_d2, R, x, me, li, xi, yi, zi);
     while (x < end) {
       const NodeRec cur = load_rec(R, x);
       const bool active = x >= me;
@@ -229,10 +228,9 @@ __global__ void __launch_bounds__(256) attract_bwd_k(BatchDev B, AttractArgs O) 
   const int64_t unit = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
   if (unit >= *O.unit_count) return;
   const SearchArgs A = args_of(B.sims, 0, B.work);
-  const int plog = __builtin_amdgcn_readfirstlane((int)as_const(B.plog)[0]);
-  const int local = __builtin_amdgcn_readfirstlane((int)(unit - as_const(B.unit_base)[0]));
-  const int tile = as_const(B.tile_base)[0] + (local >> plog);
-  attract_tile(A, O, tile, local & ((1 << plog) - 1), plog, lane);
+  int sim, tile;
+  const UnitParts U = unit_parts(B, __builtin_amdgcn_readfirstlane((int)unit), sim, tile);
+  attract_unit(A, O, tile, U, lane);
 }
 
 // Z of every source from the sweep's part sums (added in part order, then rounded to
@@ -245,7 +243,7 @@ __global__ void z_scatter_k(BatchDev B, SweepOut W, float* __restrict__ Z) {
   if (i < 0) return;
   const int sim = find_sim(B.tile_base, B.nsims, tile);
   const int plog = B.plog[sim];
-  const int64_t u0 = (int64_t)B.unit_base[sim] + ((tile - (int64_t)B.tile_base[sim]) << plog);
+  const int64_t u0 = (int64_t)B.part_base[sim] + ((tile - (int64_t)B.tile_base[sim]) << plog);
   const int64_t lane = slot % kWave;
   double z = 0.0;
   for (int q = 0; q < (1 << plog); ++q) z = z + W.Z[(u0 + q) * kWave + lane];

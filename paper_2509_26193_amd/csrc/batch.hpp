@@ -14,6 +14,7 @@
 
 #include <algorithm>
 
+#include "build.hpp"
 #include "scan.hpp"
 #include "search_wave.hpp"
 
@@ -23,141 +24,60 @@ namespace msp {
 // and ids (see restart_search).
 constexpr size_t kRestartLds = kRestartKeep * (sizeof(double) + sizeof(uint32_t));
 
-struct SimDesc {
-  const NodeRec* rec[2];
-  const int32_t* vs[2];
-  const double* pos;
-  const int32_t* order;
-  const uint64_t* keys;         // [n] sorted Morton keys (position g: neuron order[g])
-  const int32_t* nbeg;
-  const int32_t* nend;
-  const int32_t* leaf_of;
-  int32_t own;                  // per-thread walks test for the source's own cell
-  int32_t inside;               // the octree's positions lie inside its cube
-  int32_t* err;                 // the octree's sticky device flag
-  const uint8_t* type;          // [n]
-  const int32_t* vac_axon;      // [n]
-  int64_t* elem_off;            // [n + 1] output
-  int32_t* target;              // [capacity] output
-  int64_t capacity;
-  int64_t n;
-  double L2, theta2, acc_d2, k2;  // acc_d2: accept_bound(L2, theta2)
-  uint64_t seed, step;
-  DiagOut diag;                 // nullable outputs of counting launches
-};
-
-// per-simulation status bits (device), 0 = ok
-constexpr int32_t kSimInvalid = 1;     // negative vac_axon or a type > 1
-constexpr int32_t kSimCapacity = 2;    // more searches than target capacity
-
-struct BatchDev {
-  const SimDesc* sims;          // [nsims]
-  int32_t nsims;
-  const int64_t* nbase;         // [nsims + 1] flat neuron offsets
-  int64_t* ea;                  // [total + 1] flat exclusive scan of vac_axon
-  int32_t* p0;                  // [total + 1] flat scan: excitatory sources, Morton order
-  int32_t* p1;                  // [total + 1] flat scan: inhibitory sources, Morton order
-  uint8_t* src_type;            // [total] type of the source at flat position g, 2: none
-  int32_t* tile_base;           // [nsims + 1]
-  int32_t* unit_base;           // [nsims + 1] sweep units (a tile's parts) before each
-  uint8_t* plog;                // [nsims] log2 of the parts per tile
-  int32_t* status;              // [nsims]
-  int32_t* work;                // [max_slots] source id per slot, -1 = padding
-  int64_t max_slots;
-};
-
-// Largest s with base[s] <= g (base ascending, base[0] = 0).
-template <class T>
-__device__ __forceinline__ int find_sim(const T* base, int nsims, int64_t g) {
-  int lo = 0, hi = nsims - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if ((int64_t)base[mid] <= g) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ SearchArgs args_of(const SimDesc* sims, int s, const int32_t* work) {
-  const cptr<SimDesc> d = as_const(sims) + s;
-  SearchArgs A;
-  A.rec[0] = d->rec[0];
-  A.rec[1] = d->rec[1];
-  A.vs[0] = d->vs[0];
-  A.vs[1] = d->vs[1];
-  A.pos = d->pos;
-  A.order = d->order;
-  A.nbeg = d->nbeg;
-  A.nend = d->nend;
-  A.leaf_of = d->leaf_of;
-  A.own = d->own != 0;
-  A.type = d->type;
-  A.vac_axon = d->vac_axon;
-  A.elem_off = d->elem_off;
-  A.work = work;
-  A.target = d->target;
-  A.err = d->err;
-  A.L2 = d->L2;
-  A.theta2 = d->theta2;
-  A.acc_d2 = d->acc_d2;
-  A.k2 = d->k2;
-  A.seed = d->seed;
-  A.step = d->step;
-  return A;
-}
-
-// Persistent waves pull units (parts of 64-source tiles, in tile order): first from
-// the Morton range of their own die (neighbouring sources share upper-tree nodes in
-// that die's L2), then from the other dies' ranges. A unit's simulation is found from
-// the unit bases.
+// Persistent waves take units (runs of parts of 64-source tiles, in tile order) from the
+// range of their own die (neighbouring sources share upper-tree nodes in that die's L2):
+// the first one by the wave's own index, the following ones from the die's counter, then
+// from the other dies' counters. A unit's simulation is found from the unit bases. An
+// atomic on a counter takes about 25 ns of the one memory channel that holds it, and what
+// else that channel serves waits: with all the counters in one cache line and every wave
+// asking all of them, a launch of 2 800 short units took 650 us, most of it that. The
+// counters lie 128 bytes apart, and none is asked that has nothing left.
 // Scalar registers: on this chip a wave that needs more than 80 (the count the compiler
 // reports, with VCC) leaves room for only 7 waves per SIMD, although the compiler and the
 // occupancy query both count 8 (measured: 78 give 8 resident waves per SIMD, 82 give 7).
 // The sweep hides record latency with resident waves, so it is held to 80; what does not
 // fit is kept in vector-register lanes on the rare paths (bucket leaves, thinning).
-template <bool DIAG, int SLOTS, bool OWN>
+template <bool DIAG, bool CKPT, bool OWN>
 __global__ void __launch_bounds__(kWaveBlock) __attribute__((amdgpu_num_sgpr(80)))
-search_sweep_k(BatchDev B, SweepOut W) {
+search_sweep_k(BatchDev, SweepOut) {
+  const auto K = (cptr<SweepKernargs>)__builtin_amdgcn_kernarg_segment_ptr();
   const int lane = threadIdx.x & (kWave - 1);
-  const int home = blockIdx.x % kXcd;
-  const int nunits = *W.unit_count;
-  const bool own = nunits <= W.ck_units;
-  int q = 0;
-  int prev = 0;                          // wave steps of this wave's previous unit
-  while (q < kXcd) {
-    const int qq = (home + q) % kXcd;
+  int q = park(0);
+  int prev = park(0);
+  int mine = park((int)(blockIdx.x / kXcd * (kWaveBlock / kWave) + threadIdx.x / kWave));
+  while (unpark(q) < kXcd) {
+    const cptr<SweepKernargs> Kq = again(K);
+    const int nunits = *Kq->W.unit_count;
+    const int qq = (int)((blockIdx.x + unpark(q)) % kXcd);
     const int lo = (int)((int64_t)nunits * qq / kXcd);
-    const int hi = (int)((int64_t)nunits * (qq + 1) / kXcd);
-    int got = 0;
-    if (lane == 0) got = atomicAdd(&W.queue[qq], 1);
-    got = __shfl(got, 0, kWave);
-    if (lo + got >= hi) {
-      ++q;
+    const int count = (int)((int64_t)nunits * (qq + 1) / kXcd) - lo;
+    // the die's waves take its first units by their own index
+    const int fixed = ((int)gridDim.x - qq + kXcd - 1) / kXcd * (kWaveBlock / kWave);
+    int got = unpark(mine);
+    if (got < 0) {
+      got = count;
+      if (count > fixed) {
+        int at = 0;
+        if (lane == 0) {
+          int32_t* next = &Kq->W.queue[qq * kQueueStride];
+          at = __hip_atomic_load(next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (at + fixed < count) at = atomicAdd(next, 1);
+        }
+        got = __builtin_amdgcn_readfirstlane(at) + fixed;
+      }
+    }
+    mine = park(-1);
+    if (got >= count) {
+      q = park(unpark(q) + 1);
       continue;
     }
-    const int unit = lo + got;
-    const int sim = __builtin_amdgcn_readfirstlane(
-        find_sim(as_const(B.unit_base), B.nsims, (int64_t)unit));
-    const int plog = __builtin_amdgcn_readfirstlane((int)as_const(B.plog)[sim]);
-    const int local = unit - as_const(B.unit_base)[sim];
-    const int tile = as_const(B.tile_base)[sim] + (local >> plog);
-    const int part = local & ((1 << plog) - 1);
-    const SearchArgs A = args_of(B.sims, sim, B.work);
-    // checkpoint interval: about as many checkpoints as the part has slots over a
-    // walk as long as the previous one
-    int step0 = 2 * kCkptStepMin;
-    if (SLOTS > 0 && prev > 0) {
-      // as many checkpoints per tile as without parts: a unit with a region of its
-      // own keeps the rest of its slots as headroom (no thinning in long parts)
-      step0 = kCkptStepMin;
-      while (step0 * (SLOTS >> plog) < prev) step0 <<= 1;
-    }
-    prev = sweep_tile<DIAG, SLOTS, OWN>(A, W, tile, part, plog, unit, own, lane, step0);
+    prev = park(sweep_unit<DIAG, CKPT, OWN>(again(K), lo + got, lane, unpark(prev)));
   }
 }
 
 // One thread per worklist slot (source): its elements' draws and restarts. The 64
 // slots of a wavefront form one tile, so the simulation is uniform across the wave.
-template <bool DIAG, int SLOTS, bool DEFER>
+template <bool DIAG, bool DEFER>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) search_draw_k(BatchDev B, SweepOut W) {
   const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t tile = slot / kWave;
@@ -165,8 +85,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) s
   const int sim = __builtin_amdgcn_readfirstlane(find_sim(as_const(B.tile_base), B.nsims, tile));
   const SearchArgs A = args_of(B.sims, sim, B.work);
   const int plog = __builtin_amdgcn_readfirstlane((int)as_const(B.plog)[sim]);
-  const int64_t u0 = (int64_t)as_const(B.unit_base)[sim] +
-                     ((tile - (int64_t)as_const(B.tile_base)[sim]) << plog);
+  const int nslog = __builtin_amdgcn_readfirstlane((int)as_const(B.nslog)[sim]);
+  const int64_t p0 = (tile - (int64_t)as_const(B.tile_base)[sim]) << plog;
+  const int64_t u0 = as_const(B.part_base)[sim] + p0;
+  const int64_t s0 = as_const(B.slot_base)[sim] + (p0 << nslog);
   DiagOut D{};
   if (DIAG) {
     const cptr<SimDesc> d = as_const(B.sims) + sim;
@@ -185,7 +107,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) s
                          reinterpret_cast<uint32_t*>(keep_lds + kRestartKeep * blockDim.x) +
                              threadIdx.x,
                          (int)blockDim.x};
-  draw_slot<DIAG, SLOTS, DEFER>(A, D, W, slot, u0, plog, *W.unit_count <= W.ck_units, &keep);
+  draw_slot<DIAG, DEFER>(A, D, W, slot, u0, plog, s0, nslog, &keep);
 }
 
 // Second phase of a two-phase search (one simulation): one thread per request in
@@ -317,43 +239,355 @@ struct FlatSource {             // flat Morton position g is a type-`want` sourc
   __device__ int32_t operator()(int32_t, int64_t g) const { return src_type[g] == want ? 1 : 0; }
 };
 
+// log2 of the parts of each of a simulation's `ts` tiles (force >= 0: that). A launch with
+// few tiles takes as long as the longest chain of dependent record loads in it: the more
+// parts, the shorter that is (4 096 neurons, 45 tiles: the sweep takes 25 us with 64 parts
+// per tile, 356 us with 2; 20 011 neurons, 12 % searching: 100 and 898 us). Every part
+// costs its wave a start (the ancestors of its first node, about 4 us) and the draw a
+// sum to pass over, so parts are no longer added once every wave has one: with 16 or more
+// per tile up to 16 384 parts, 60 001 neurons at theta = 0.2 take 1.78 instead of 1.87 ms,
+// but a batch of 64 simulations 13.2 instead of 11.9 ms; 8 parts of 2 000 to 16 000 tiles
+// balance the waves' loads (1.5 M neurons, 12 % searching: search 3.05 ms, with 2 parts
+// 4.0 ms; 1 M clustered neurons: 6.6 ms with 8, 7.1 ms with 2). The number depends on the
+// simulation alone, so that its results do not depend on the batch it runs in.
+__host__ __device__ inline int parts_log(int64_t ts, int force) {
+  if (force >= 0) return force;
+  int p = 0;
+  while (p < kPartLogMax && (ts << (p + 1)) <= (p + 1 > 3   ? (int64_t)kPartsFine
+                                                : p + 1 > 1 ? (int64_t)kPartsMax
+                                                            : 2 * (int64_t)kPartsMax))
+    ++p;
+  return p;
+}
+
 // Tiles per simulation: excitatory sources padded to a multiple of 64, then
-// inhibitory ones, so no tile mixes simulations or types. A simulation with few tiles
-// cuts each into 2^p parts (p <= kPartLogMax): as many as keep its units within
-// kPartUnits and, for a launch with checkpoints, within one checkpoint region per 64 of
-// its neurons (every launch has at least that many); else 2 parts where that stays
-// within 2 kPartUnits (a launch has up to twice those regions where memory allows, else
-// the two parts share their tile's region). p depends on the simulation alone, so a
-// simulation's results do not depend on the batch it runs in (force >= 0: p = force).
-// One thread. Also writes the unit count and the number of sources (the length of the
-// Hilbert sort).
-__global__ void b_tiles_k(BatchDev B, int32_t* tile_count, int32_t* unit_count,
-                          int32_t* sources, int64_t total, int force, bool ckpt) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int32_t t = 0, u = 0;
-  for (int s = 0; s < B.nsims; ++s) {
-    B.tile_base[s] = t;
-    B.unit_base[s] = u;
+// inhibitory ones, so no tile mixes simulations or types; their parts, the parts' units
+// (a launch with more than kUnitsMax parts groups 2^g consecutive parts of a tile into a
+// unit, or as many as its tile has) and the parts' checkpoint slots: twice a tile's share of
+// `ck_slots`, at least kMinSlots, halved until all fit into `ck_cap` slots (at least two
+// each). One block; a thread takes every kTilesBlock-th simulation. Also writes the tile
+// and unit counts and the number of sources (the length of the Hilbert sort).
+constexpr int kTilesBlock = kScanBlock;
+
+__global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* tile_count,
+                                                        int32_t* unit_count, int32_t* sources,
+                                                        int64_t total, int force, int ck_slots,
+                                                        int64_t ck_cap) {
+  __shared__ int64_t lds[kTilesBlock / kWave];
+  const int t = (int)threadIdx.x;
+  auto tiles = [&](int s) -> int64_t {
+    if (s >= B.nsims) return 0;
     const int64_t b = B.nbase[s], e = B.nbase[s + 1];
     const int32_t c0 = B.p0[e] - B.p0[b], c1 = B.p1[e] - B.p1[b];
-    const int32_t ts = (c0 + kWave - 1) / kWave + (c1 + kWave - 1) / kWave;
-    int p = force;
-    if (p < 0) {
-      const int64_t regions = (e - b) / kWave + 2;
-      const int64_t lim = ckpt && regions < kPartUnits ? regions : kPartUnits;
-      p = 0;
-      while (p < kPartLogMax && ((int64_t)ts << (p + 1)) <= lim) ++p;
-      if (p == 0 && 2 * (int64_t)ts <= 2 * (int64_t)kPartUnits) p = 1;
-    }
-    B.plog[s] = (uint8_t)p;
-    t += ts;
-    u += ts << p;
+    return (c0 + kWave - 1) / kWave + (c1 + kWave - 1) / kWave;
+  };
+  // the launch's parts, and its slots at ever fewer per part
+  int64_t parts = 0;
+  for (int s0 = 0; s0 < B.nsims; s0 += kTilesBlock) {
+    const int64_t ts = tiles(s0 + t);
+    int64_t tot;
+    (void)block_exclusive_scan<int64_t>(ts << parts_log(ts, force), lds, &tot);
+    parts += tot;
   }
-  B.tile_base[B.nsims] = t;
-  B.unit_base[B.nsims] = u;
-  *tile_count = t;
-  *unit_count = u;
-  *sources = B.p0[total] + B.p1[total];
+  int g = 0;
+  while (g < kPartLogMax && (parts >> g) > kUnitsMax) ++g;
+  if (force >= 0 || B.nsims == 1) g = 0;
+  auto slots = [&](int p, int cut) -> int {       // log2 of the slots per part
+    if (ck_slots == 0) return 0;
+    int want = (2 * ck_slots) >> p;
+    want = want > ck_slots ? ck_slots : want < kMinSlots ? kMinSlots : want;
+    const int l = 31 - __clz(want) - cut;
+    return l < 1 ? 1 : l;
+  };
+  int cut = 0;
+  for (; cut < 8; ++cut) {
+    int64_t sum = 0;
+    for (int s0 = 0; s0 < B.nsims; s0 += kTilesBlock) {
+      const int64_t ts = tiles(s0 + t);
+      const int p = parts_log(ts, force);
+      int64_t tot;
+      (void)block_exclusive_scan<int64_t>((ts << p) << slots(p, cut), lds, &tot);
+      sum += tot;
+    }
+    if (sum <= ck_cap) break;
+  }
+  int64_t at_t = 0, at_p = 0, at_u = 0, at_s = 0;
+  for (int s0 = 0; s0 < B.nsims; s0 += kTilesBlock) {
+    const int s = s0 + t;
+    const int64_t ts = tiles(s);
+    const int p = parts_log(ts, force);
+    const int u = p > g ? p - g : 0;
+    const int l = slots(p, cut);
+    int64_t tt, tp, tu, tl;
+    const int64_t et = block_exclusive_scan<int64_t>(ts, lds, &tt);
+    const int64_t ep = block_exclusive_scan<int64_t>(ts << p, lds, &tp);
+    const int64_t eu = block_exclusive_scan<int64_t>(ts << u, lds, &tu);
+    const int64_t el = block_exclusive_scan<int64_t>((ts << p) << l, lds, &tl);
+    if (s < B.nsims) {
+      B.tile_base[s] = (int32_t)(at_t + et);
+      B.part_base[s] = (int32_t)(at_p + ep);
+      B.unit_base[s] = (int32_t)(at_u + eu);
+      B.slot_base[s] = at_s + el;
+      B.plog[s] = (uint8_t)p;
+      B.ulog[s] = (uint8_t)u;
+      B.nslog[s] = (uint8_t)l;
+    }
+    at_t += tt;
+    at_p += tp;
+    at_u += tu;
+    at_s += tl;
+  }
+  if (t == 0) {
+    B.tile_base[B.nsims] = (int32_t)at_t;
+    B.part_base[B.nsims] = (int32_t)at_p;
+    B.unit_base[B.nsims] = (int32_t)at_u;
+    B.slot_base[B.nsims] = at_s;
+    *tile_count = (int32_t)at_t;
+    *unit_count = (int32_t)at_u;
+    *sources = B.p0[total] + B.p1[total];
+  }
+}
+
+// The cuts of a tile with 4 parts or more, one block per tile. A model of the walk says
+// how many of its steps fall on a run of sorted neurons (a run's nodes are a range of the
+// pre-order): all of the run's nodes, about 1.45 per neuron, where the run's box meets
+// the box of the tile's sources; else the cells that the walk accepts at the distance d
+// between the two boxes, whose edge is about theta d, so V / (theta d)^3 of them in the
+// run's volume V, if that is less. The model is evaluated on every run of 64 runs and,
+// where such a one holds more than a few steps, on its 64 runs; the cuts then lie on run
+// boundaries at equal shares of the steps. (A host count of the walks' steps gives the
+// longest of 64 parts 1.6-1.9 times the mean one and the longest of 8 parts 1.2 times,
+// uniform or clustered, dense or sparse sources; cuts at m +- s, 8 s and 64 s around the
+// sources' median m gave the longest of 8 parts 2.5-3.4 times, and two parts cut at m
+// 1.2-1.3 times.) Any ascending cuts give the same lists: the model only
+// balances the parts. Bound by latency where tiles are few (13 us at 45 tiles, 18 us at
+// 640), by the model's vector instructions where they are many.
+constexpr int kCutBlock = 256;
+constexpr int kFineRuns = 64;              // runs of 64 runs that are looked into, per tile
+constexpr int kCutThr = 8;                 // thresholds tried, each twice the one before
+
+__device__ __forceinline__ float run_steps(const float* __restrict__ box, int64_t stride,
+                                           int64_t r, float m, const float* lo, const float* hi,
+                                           float inv_t3) {
+  float e[3], gap[3], ext = 0.0f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float bl = box[a * stride + r], bh = box[(3 + a) * stride + r];
+    e[a] = bh - bl;
+    ext = fmaxf(ext, e[a]);
+    gap[a] = fmaxf(0.0f, fmaxf(bl - hi[a], lo[a] - bh));
+  }
+  float V = 1.0f, d2 = 0.0f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float w = fmaxf(e[a], 0.25f * ext);
+    V *= w;
+    const float q = gap[a] > 0.0f ? gap[a] + 0.25f * w : 0.0f;
+    d2 += q * q;
+  }
+  const float all = 1.45f * m;
+  return d2 > 0.0f ? fminf(all, V * inv_t3 / (d2 * sqrtf(d2))) : all;
+}
+
+// One value per thread summed over the block (every thread gets the sum).
+__device__ __forceinline__ float cut_block_sum(float v, float* lds, int lane, int wave) {
+  for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
+  if (lane == 0) lds[wave] = v;
+  __syncthreads();
+  float s = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kCutBlock / kWave; ++w) s += lds[w];
+  return s;
+}
+
+__global__ void __launch_bounds__(kCutBlock) part_cuts_k(BatchDev B, const int32_t* tile_count) {
+  __shared__ float c1[kMaxRuns1 + 1];          // steps of each run of 64 runs, then before it
+  __shared__ float c0[kFineRuns][kWave + 1];   // steps before each run of those looked into
+  __shared__ uint8_t fine[kMaxRuns1];          // 1 + its row of c0; 0: none
+  __shared__ int32_t rows[kFineRuns];
+  __shared__ float tot[2][kCutBlock / kWave];
+  __shared__ float tbox[6];
+  __shared__ int32_t above[kCutThr], nfine;
+  const int tile = (int)blockIdx.x;
+  if (tile >= *tile_count) return;
+  const int sim = __builtin_amdgcn_readfirstlane(find_sim(as_const(B.tile_base), B.nsims, tile));
+  const int plog = __builtin_amdgcn_readfirstlane((int)as_const(B.plog)[sim]);
+  if (plog < 2) return;
+  const cptr<SimDesc> d = as_const(B.sims) + sim;
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int64_t n = d->n;
+  const int log = d->run_log;
+  const int64_t r0 = (n + ((int64_t)1 << log) - 1) >> log;
+  const int nr = (int)((n + ((int64_t)64 << log) - 1) >> (log + 6));   // <= kMaxRuns1
+  if (wave == 0) {
+    // the box of the tile's sources, in grid cells
+    const int32_t i = B.work[(int64_t)tile * kWave + lane];
+    float lo[3] = {3e38f, 3e38f, 3e38f}, hi[3] = {-3e38f, -3e38f, -3e38f};
+    if (i >= 0) {
+      const double* p = d->pos + 3 * (int64_t)i;
+      const double o[3] = {d->x0, d->y0, d->z0};
+      const double s = 2097152.0 / d->edge;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double f = (p[a] - o[a]) * s;
+        lo[a] = hi[a] = (float)(f < 0.0 ? 0.0 : f > 2097151.0 ? 2097151.0 : f);
+      }
+    }
+    for (int k = 1; k < kWave; k <<= 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = fminf(lo[a], __shfl_xor(lo[a], k, kWave));
+        hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], k, kWave));
+      }
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        tbox[a] = lo[a];
+        tbox[3 + a] = hi[a];
+      }
+    }
+  }
+  if (t < kCutThr) above[t] = 0;
+  if (t == 0) nfine = 0;
+  __syncthreads();
+  float lo[3], hi[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = tbox[a];
+    hi[a] = tbox[3 + a];
+  }
+  const double theta = sqrt(d->theta2);
+  const float inv_t3 = (float)(1.0 / fmax(theta * d->theta2, 1e-30));
+  float sum = 0.0f;
+  for (int r = t; r < nr; r += kCutBlock) {
+    const int64_t left = n - ((int64_t)r << (log + 6));
+    const int64_t m = left < ((int64_t)64 << log) ? left : ((int64_t)64 << log);
+    const float c = run_steps(d->box[1], nr, r, (float)m, lo, hi, inv_t3);
+    c1[r] = c;
+    fine[r] = 0;
+    sum += c;
+  }
+  sum = cut_block_sum(sum, tot[0], lane, wave);
+  // look into the runs of 64 runs with more than 1/32 of a part's steps (at least 16),
+  // or the first doubling of it that at most kFineRuns of them exceed
+  const float thr0 = fmaxf(16.0f, sum * (0.03125f / (float)(1 << plog)));
+  for (int r = t; r < nr; r += kCutBlock) {
+    const float c = c1[r];
+    float thr = thr0;
+    for (int k = 0; k < kCutThr && c > thr; ++k) {
+      atomicAdd(&above[k], 1);
+      thr *= 2.0f;
+    }
+  }
+  __syncthreads();
+  float thr = thr0;
+  int pick = 0;
+  while (pick < kCutThr && above[pick] > kFineRuns) {
+    ++pick;
+    thr *= 2.0f;
+  }
+  for (int r = t; r < nr; r += kCutBlock) {
+    if (c1[r] > thr) {
+      const int at = atomicAdd(&nfine, 1);
+      if (at < kFineRuns) {
+        rows[at] = r;
+        fine[r] = (uint8_t)(at + 1);
+      }
+    }
+  }
+  __syncthreads();
+  const int nf = nfine < kFineRuns ? nfine : kFineRuns;
+  constexpr int kRows = 4;                 // rows a wave reads at once
+  for (int f0 = wave * kRows; f0 < nf; f0 += kRows * kCutBlock / kWave) {
+    float c[kRows], x[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const int f = f0 + u < nf ? f0 + u : nf - 1;
+      const int64_t run = (int64_t)rows[f] * 64 + lane;
+      const int64_t left = n - (run << log);
+      const float m = (float)(left < ((int64_t)1 << log) ? left : (int64_t)1 << log);
+      c[u] = run_steps(d->box[0], r0, run < r0 ? run : r0 - 1, m, lo, hi, inv_t3);
+      c[u] = run < r0 ? c[u] : 0.0f;
+      x[u] = c[u];
+    }
+    for (int o = 1; o < kWave; o <<= 1) {
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const float y = __shfl_up(x[u], o, kWave);
+        if (lane >= o) x[u] += y;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      if (f0 + u >= nf) break;
+      c0[f0 + u][lane + 1] = x[u];
+      if (lane == 0) c0[f0 + u][0] = 0.0f;
+      if (lane == kWave - 1) c1[rows[f0 + u]] = x[u];
+    }
+  }
+  __syncthreads();
+  // the steps before each run of 64 runs, each thread kPer consecutive ones
+  constexpr int kPer = kMaxRuns1 / kCutBlock;
+  float v[kPer], s = 0.0f;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int r = t * kPer + q;
+    v[q] = r < nr ? c1[r] : 0.0f;
+    s += v[q];
+  }
+  float x = s;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const float y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  if (lane == kWave - 1) tot[1][wave] = x;
+  __syncthreads();
+  float before = x - s, total = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kCutBlock / kWave; ++w) {
+    before += w < wave ? tot[1][w] : 0.0f;
+    total += tot[1][w];
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    c1[t * kPer + q] = before;
+    before += v[q];
+  }
+  if (t == kCutBlock - 1) c1[kMaxRuns1] = before;
+  __syncthreads();
+  if (t >= 1 << plog) return;
+  const uint32_t root = d->rec[0][0].meta;
+  const int32_t end = (root & kLeafBit) ? 1 : (int32_t)(root & kSkipMask);
+  int32_t cut = 1;
+  if (t > 0) {
+    const float want = total * ((float)t / (float)(1 << plog));
+    int a = 0, b = nr - 1;               // the run of 64 runs that holds it
+    while (a < b) {
+      const int mid = (a + b + 1) >> 1;
+      if (c1[mid] <= want) a = mid; else b = mid - 1;
+    }
+    const float have = want - c1[a];
+    int64_t m;
+    if (fine[a]) {
+      const float* row = c0[fine[a] - 1];
+      int k = 0;
+      for (int o = kWave / 2; o > 0; o >>= 1) k += row[k + o] <= have ? o : 0;
+      m = ((int64_t)a * 64 + k + (have - row[k] > 0.5f * (row[k + 1] - row[k]) ? 1 : 0)) << log;
+    } else {
+      m = (int64_t)(a + (have > 0.5f * (c1[a + 1] - c1[a]) ? 1 : 0)) << (log + 6);
+    }
+    if (m >= n) {
+      cut = end;
+    } else if (m > 0) {
+      // the first node that starts at sorted neuron m
+      const int32_t leaf = d->leaf_at[m];
+      cut = leaf - ((int32_t)d->depth[leaf] - common_digits(d->keys[m - 1], d->keys[m]) - 1);
+      cut = cut < 1 ? 1 : cut > end ? end : cut;
+    }
+  }
+  const int64_t p = (int64_t)(tile - B.tile_base[sim]) << plog;
+  B.cuts[B.part_base[sim] + p + t] = cut;
 }
 
 // Hilbert index of a cell of the 2^21 grid (J. Skilling, "Programming the Hilbert
@@ -442,10 +676,24 @@ __global__ void b_work_sorted_k(BatchDev B, int64_t total, const int32_t* __rest
 // ---------------------------------------------------------------------------
 // Scratch layout (device), carved from one buffer.
 // ---------------------------------------------------------------------------
+// What the working memory of a search is sized by: `slots` checkpoints aimed at per tile
+// (0: no checkpoints, for launches without draws) and ck_cap checkpoint slots in all; force
+// >= 0: every tile has 2^force parts; counts: a launch that counts visits and opens.
+struct SearchSize {
+  int64_t total_n;
+  int nsims;
+  int slots;
+  int64_t ck_cap;
+  int force;
+  bool counts;
+};
+
 struct SearchScratch {
+  SearchSize q;
   BatchDev B;
   SweepOut W;
-  int32_t* counters;            // [0] tile count, [1..8] die queues, [9] sources, [10] units
+  int32_t* counters;            // [0] tile count, [1] sources, [2] units, then the dies'
+                                // queues, kQueueStride apart
   void* scan_tmp;
   uint64_t* hkey[2];            // [total_n] sort keys of the Hilbert-ordered worklist
   int32_t* hval[2];             // [total_n] their flat positions
@@ -455,95 +703,111 @@ struct SearchScratch {
 
 inline int64_t max_tiles_for(int64_t total_n, int nsims) { return total_n / kWave + 2 * nsims + 1; }
 
-// Sweep units: a simulation has at most 2^kPartLogMax units per tile, and more units
-// than tiles only while they stay within kPartUnits or, with 2 parts, while its tiles do;
-// with the parts forced to 2^force (force >= 0), exactly that many per tile.
-inline int64_t max_units_for(int64_t total_n, int nsims, int force = -1) {
+// Parts of all tiles (see parts_log), of at most mt tiles; with the parts forced to
+// 2^force (force >= 0), exactly that many per tile.
+inline int64_t max_parts_for(int64_t total_n, int nsims, int force = -1) {
   const int64_t mt = max_tiles_for(total_n, nsims);
   if (force >= 0) return mt << force;
-  return std::min(mt << kPartLogMax, mt + (int64_t)nsims * kPartUnits);
+  // per simulation of ts tiles: ts, or 2 ts <= 2 kPartsMax, or 8 ts <= kPartsMax, or
+  // 64 ts <= kPartsFine
+  const int64_t two = std::max(mt, std::min(mt << 1, (int64_t)nsims * 2 * kPartsMax)),
+                eight = std::min(mt << 3, (int64_t)nsims * kPartsMax),
+                fine = std::min(mt << kPartLogMax, (int64_t)nsims * kPartsFine);
+  return nsims == 1 ? std::max(two, std::max(eight, fine))
+                    : std::min(mt << kPartLogMax, two + eight + fine);
+}
+
+// Sweep units of all tiles: the parts, in a batch grouped to about kUnitsMax.
+inline int64_t max_units_for(int64_t total_n, int nsims, int force = -1) {
+  const int64_t mp = max_parts_for(total_n, nsims, force);
+  if (force >= 0 || nsims == 1) return mp;
+  return std::min(mp, std::max<int64_t>(kUnitsMax, max_tiles_for(total_n, nsims)));
 }
 
 struct ScratchSizes {
-  size_t ea, p, tile_base, unit_base, plog, status, work, Z, v, nck, ckx, ckP, ckme, counters,
+  size_t ea, p, base, slot_base, log, status, work, Z, v, nck, cuts, ckx, ckP, ckme, counters,
       scan, srct, hkey, hval, hsort, total;
 };
 
-// Checkpoint bytes per slot of a tile: the wave position and, per lane, the running
-// sum and the mask end.
+// Checkpoint bytes per slot: the wave position and, per lane, the running sum and the
+// mask end.
 constexpr size_t kCkptSlotBytes = sizeof(int32_t) + kWave * (sizeof(double) + sizeof(int32_t));
 
-// `slots` checkpoint slots per tile (0: no checkpoints, for launches without draws).
-// regions: checkpoint regions of `slots` slots (< 0: one per tile).
-inline ScratchSizes scratch_sizes(int64_t total_n, int nsims, int slots, int force = -1,
-                                  int64_t regions = -1) {
+inline ScratchSizes scratch_sizes(const SearchSize& q) {
   ScratchSizes z;
-  const int64_t mt = max_tiles_for(total_n, nsims);
+  const int64_t mt = max_tiles_for(q.total_n, q.nsims);
   const int64_t ms = mt * kWave;
-  const int64_t mu = max_units_for(total_n, nsims, force);
-  z.ea = align_up(sizeof(int64_t) * (total_n + 1));
-  z.p = align_up(sizeof(int32_t) * (total_n + 1));
-  z.tile_base = align_up(sizeof(int32_t) * (nsims + 1));
-  z.unit_base = align_up(sizeof(int32_t) * (nsims + 1));
-  z.plog = align_up(sizeof(uint8_t) * nsims);
-  z.status = align_up(sizeof(int32_t) * nsims);
+  const int64_t mp = max_parts_for(q.total_n, q.nsims, q.force);
+  const bool ck = q.slots > 0;
+  z.ea = align_up(sizeof(int64_t) * (q.total_n + 1));
+  z.p = align_up(sizeof(int32_t) * (q.total_n + 1));
+  z.base = align_up(sizeof(int32_t) * (q.nsims + 1));
+  z.slot_base = align_up(sizeof(int64_t) * (q.nsims + 1));
+  z.log = align_up(sizeof(uint8_t) * q.nsims);
+  z.status = align_up(sizeof(int32_t) * q.nsims);
   z.work = align_up(sizeof(int32_t) * ms);
-  z.Z = align_up(sizeof(double) * mu * kWave);
-  z.v = align_up(sizeof(int32_t) * mu * kWave);
-  z.nck = align_up(sizeof(int32_t) * mu);
-  const int64_t mr = regions < 0 ? mt : regions;
-  z.ckx = align_up(sizeof(int32_t) * mr * slots);
-  z.ckP = align_up(sizeof(double) * mr * slots * kWave);
-  z.ckme = align_up(sizeof(int32_t) * mr * slots * kWave);
-  z.counters = align_up(sizeof(int32_t) * (3 + kXcd));
-  z.scan = align_up(std::max(scan_tmp_bytes<int64_t>(total_n), scan_tmp_bytes<int32_t>(total_n)));
-  z.srct = align_up(sizeof(uint8_t) * total_n);
-  z.hkey = align_up(sizeof(uint64_t) * total_n);
-  z.hval = align_up(sizeof(int32_t) * total_n);
-  z.hsort = align_up(radix_sort_ws_bytes(total_n));
-  z.total = z.ea + 2 * z.p + z.tile_base + z.unit_base + z.plog + z.status + z.work + z.Z +
-            3 * z.v + z.nck + z.ckx +
-            z.ckP + z.ckme + z.counters + z.scan + z.srct + 2 * z.hkey + 2 * z.hval + z.hsort;
+  z.Z = align_up(sizeof(double) * mp * kWave);
+  z.v = q.counts ? align_up(sizeof(int32_t) * mp * kWave) : 0;
+  z.nck = ck ? align_up(sizeof(int32_t) * mp) : 0;
+  z.cuts = align_up(sizeof(int32_t) * mp);
+  z.ckx = ck ? align_up(sizeof(int32_t) * q.ck_cap) : 0;
+  z.ckP = ck ? align_up(sizeof(double) * q.ck_cap * kWave) : 0;
+  z.ckme = ck ? align_up(sizeof(int32_t) * q.ck_cap * kWave) : 0;
+  z.counters = align_up(sizeof(int32_t) * kCounters);
+  z.scan = align_up(std::max(scan_tmp_bytes<int64_t>(q.total_n),
+                             scan_tmp_bytes<int32_t>(q.total_n)));
+  z.srct = align_up(sizeof(uint8_t) * q.total_n);
+  z.hkey = align_up(sizeof(uint64_t) * q.total_n);
+  z.hval = align_up(sizeof(int32_t) * q.total_n);
+  z.hsort = align_up(radix_sort_ws_bytes(q.total_n));
+  z.total = z.ea + 2 * z.p + 3 * z.base + z.slot_base + 3 * z.log + z.status + z.work + z.Z +
+            3 * z.v + z.nck + z.cuts + z.ckx + z.ckP + z.ckme + z.counters + z.scan + z.srct +
+            2 * z.hkey + 2 * z.hval + z.hsort;
   return z;
 }
 
-inline SearchScratch carve(void* base, int64_t total_n, int nsims, int slots,
-                           const SimDesc* d_sims, const int64_t* d_nbase, int force = -1,
-                           int64_t regions = -1) {
-  const ScratchSizes z = scratch_sizes(total_n, nsims, slots, force, regions);
+inline SearchScratch carve(void* base, const SearchSize& q, const SimDesc* d_sims,
+                           const int64_t* d_nbase) {
+  const ScratchSizes z = scratch_sizes(q);
   char* p = static_cast<char*>(base);
   auto take = [&](size_t bytes) {
-    char* q = p;
+    char* r = bytes ? p : nullptr;
     p += bytes;
-    return q;
+    return r;
   };
   SearchScratch S{};
+  S.q = q;
   S.B.sims = d_sims;
-  S.B.nsims = nsims;
+  S.B.nsims = q.nsims;
   S.B.nbase = d_nbase;
   S.B.ea = reinterpret_cast<int64_t*>(take(z.ea));
   S.B.p0 = reinterpret_cast<int32_t*>(take(z.p));
   S.B.p1 = reinterpret_cast<int32_t*>(take(z.p));
-  S.B.tile_base = reinterpret_cast<int32_t*>(take(z.tile_base));
-  S.B.unit_base = reinterpret_cast<int32_t*>(take(z.unit_base));
-  S.B.plog = reinterpret_cast<uint8_t*>(take(z.plog));
+  S.B.tile_base = reinterpret_cast<int32_t*>(take(z.base));
+  S.B.part_base = reinterpret_cast<int32_t*>(take(z.base));
+  S.B.unit_base = reinterpret_cast<int32_t*>(take(z.base));
+  S.B.slot_base = reinterpret_cast<int64_t*>(take(z.slot_base));
+  S.B.plog = reinterpret_cast<uint8_t*>(take(z.log));
+  S.B.ulog = reinterpret_cast<uint8_t*>(take(z.log));
+  S.B.nslog = reinterpret_cast<uint8_t*>(take(z.log));
   S.B.status = reinterpret_cast<int32_t*>(take(z.status));
   S.B.work = reinterpret_cast<int32_t*>(take(z.work));
-  S.B.max_slots = max_tiles_for(total_n, nsims) * kWave;
+  S.B.max_slots = max_tiles_for(q.total_n, q.nsims) * kWave;
   S.W.Z = reinterpret_cast<double*>(take(z.Z));
   S.W.v0 = reinterpret_cast<int32_t*>(take(z.v));
   S.W.o0 = reinterpret_cast<int32_t*>(take(z.v));
   S.W.e0 = reinterpret_cast<int32_t*>(take(z.v));
   S.W.nck = reinterpret_cast<int32_t*>(take(z.nck));
+  S.B.cuts = reinterpret_cast<int32_t*>(take(z.cuts));
   S.W.ck_x = reinterpret_cast<int32_t*>(take(z.ckx));
   S.W.ck_P = reinterpret_cast<double*>(take(z.ckP));
   S.W.ck_me = reinterpret_cast<int32_t*>(take(z.ckme));
-  S.W.ck_slots = slots;
-  S.W.ck_units = regions < 0 ? max_tiles_for(total_n, nsims) : regions;
+  S.W.ck_slots = q.slots;
+  S.W.ck_cap = q.ck_cap;
   S.counters = reinterpret_cast<int32_t*>(take(z.counters));
   S.W.tile_count = S.counters;
-  S.W.unit_count = S.counters + 2 + kXcd;
-  S.W.queue = S.counters + 1;
+  S.W.unit_count = S.counters + 2;
+  S.W.queue = S.counters + kQueueStride;
   S.W.wave_steps = nullptr;
   S.own_cell = true;
   S.scan_tmp = take(z.scan);
@@ -556,16 +820,15 @@ inline SearchScratch carve(void* base, int64_t total_n, int nsims, int slots,
   return S;
 }
 
-// Preparation: status, CSR offsets, worklists, tile and unit bases. Kernels only.
-// force >= 0: every tile has 2^force parts (the scratch carved for it). ckpt: the
-// sweep will write checkpoints.
-inline hipError_t enqueue_prep(SearchScratch& S, int64_t total_n, hipStream_t s, int force = -1,
-                               bool ckpt = true) {
+// Preparation: status, CSR offsets, worklists, tile, part and unit bases, the parts' cuts.
+// Kernels only.
+inline hipError_t enqueue_prep(SearchScratch& S, hipStream_t s) {
   BatchDev& B = S.B;
+  const int64_t total_n = S.q.total_n;
   const unsigned g = grid_for(total_n, 256);
   fill_i32_k<<<grid_for(B.nsims, 256), 256, 0, s>>>(B.status, B.nsims, 0);
   fill_i32_k<<<grid_for(B.max_slots, 256), 256, 0, s>>>(B.work, B.max_slots, -1);
-  fill_i32_k<<<1, 64, 0, s>>>(S.counters, 3 + kXcd, 0);
+  fill_i32_k<<<grid_for(kCounters, 256), 256, 0, s>>>(S.counters, kCounters, 0);
   b_check_k<<<g, 256, 0, s>>>(B, total_n);
   hipError_t e = exclusive_scan<int64_t, int32_t, FlatAxon>(nullptr, B.ea, total_n, FlatAxon{B},
                                                              true, s, S.scan_tmp);
@@ -578,8 +841,8 @@ inline hipError_t enqueue_prep(SearchScratch& S, int64_t total_n, hipStream_t s,
   e = exclusive_scan<int32_t, int32_t, FlatSource>(nullptr, B.p1, total_n,
                                                    FlatSource{B.src_type, 1}, true, s, S.scan_tmp);
   if (e != hipSuccess) return e;
-  b_tiles_k<<<1, 64, 0, s>>>(B, S.counters, S.counters + 2 + kXcd, S.counters + 1 + kXcd,
-                             total_n, force, ckpt);
+  b_tiles_k<<<1, kTilesBlock, 0, s>>>(B, S.counters, S.counters + 2, S.counters + 1, total_n,
+                                      S.q.force, S.W.ck_slots, S.W.ck_cap);
   // 64-source tiles in Hilbert order within each (simulation, type) group
   // (32-bit keys keep 20 or more Hilbert bits, cells of about a hundredth of the box
   // edge or finer, for up to 2048 simulations)
@@ -588,54 +851,50 @@ inline hipError_t enqueue_prep(SearchScratch& S, int64_t total_n, hipStream_t s,
   const int kb = gb <= 12 ? 32 : 48;
   b_hkeys_k<<<g, 256, 0, s>>>(B, total_n, gb, kb, S.hkey[0], S.hval[0]);
   e = radix_sort_pairs_ws(S.hkey[0], S.hval[0], S.hkey[1], S.hval[1], total_n, kb, s, S.hsort,
-                          S.counters + 1 + kXcd);
+                          S.counters + 1);
   if (e != hipSuccess) return e;
   b_work_sorted_k<<<g, 256, 0, s>>>(B, total_n, S.hval[0]);
+  // a simulation with 4 parts per tile or more has at most kPartsMax / 4 tiles, unless forced
+  int64_t tiles = max_tiles_for(total_n, B.nsims);
+  if (S.q.force < 0) tiles = B.nsims == 1 ? std::min<int64_t>(tiles, kPartsMax / 4) : tiles;
+  if (S.q.force < 0 || S.q.force >= 2)
+    part_cuts_k<<<(unsigned)tiles, kCutBlock, 0, s>>>(B, S.counters);
   return hipGetLastError();
 }
 
 // The sweep and draw launches. `sweep_blocks` persistent blocks; the draw covers
 // every possible slot (threads past the tile count return at once).
-template <bool DIAG, int SLOTS>
+template <bool DIAG, bool CKPT>
 inline void launch_sweep(const SearchScratch& S, unsigned blocks, hipStream_t s) {
   if (S.own_cell)
-    search_sweep_k<DIAG, SLOTS, true><<<blocks, kWaveBlock, 0, s>>>(S.B, S.W);
+    search_sweep_k<DIAG, CKPT, true><<<blocks, kWaveBlock, 0, s>>>(S.B, S.W);
   else
-    search_sweep_k<DIAG, SLOTS, false><<<blocks, kWaveBlock, 0, s>>>(S.B, S.W);
+    search_sweep_k<DIAG, CKPT, false><<<blocks, kWaveBlock, 0, s>>>(S.B, S.W);
 }
 
-template <bool DIAG, int SLOTS>
+template <bool DIAG>
 inline void launch_draw(const SearchScratch& S, unsigned grid, int block, hipStream_t s) {
   if (S.W.defer.depth < kNoDefer)
-    search_draw_k<DIAG, SLOTS, true><<<grid, block, kRestartLds * block, s>>>(S.B, S.W);
+    search_draw_k<DIAG, true><<<grid, block, kRestartLds * block, s>>>(S.B, S.W);
   else
-    search_draw_k<DIAG, SLOTS, false><<<grid, block, kRestartLds * block, s>>>(S.B, S.W);
+    search_draw_k<DIAG, false><<<grid, block, kRestartLds * block, s>>>(S.B, S.W);
 }
 
 inline hipError_t enqueue_search(SearchScratch& S, bool diag, unsigned sweep_blocks,
                                  int draw_block, hipStream_t s, hipEvent_t mid = nullptr) {
   const unsigned draw_grid = grid_for(S.B.max_slots, draw_block);
-  const bool big = S.W.ck_slots == kCkptMax;
-  if (diag && big)
-    launch_sweep<true, kCkptMax>(S, sweep_blocks, s);
-  else if (diag)
-    launch_sweep<true, kCkptMin>(S, sweep_blocks, s);
-  else if (big)
-    launch_sweep<false, kCkptMax>(S, sweep_blocks, s);
+  if (diag)
+    launch_sweep<true, true>(S, sweep_blocks, s);
   else
-    launch_sweep<false, kCkptMin>(S, sweep_blocks, s);
+    launch_sweep<false, true>(S, sweep_blocks, s);
   if (mid) {
     hipError_t e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
   }
-  if (diag && big)
-    launch_draw<true, kCkptMax>(S, draw_grid, draw_block, s);
-  else if (diag)
-    launch_draw<true, kCkptMin>(S, draw_grid, draw_block, s);
-  else if (big)
-    launch_draw<false, kCkptMax>(S, draw_grid, draw_block, s);
+  if (diag)
+    launch_draw<true>(S, draw_grid, draw_block, s);
   else
-    launch_draw<false, kCkptMin>(S, draw_grid, draw_block, s);
+    launch_draw<false>(S, draw_grid, draw_block, s);
   return hipGetLastError();
 }
 

@@ -242,4 +242,89 @@ __global__ void __launch_bounds__(kBuildBlock) init_meta_k(const int32_t* __rest
   r1[x] = r;
 }
 
+// Boxes of runs of consecutive sorted neurons, in grid cells: runs of 2^run_log(n)
+// neurons and runs of 64 such runs. They tell how the steps of a tile's walk spread over
+// the pre-order (see part_cuts_k). Each is 6 arrays (x, y, z minima, then maxima) over
+// the runs, so that the lanes of a wave read neighbouring runs coalesced.
+constexpr int kRunLogMin = 3;
+constexpr int64_t kMaxRuns1 = 1024;        // runs of 64 runs: at most this many
+
+inline int64_t runs_of(int64_t n, int log) { return (n + ((int64_t)1 << log) - 1) >> log; }
+
+inline int run_log(int64_t n) {
+  int b = kRunLogMin;
+  while (runs_of(n, 6 + b) > kMaxRuns1) ++b;
+  return b;
+}
+
+__device__ __forceinline__ uint32_t gather3(uint64_t v) {   // every third bit -> 21 bits
+  v &= 0x1249249249249249ull;
+  v = (v | (v >> 2)) & 0x10C30C30C30C30C3ull;
+  v = (v | (v >> 4)) & 0x100F00F00F00F00Full;
+  v = (v | (v >> 8)) & 0x1F0000FF0000FFull;
+  v = (v | (v >> 16)) & 0x1F00000000FFFFull;
+  v = (v | (v >> 32)) & 0x1FFFFFull;
+  return (uint32_t)v;
+}
+
+// One block per run of 64 runs. Bound by reading the keys once (8 B per neuron); the
+// minima and maxima go across the lanes of a run, then across the runs through LDS.
+__global__ void __launch_bounds__(kBuildBlock) boxes_k(const uint64_t* __restrict__ keys,
+                                                      int64_t n, int log, int64_t r0, int64_t r1,
+                                                      float* __restrict__ box0,
+                                                      float* __restrict__ box1) {
+  __shared__ uint32_t b[6][64];
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const int wave = (int)(threadIdx.x / kWave);
+  const int64_t first = ((int64_t)blockIdx.x * 64) << log;      // the block's neurons
+  const int per = log < 6 ? 6 - log : 0;                         // log2 of runs per pass
+  const int passes = log < 6 ? 1 : 1 << (log - 6);               // passes per run
+  for (int r = wave << per; r < 64; r += (kBuildBlock / kWave) << per) {
+    uint32_t lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0, 0, 0};
+    for (int q = 0; q < passes; ++q) {
+      const int64_t p = first + ((int64_t)r << log) + (int64_t)q * kWave + lane;
+      if (p < n) {
+        const uint64_t k = keys[p];
+        const uint32_t c[3] = {gather3(k >> 2), gather3(k >> 1), gather3(k)};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          lo[a] = c[a] < lo[a] ? c[a] : lo[a];
+          hi[a] = c[a] > hi[a] ? c[a] : hi[a];
+        }
+      }
+    }
+    const int span = log < 6 ? 1 << log : kWave;
+    for (int o = 1; o < span; o <<= 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const uint32_t l = (uint32_t)__shfl_xor((int)lo[a], o, kWave);
+        const uint32_t h = (uint32_t)__shfl_xor((int)hi[a], o, kWave);
+        lo[a] = l < lo[a] ? l : lo[a];
+        hi[a] = h > hi[a] ? h : hi[a];
+      }
+    }
+    if ((lane & (span - 1)) == 0) {
+      const int k = r + (log < 6 ? lane >> log : 0);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        b[a][k] = lo[a];
+        b[3 + a][k] = hi[a];
+      }
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const int64_t run = (int64_t)blockIdx.x * 64 + lane;
+#pragma unroll
+  for (int a = 0; a < 6; ++a) {
+    uint32_t v = b[a][lane];
+    if (run < r0) box0[(int64_t)a * r0 + run] = (float)v;       // 21 bits: exact
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t w = (uint32_t)__shfl_xor((int)v, o, kWave);
+      v = a < 3 ? (w < v ? w : v) : (w > v ? w : v);
+    }
+    if (lane == 0) box1[(int64_t)a * r1 + blockIdx.x] = (float)v;
+  }
+}
+
 }  // namespace msp

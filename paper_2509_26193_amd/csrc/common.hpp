@@ -67,6 +67,7 @@ struct msp_octree_s {
   int64_t level_off[msp::kMaxDepth + 2];   // runs of level_nodes (inner nodes only)
   msp::NodeRec* rec[2];  // [N + 1] per type (index N: zero sentinel, never visited)
   int32_t* vs[2];        // [n] per type: counts in sorted order (bucket members)
+  float* box[2];         // boxes of runs of sorted neurons (see boxes_k): 6 arrays each
   int32_t* err;          // [1] sticky device error flags
   bool refreshed;
   bool inside;           // every position lies in the closed cube, and the cube lies

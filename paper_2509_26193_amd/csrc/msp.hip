@@ -33,6 +33,9 @@ void carve_neurons(msp_octree_s* t, char* base, size_t* bytes) {
   t->leaf_at = c.take<int32_t>(n);
   t->vs[0] = c.take<int32_t>(n);
   t->vs[1] = c.take<int32_t>(n);
+  const int log = run_log(n);
+  t->box[0] = c.take<float>(6 * runs_of(n, log));
+  t->box[1] = c.take<float>(6 * runs_of(n, log + 6));
   t->err = c.take<int32_t>(1);
   *bytes = c.off;
 }
@@ -95,6 +98,15 @@ SimDesc make_desc(const msp_octree_s* t, const uint8_t* neuron_type, const int32
   d.nbeg = t->nbeg;
   d.nend = t->nend;
   d.leaf_of = t->leaf_of;
+  d.leaf_at = t->leaf_at;
+  d.depth = t->depth;
+  d.box[0] = t->box[0];
+  d.box[1] = t->box[1];
+  d.run_log = run_log(t->n);
+  d.x0 = t->box_min[0];
+  d.y0 = t->box_min[1];
+  d.z0 = t->box_min[2];
+  d.edge = t->box_edge;
   d.own = own_cell_needed(t, theta) ? 1 : 0;
   d.inside = t->inside ? 1 : 0;
   d.err = t->err;
@@ -126,8 +138,8 @@ hipError_t sweep_blocks_for(int device, bool diag, int64_t max_units, double fra
   if (e != hipSuccess) return e;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
       &per_cu,
-      diag ? (const void*)search_sweep_k<true, kCkptMax, true>
-           : (const void*)search_sweep_k<false, kCkptMax, true>,
+      diag ? (const void*)search_sweep_k<true, true, true>
+           : (const void*)search_sweep_k<false, true, true>,
       kWaveBlock, 0);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
@@ -139,13 +151,13 @@ hipError_t sweep_blocks_for(int device, bool diag, int64_t max_units, double fra
   return hipSuccess;
 }
 
-// Checkpoint slots per region: kCkptMax if one region per tile fits in an eighth of the
-// device's memory, else kCkptMin. More slots mean shorter re-walks in the draw kernel;
-// the targets do not depend on the choice. Regions: one per tile, and as many more as
-// that eighth holds up to twice that (automatic parts) or the forced parts' units, so
-// that most launches cut into parts give every part a region of its own.
-hipError_t ck_slots_for(int device, int64_t total_n, int nsims, int force, int* slots_out,
-                        int64_t* regions_out) {
+// The checkpoints of a search: kCkptMax aimed at per tile if that many slots per tile fit
+// in an eighth of the device's memory, else kCkptMin. More slots mean shorter re-walks in
+// the draw kernel; the targets do not depend on the choice. Slots in all: as many per
+// tile, and as many more as that eighth holds up to twice that (the forced parts' share,
+// where parts are forced) or kMinSlots for each part of a launch with few tiles.
+hipError_t search_size(int device, int64_t total_n, int nsims, int force, bool counts,
+                       SearchSize* out) {
   static size_t mem[64] = {};
   if (device < 0 || device >= 64) return hipErrorInvalidDevice;
   if (mem[device] == 0) {
@@ -157,10 +169,11 @@ hipError_t ck_slots_for(int device, int64_t total_n, int nsims, int force, int* 
   const int64_t mt = max_tiles_for(total_n, nsims);
   const double budget = (double)(mem[device] / 8);
   const int slots = (double)mt * kCkptMax * (double)kCkptSlotBytes <= budget ? kCkptMax : kCkptMin;
-  const int64_t want = force >= 0 ? (mt << force) : 2 * mt;
-  const int64_t fit = (int64_t)(budget / ((double)slots * (double)kCkptSlotBytes));
-  *slots_out = slots;
-  *regions_out = std::max(mt, std::min(want, fit));
+  const int64_t fine = std::min(mt << kPartLogMax, (int64_t)nsims * kPartsFine) * kMinSlots;
+  const int64_t want = force >= 0 ? (mt << force) * slots : std::max(2 * mt * slots, fine);
+  const int64_t fit = (int64_t)(budget / (double)kCkptSlotBytes);
+  *out = SearchSize{total_n, nsims, slots, std::max(mt * slots, std::min(want, fit)), force,
+                    counts};
   return hipSuccess;
 }
 
@@ -412,6 +425,9 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
                                                              t->nbeg, t->nend, t->leaf_of,
                                                              t->leaf_at);
     TRY(hipGetLastError());
+    const int log = run_log(n);
+    boxes_k<<<(unsigned)runs_of(n, log + 6), kBuildBlock, 0, s>>>(
+        t->keys, n, log, runs_of(n, log), runs_of(n, log + 6), t->box[0], t->box[1]);
     TRY(hipGetLastError());
     level_count_k<<<grid_for(N, kBuildBlock * kLevelItems), kBuildBlock, 0, s>>>(t->depth, t->skip,
                                                                                 N, lcnt);
@@ -512,13 +528,12 @@ msp_status msp_find_targets_diag(msp_octree t, const uint8_t* neuron_type,
     if (pp != 1 && pp != 2 && pp != 4 && pp != 8) return MSP_ERR_INVALID;
     force = pp == 1 ? 0 : pp == 2 ? 1 : pp == 4 ? 2 : 3;
   }
-  int slots = 0;
-  int64_t regions = 0;
-  MSP_HIP_TRY(ck_slots_for(t->device, n, 1, force, &slots, &regions));
+  SearchSize size;
+  MSP_HIP_TRY(search_size(t->device, n, 1, force, any, &size));
   WorkspaceLease ws(t->device);
   void* scratch = nullptr;
   // the workspace also holds the simulation descriptor and the neuron bases
-  const size_t body = scratch_sizes(n, 1, slots, force, regions).total;
+  const size_t body = scratch_sizes(size).total;
   MSP_HIP_TRY(ws.acquire(body + align_up(sizeof(SimDesc)) + align_up(sizeof(hbase)), s,
                          &scratch));
   SimDesc* dsim = reinterpret_cast<SimDesc*>(static_cast<char*>(scratch) + body);
@@ -526,10 +541,10 @@ msp_status msp_find_targets_diag(msp_octree t, const uint8_t* neuron_type,
                                               align_up(sizeof(SimDesc)));
   MSP_HIP_TRY(hipMemcpyAsync(dsim, &h, sizeof(SimDesc), hipMemcpyHostToDevice, s));
   MSP_HIP_TRY(hipMemcpyAsync(dbase, hbase, sizeof(hbase), hipMemcpyHostToDevice, s));
-  SearchScratch S = carve(scratch, n, 1, slots, dsim, dbase, force, regions);
+  SearchScratch S = carve(scratch, size, dsim, dbase);
   S.own_cell = own_cell_needed(t, theta);
   if (any) S.W.wave_steps = reinterpret_cast<unsigned long long*>(diag->wave_steps);
-  MSP_HIP_TRY(enqueue_prep(S, n, s, force));
+  MSP_HIP_TRY(enqueue_prep(S, s));
   int32_t status = 0, ntiles = 0, nunits = 0;
   int64_t total_S = 0;
   MSP_HIP_TRY(hipMemcpyAsync(&status, S.B.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -662,11 +677,17 @@ msp_status msp_find_targets_noalloc(msp_octree t, const uint8_t* neuron_type,
   int cur = -1;
   MSP_HIP_TRY(hipGetDevice(&cur));
   if (cur != t->device) return MSP_ERR_INVALID;   // the array of the tree's device
-  // the same layout as msp_find_targets' workspace, with kCkptMin slots and one
-  // checkpoint region per tile; the descriptor and the neuron bases follow it
-  const size_t body = scratch_sizes(n, 1, kCkptMin).total;
-  const size_t need = body + align_up(sizeof(SimDesc)) + align_up(2 * sizeof(int64_t));
-  if (need > kNoAllocBytes) return MSP_ERR_TOO_LARGE;
+  // the same layout as msp_find_targets' workspace, with kCkptMin checkpoints aimed at per
+  // tile and as many slots as the rest of the array holds; the descriptor and the neuron
+  // bases follow it
+  SearchSize size{n, 1, kCkptMin, 0, -1, false};
+  const size_t tail = align_up(sizeof(SimDesc)) + align_up(2 * sizeof(int64_t));
+  const size_t fixed = scratch_sizes(size).total + tail + 3 * 256;     // (rounding of the slots)
+  if (fixed >= kNoAllocBytes) return MSP_ERR_TOO_LARGE;
+  size.ck_cap = std::min<int64_t>((int64_t)((kNoAllocBytes - fixed) / kCkptSlotBytes),
+                                  (max_tiles_for(n, 1) << kPartLogMax) * kMinSlots);
+  if (size.ck_cap < 2 * max_parts_for(n, 1)) return MSP_ERR_TOO_LARGE;
+  const size_t body = scratch_sizes(size).total;
   void* base = nullptr;
   MSP_HIP_TRY(noalloc_scratch(t->device, &base));
   char* p = static_cast<char*>(base);
@@ -676,9 +697,9 @@ msp_status msp_find_targets_noalloc(msp_octree t, const uint8_t* neuron_type,
                               elem_offset_out, capacity_S);
   put_desc_k<<<1, 64, 0, s>>>(h, dsim, dbase, n);
   MSP_HIP_TRY(hipGetLastError());
-  SearchScratch S = carve(base, n, 1, kCkptMin, dsim, dbase);
+  SearchScratch S = carve(base, size, dsim, dbase);
   S.own_cell = own_cell_needed(t, theta);
-  MSP_HIP_TRY(enqueue_prep(S, n, s));
+  MSP_HIP_TRY(enqueue_prep(S, s));
   int32_t status = 0, ntiles = 0, nunits = 0;
   MSP_HIP_TRY(hipMemcpyAsync(&status, S.B.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   MSP_HIP_TRY(hipMemcpyAsync(&ntiles, S.counters, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -815,8 +836,6 @@ struct msp_batch_s {
   bool uploaded;            // the device table holds descriptors of the plan's sims
   unsigned sweep_blocks;
   int draw_block;
-  int ck_slots;             // checkpoint slots per region
-  int64_t ck_regions;       // checkpoint regions
   bool tuned;
   bool captured_own;        // own-cell test of the captured sweep
   hipGraphExec_t exec;
@@ -856,23 +875,22 @@ bool sim_ok(const msp_sim& m) {
 }
 
 hipError_t batch_enqueue(msp_batch_s* b, hipStream_t s) {
-  hipError_t e = enqueue_prep(b->S, b->total_n, s);
+  hipError_t e = enqueue_prep(b->S, s);
   if (e != hipSuccess) return e;
   return enqueue_search(b->S, false, b->sweep_blocks, b->draw_block, s);
 }
 
 // Time launch shapes on the current descriptors and keep the fastest: the sweep's
-// occupancy, the draw's block size and the checkpoint depth (slots per region: the
-// plan's own, and kCkptMin where the plan holds more; the scratch carved for more
-// slots holds fewer). Each shape is timed kTuneReps times after one untimed run, and
+// occupancy, the draw's block size and the checkpoints aimed at per tile (the plan's own
+// number, and kCkptMin where that is more; the scratch carved for more slots holds fewer). Each shape is timed kTuneReps times after one untimed run, and
 // its median counts. The targets do not depend on the shape.
 constexpr int kTuneReps = 3;
 
 hipError_t batch_autotune(msp_batch_s* b, hipStream_t s) {
   const double fracs[] = {1.0, 0.75, 0.5};
   const int draws[] = {256, 128, 64};
-  const int slots_opts[] = {b->ck_slots, kCkptMin};
-  const int n_slots = b->ck_slots == kCkptMin ? 1 : 2;
+  const int slots_opts[] = {b->S.q.slots, kCkptMin};
+  const int n_slots = b->S.q.slots == kCkptMin ? 1 : 2;
   const int64_t max_units = max_units_for(b->total_n, b->nsims);
   hipEvent_t e0, e1;
   hipError_t e = hipEventCreate(&e0);
@@ -963,14 +981,12 @@ msp_status msp_batch_create(const msp_sim* sims, int32_t n_sims, int32_t flags, 
   b->captured_own = true;
   b->cap_stream = nullptr;
   b->draw_block = 256;
-  b->ck_slots = kCkptMin;
+  SearchSize size{};
   hipError_t e = hipHostMalloc((void**)&b->h_sims, sizeof(SimDesc) * n_sims, hipHostMallocDefault);
   if (e == hipSuccess) e = hipMalloc((void**)&b->d_sims, sizeof(SimDesc) * n_sims);
   if (e == hipSuccess) e = hipMalloc((void**)&b->d_nbase, sizeof(int64_t) * (n_sims + 1));
-  b->ck_regions = 0;
-  if (e == hipSuccess) e = ck_slots_for(dev, total, n_sims, -1, &b->ck_slots, &b->ck_regions);
-  if (e == hipSuccess)
-    e = hipMalloc(&b->scratch, scratch_sizes(total, n_sims, b->ck_slots, -1, b->ck_regions).total);
+  if (e == hipSuccess) e = search_size(dev, total, n_sims, -1, false, &size);
+  if (e == hipSuccess) e = hipMalloc(&b->scratch, scratch_sizes(size).total);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->staged, hipEventDisableTiming);
   b->cap_stream = nullptr;
   if (e == hipSuccess && (flags & MSP_BATCH_GRAPH))
@@ -984,7 +1000,7 @@ msp_status msp_batch_create(const msp_sim* sims, int32_t n_sims, int32_t flags, 
     batch_release(b);
     return e == hipErrorOutOfMemory ? MSP_ERR_OOM : MSP_ERR_HIP;
   }
-  b->S = carve(b->scratch, total, n_sims, b->ck_slots, b->d_sims, b->d_nbase, -1, b->ck_regions);
+  b->S = carve(b->scratch, size, b->d_sims, b->d_nbase);
   handle_register(b, HandleKind::kBatch);
   *out = b;
   return MSP_OK;
@@ -1099,11 +1115,12 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   MSP_HIP_TRY(dsim.alloc(sizeof(SimDesc)));
   MSP_HIP_TRY(dbase.alloc(sizeof(hbase)));
   // the worklist only: no draws, so no checkpoints
-  MSP_HIP_TRY(scratch.alloc(scratch_sizes(n, 1, 0).total));
+  const SearchSize size{n, 1, 0, 0, -1, false};
+  MSP_HIP_TRY(scratch.alloc(scratch_sizes(size).total));
   MSP_HIP_TRY(hipMemcpyAsync(dsim.p, &h, sizeof(SimDesc), hipMemcpyHostToDevice, s));
   MSP_HIP_TRY(hipMemcpyAsync(dbase.p, hbase, sizeof(hbase), hipMemcpyHostToDevice, s));
-  SearchScratch S = carve(scratch.p, n, 1, 0, dsim.as<SimDesc>(), dbase.as<int64_t>());
-  MSP_HIP_TRY(enqueue_prep(S, n, s, -1, false));
+  SearchScratch S = carve(scratch.p, size, dsim.as<SimDesc>(), dbase.as<int64_t>());
+  MSP_HIP_TRY(enqueue_prep(S, s));
   int32_t status = 0;
   MSP_HIP_TRY(hipMemcpyAsync(&status, S.B.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   MSP_HIP_TRY(hipStreamSynchronize(s));
@@ -1115,7 +1132,7 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
     MSP_HIP_TRY(sweep_blocks_for(t->device, false, max_units_for(n, 1), 1.0, &blocks));
     fill_i32_k<<<grid_for(n, 256), 256, 0, s>>>(reinterpret_cast<int32_t*>(Z_out), n, 0);
     S.own_cell = own_cell_needed(t, theta);
-    launch_sweep<false, 0>(S, blocks, s);
+    launch_sweep<false, false>(S, blocks, s);
     z_scatter_k<<<grid_for(S.B.max_slots, 256), 256, 0, s>>>(S.B, S.W, Z_out);
     MSP_HIP_TRY(hipGetLastError());
     return MSP_OK;
@@ -1347,10 +1364,10 @@ void cycle_release(msp_cycle_s* c) {
 }
 
 // Carves the plan's memory (base null: sizes it).
-size_t cycle_carve(msp_cycle_s* c, char* base, int slots, int64_t regions) {
+size_t cycle_carve(msp_cycle_s* c, char* base, const SearchSize& size) {
   Carver cv{base};
   const int64_t n = c->n;
-  void* search = cv.take_bytes(scratch_sizes(n, 1, slots, -1, regions).total);
+  void* search = cv.take_bytes(scratch_sizes(size).total);
   c->d_sim = cv.take<SimDesc>(1);
   c->d_nbase = cv.take<int64_t>(2);
   c->elem_off = cv.take<int64_t>(n + 1);
@@ -1366,7 +1383,7 @@ size_t cycle_carve(msp_cycle_s* c, char* base, int slots, int64_t regions) {
   (void)plast_ws(nullptr, n, c->cap_syn, &bytes);
   void* pw = cv.take_bytes(bytes);
   if (base) {
-    c->S = carve(search, n, 1, slots, c->d_sim, c->d_nbase, -1, regions);
+    c->S = carve(search, size, c->d_sim, c->d_nbase);
     c->cw = commit_ws(cw, n, c->cap_S, &bytes);
     c->pw = plast_ws(pw, n, c->cap_syn, &bytes);
   }
@@ -1381,7 +1398,7 @@ hipError_t cycle_enqueue(msp_cycle_s* c, hipStream_t s) {
   cycle_begin_k<<<1, 64, 0, s>>>(c->d_sim, st.step, c->rec_flags);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = enqueue_refresh(c->t, st.vac_exc, st.vac_inh, s);
-  if (e == hipSuccess) e = enqueue_prep(c->S, n, s);
+  if (e == hipSuccess) e = enqueue_prep(c->S, s);
   if (e == hipSuccess) e = enqueue_search(c->S, false, c->sweep_blocks, 256, s);
   if (e != hipSuccess) return e;
   cycle_searches_k<<<1, 64, 0, s>>>(c->S.B.status, c->elem_off, n, c->cnt);
@@ -1442,12 +1459,11 @@ msp_status msp_cycle_create(msp_octree t, const uint8_t* neuron_type, double sig
   c->mem = nullptr;
   c->captured = false;
   c->cap_stream = nullptr;
-  int slots = 0;
-  int64_t regions = 0;
-  hipError_t e = ck_slots_for(dev, c->n, 1, -1, &slots, &regions);
-  if (e == hipSuccess) e = hipMalloc(&c->mem, cycle_carve(c, nullptr, slots, regions));
+  SearchSize size;
+  hipError_t e = search_size(dev, c->n, 1, -1, false, &size);
+  if (e == hipSuccess) e = hipMalloc(&c->mem, cycle_carve(c, nullptr, size));
   if (e == hipSuccess) {
-    (void)cycle_carve(c, static_cast<char*>(c->mem), slots, regions);
+    (void)cycle_carve(c, static_cast<char*>(c->mem), size);
     e = sweep_blocks_for(dev, false, max_units_for(c->n, 1), 1.0, &c->sweep_blocks);
   }
   if (e == hipSuccess && (flags & MSP_CYCLE_GRAPH))
