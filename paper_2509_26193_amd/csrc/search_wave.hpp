@@ -375,7 +375,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
   // coordinates wait for them
   __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
   const double L2 = d->L2, theta2 = d->theta2, acc_d2 = d->acc_d2, k2 = d->k2;
-  SumPass sum{k2};
+  double Z = 0.0;
   Count c0;
   int steps = park(0);
   const NodeRec root = load_rec(R, 0);
@@ -465,7 +465,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
       int done = 0;                          // the part's steps
       ph = 0;
       s1 = 0;
-      sum.Z = 0.0;
+      Z = 0.0;
       // a checkpoint at step index s1, a multiple of the interval; a full buffer keeps every
       // other one and doubles the interval
       auto checkpoint = [&]() {
@@ -486,7 +486,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
             return;
           }
         }
-        ckP[nck * kWave] = sum.Z;
+        ckP[nck * kWave] = Z;
         ckme[nck * kWave] = (int32_t)(meb >> kRecShift);
         if (lane == 0) ckx[nck] = (int32_t)(xb >> kRecShift);
         nck = __builtin_amdgcn_readfirstlane(nck + 1);
@@ -531,7 +531,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
               // be scheduled above the load)
               nxt = load_rec_b(R, next);
               __builtin_amdgcn_sched_barrier(0);
-              sum.Z = sum.Z + kernel_weight_vd(keep, vd, d2, k2);
+              Z = kernel_add(Z, keep, vd, d2, k2);
             } else {                              // several neurons at one finest cell
               nxt = load_rec_b(R, next);
               const int32_t x = (int32_t)(xb >> kRecShift);
@@ -545,11 +545,10 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
                 const int32_t v = vs[p];
                 if (v == 0) continue;
                 if (DIAG && active && id != i) c0.entries += 1;
-                sum.Z = sum.Z + kernel_weight_if(
-                    active && id != i, v,
-                    dist2(xi, yi, zi, pos[3 * (int64_t)id], pos[3 * (int64_t)id + 1],
-                          pos[3 * (int64_t)id + 2]),
-                    k2);
+                Z = kernel_add(Z, active && id != i, (double)v,
+                               dist2(xi, yi, zi, pos[3 * (int64_t)id], pos[3 * (int64_t)id + 1],
+                                     pos[3 * (int64_t)id + 2]),
+                               k2);
               }
             }
           } else if (__builtin_expect(cur.v == 0, 0)) {   // no vacancy below: over the subtree
@@ -576,7 +575,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
                 : "scc");
             nxt = load_rec_b(R, next);
             __builtin_amdgcn_sched_barrier(0);
-            sum.Z = sum.Z + kernel_weight_vd(take, vd, d2, k2);
+            Z = kernel_add(Z, take, vd, d2, k2);
             meb = me_next;
             if (DIAG && __builtin_amdgcn_inverse_ballot_w64(m_open)) c0.opens += 1;
             if (DIAG && take) c0.entries += 1;
@@ -604,7 +603,7 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
       const int64_t at = (int64_t)unpark(index) + unpark(part);
       const int64_t us = at * kWave + lane;
       if (CKPT && lane == 0) Ke->W.nck[at] = nck;
-      Ke->W.Z[us] = sum.Z;
+      Ke->W.Z[us] = Z;
       if (DIAG) {
         Ke->W.v0[us] = c0.visits;
         Ke->W.o0[us] = c0.opens;
@@ -652,6 +651,14 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
   for (; q0 < np; ++q0) Z = Z + Zp[q0 * kWave];
   const NodeRec root = R[0];             // Z > 0 implies an inner root
   const int32_t end = (int32_t)(root.meta & kSkipMask);
+  // a sum that small once more, from the rounded products (see kernel_add)
+  const bool tiny = Z > 0.0 && Z < kTinyZ;
+  if (__builtin_expect(tiny, 0)) {
+    SumPass s{A.k2};
+    Count none;
+    expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, s, none);
+    Z = s.Z;
+  }
   const int32_t a = A.vac_axon[i];
   const int64_t off = A.elem_off[i];
   Count c0;
@@ -669,7 +676,7 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
     int32_t deferred = -1;
     if (Z > 0.0) {
       const double T = draw_u(A.seed, i, j, A.step, 0) * Z;
-      SelectPass p{A.k2, T};
+      SelectPass<true> p{A.k2, T};
       Count none;
       // the part where the running sum crosses T (the sums added as for Z), and T
       // from that part's start
@@ -705,11 +712,17 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
         expand_range<false>(A, R, vs, cx > cm ? cx : cm, end, i, li, xi, yi, zi, p, none);
       }
       if (p.chosen < 0) {                       // not crossed (rounding): full walk
-        p = SelectPass{A.k2, T};
+        p = SelectPass<true>{A.k2, T};
         expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, p, none);
       }
-      const int32_t id = p.chosen >= 0 ? p.chosen : p.last;
-      const bool neuron = p.chosen >= 0 ? p.chosen_neuron : p.last_neuron;
+      int32_t id = p.chosen >= 0 ? p.chosen : p.last;
+      bool neuron = p.chosen >= 0 ? p.chosen_neuron : p.last_neuron;
+      if (__builtin_expect(tiny, 0)) {          // (see kernel_add)
+        SelectPass<false> s{A.k2, T};
+        expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, s, none);
+        id = s.chosen >= 0 ? s.chosen : s.last;
+        neuron = s.chosen >= 0 ? s.chosen_neuron : s.last_neuron;
+      }
       if (id >= 0)
         tgt = neuron ? id
                      : restart_search<DIAG, DEFER>(A, R, vs, id, 1, W.defer.depth, i, j, li,
