@@ -844,16 +844,19 @@ inline hipError_t enqueue_prep(SearchScratch& S, hipStream_t s) {
   b_tiles_k<<<1, kTilesBlock, 0, s>>>(B, S.counters, S.counters + 2, S.counters + 1, total_n,
                                       S.q.force, S.W.ck_slots, S.W.ck_cap);
   // 64-source tiles in Hilbert order within each (simulation, type) group
-  // (32-bit keys keep 20 or more Hilbert bits, cells of about a hundredth of the box
-  // edge or finer, for up to 2048 simulations)
-  int gb = 1;
+  // (the keys keep 6 Hilbert bits more than it takes to number the neurons, which leaves
+  // about a neuron per cell where they lie 64 times denser than on average, up to 20 bits or
+  // more: cells of about a hundredth of the box edge or finer, for up to 2048 simulations)
+  int gb = 1, nb = 1;
   while ((1ll << gb) < 2ll * B.nsims) ++gb;
-  const int kb = gb <= 12 ? 32 : 48;
+  while ((1ll << nb) < total_n) ++nb;
+  const int kb = gb > 12 ? 48 : gb + nb + 6 <= 24 ? 24 : 32;
   b_hkeys_k<<<g, 256, 0, s>>>(B, total_n, gb, kb, S.hkey[0], S.hval[0]);
-  e = radix_sort_pairs_ws(S.hkey[0], S.hval[0], S.hkey[1], S.hval[1], total_n, kb, s, S.hsort,
-                          S.counters + 1);
+  int at = 0;
+  e = radix_sort_pairs_ws(S.hkey[0], S.hval[0], S.hkey[1], S.hval[1], total_n, 0, kb, s, S.hsort,
+                          S.counters + 1, &at);
   if (e != hipSuccess) return e;
-  b_work_sorted_k<<<g, 256, 0, s>>>(B, total_n, S.hval[0]);
+  b_work_sorted_k<<<g, 256, 0, s>>>(B, total_n, S.hval[at]);
   // a simulation with 4 parts per tile or more has at most kPartsMax / 4 tiles, unless forced
   int64_t tiles = max_tiles_for(total_n, B.nsims);
   if (S.q.force < 0) tiles = B.nsims == 1 ? std::min<int64_t>(tiles, kPartsMax / 4) : tiles;

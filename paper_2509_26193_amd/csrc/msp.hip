@@ -377,7 +377,7 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
                  b_ws = align_up(radix_sort_ws_bytes(n)), b_cnt = align_up(sizeof(int32_t) * n),
                  b_base = align_up(sizeof(int32_t) * (n + 1)),
                  b_lvl = align_up(sizeof(int32_t) * 2 * (kMaxDepth + 1)),
-                 b_out = align_up(sizeof(int32_t)), b_scan = align_up(scan_tmp_bytes<int32_t>(n));
+                 b_out = align_up(2 * sizeof(int32_t)), b_scan = align_up(scan_tmp_bytes<int32_t>(n));
     Temp tmp(s);
     TRY(tmp.alloc(b_k1 + b_v1 + b_ws + b_cnt + b_base + b_lvl + b_out + b_scan));
     char* tp = tmp.as<char>();
@@ -390,24 +390,36 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
     int32_t* outside = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt + b_base +
                                                   b_lvl);
     void* scan_ws = tp + b_k1 + b_v1 + b_ws + b_cnt + b_base + b_lvl + b_out;
-    TRY(hipMemsetAsync(outside, 0, sizeof(int32_t), s));
+    TRY(hipMemsetAsync(outside, 0, 2 * sizeof(int32_t), s));
     keys_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(pos, n, box_min[0], box_min[1],
                                                             box_min[2], box_edge, t->pos, t->keys,
                                                             t->order, t->err, outside);
     TRY(hipGetLastError());
-    TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, 63, s, sort_ws));
-    node_count_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, n, cntp);
-    TRY(hipGetLastError());
-    TRY((exclusive_scan<int32_t, int32_t, Ident<int32_t>>(cntp, basep, n, Ident<int32_t>(), true,
-                                                          s, scan_ws)));
-    int32_t N32 = 0, h_outside = 1;
-    TRY(hipMemcpyAsync(&N32, basep + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    TRY(hipMemcpyAsync(&h_outside, outside, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    TRY(hipStreamSynchronize(s));
+    // the leading bits and their short runs first; if that leaves keys out of order (long
+    // runs), the whole keys (from that order, in which equal keys are in id order)
+    int32_t N32 = 0, found[2] = {0, 0};          // a position outside, keys out of order
+    for (int whole = 0;; ++whole) {
+      if (whole) {
+        TRY(hipMemsetAsync(outside + 1, 0, sizeof(int32_t), s));
+        TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, 0, 64, s, sort_ws));
+      } else {
+        TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, kLeadShift, kLeadBits, s, sort_ws));
+        order_runs_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, t->order, n);
+        TRY(hipGetLastError());
+      }
+      node_count_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, n, cntp, outside + 1);
+      TRY(hipGetLastError());
+      TRY((exclusive_scan<int32_t, int32_t, Ident<int32_t>>(cntp, basep, n, Ident<int32_t>(), true,
+                                                            s, scan_ws)));
+      TRY(hipMemcpyAsync(&N32, basep + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+      TRY(hipMemcpyAsync(found, outside, sizeof(found), hipMemcpyDeviceToHost, s));
+      TRY(hipStreamSynchronize(s));
+      if (!found[1] || whole) break;
+    }
     double far = 0.0;
     for (int a = 0; a < 3; ++a)
       far = std::max(far, std::max(std::fabs(box_min[a]), std::fabs(box_min[a] + box_edge)));
-    t->inside = h_outside == 0 && far <= std::ldexp(box_edge, 18);
+    t->inside = found[0] == 0 && far <= std::ldexp(box_edge, 18);
     if (N32 < 1 || N32 >= kMaxNodes) {
       release(t);
       return MSP_ERR_INVALID;
@@ -604,7 +616,7 @@ msp_status msp_find_targets_diag(msp_octree t, const uint8_t* neuron_type,
     const DeferOut& D = S.W.defer;
     char* p = static_cast<char*>(req.p);
     le = radix_sort_pairs_ws(D.key, D.val, reinterpret_cast<uint64_t*>(p + ks),
-                             reinterpret_cast<int32_t*>(p + 2 * ks + vs), total_S, key_bits, s,
+                             reinterpret_cast<int32_t*>(p + 2 * ks + vs), total_S, 0, key_bits, s,
                              p + 2 * ks + 5 * vs + align_up(sizeof(uint8_t) * total_S));
     if (le == hipSuccess) {
       if (any)

@@ -181,12 +181,15 @@ __device__ __forceinline__ int64_t sort_count(int64_t n, const int32_t* dn) {
 // With a device count the histograms cover only the tiles that hold items: nbd (device)
 // is their number, and it replaces nb in the digit-major layout. A block takes tiles
 // blockIdx.x, + gridDim.x, ... (a device-counted sort launches fewer blocks than tiles).
+// DIRECT: tile-major histograms instead (see rs_scatter_k).
+template <bool DIRECT>
 __global__ void __launch_bounds__(kSortBlock) rs_hist_k(const uint64_t* keys, int64_t n, int shift,
                                                        uint32_t* hist, int nb, const int32_t* dn,
                                                        const int32_t* nbd) {
-  if (nbd) nb = *nbd;
   __shared__ uint32_t h[256];
   n = sort_count(n, dn);
+  if (DIRECT) nb = (int)((n + kSortTile - 1) / kSortTile);
+  else if (nbd) nb = *nbd;
   for (int tile = blockIdx.x; tile < nb; tile += gridDim.x) {   // uniform over the block
     h[threadIdx.x] = 0;
     __syncthreads();
@@ -196,94 +199,256 @@ __global__ void __launch_bounds__(kSortBlock) rs_hist_k(const uint64_t* keys, in
       if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & 255u], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nb + tile] = h[threadIdx.x];
+    hist[DIRECT ? (int64_t)tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nb + tile] =
+        h[threadIdx.x];
     __syncthreads();                    // h is cleared for the next tile
   }
 }
 
-// One tile of kSortTile items: ranked by digit (stable) into LDS first, then written
-// out digit run by digit run, so consecutive threads store to consecutive addresses.
-// The tile's count of each digit is the difference of consecutive entries of the
-// scanned (digit-major) histogram.
+// Lanes of the wave with the same digit as this one (all 64 lanes take part; those that are
+// not `valid` match none).
+__device__ __forceinline__ uint64_t rs_peers(uint32_t d, bool valid) {
+  uint64_t peers = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t bb = __ballot(bit);
+    peers &= bit ? bb : ~bb;
+  }
+  return peers;
+}
+
+// Ranks `ITEMS` consecutive rounds of a wave's items by digit, in order: rank[c] = items of
+// the same digit before item (c, lane) in this wave. cnt: the wave's own 256 counters, zero
+// at the start, its digit counts at the end. A wave's LDS accesses are done in order, so the
+// rounds need no barrier.
+template <int ITEMS>
+__device__ __forceinline__ void rs_rank(const uint64_t (&keys)[ITEMS], int first, int n, int shift,
+                                        uint32_t* cnt, uint32_t (&rank)[ITEMS]) {
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const bool valid = first + c * kWave + lane < n;
+    const uint32_t d = (uint32_t)(keys[c] >> shift) & 255u;
+    const uint64_t peers = rs_peers(d, valid);
+    const uint32_t below = (uint32_t)__popcll(peers & lt);
+    uint32_t base = 0;
+    if (valid) base = __hip_atomic_load(&cnt[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0)
+      __hip_atomic_store(&cnt[d], base + (uint32_t)__popcll(peers), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_wave_barrier();
+    rank[c] = base + below;
+  }
+}
+
+// Exclusive scan of one value per digit over threads 0..255 of the block (others pass 0);
+// lds: 4 words; synchronises.
+__device__ __forceinline__ uint32_t rs_scan256(uint32_t v, uint32_t* lds) {
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  uint32_t x = v;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  if (lane == kWave - 1 && w < 4) lds[w] = x;
+  __syncthreads();
+  uint32_t off = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) off += k < w ? lds[k] : 0u;
+  return off + x - v;
+}
+
+// Sorts up to kSortTile items by key bits [shift0, shift0 + bits) in one block: the items
+// stay in registers and LDS over all passes (a digit that no two keys differ in takes
+// none). Bound by the barriers between the steps of a pass: 4 096 items by 32 bits take
+// 21 us, where 12 launches of tile histograms, scans and scatters took 87 us.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = kSortTile / kSmallBlock;
+
+__global__ void __launch_bounds__(kSmallBlock) rs_small_k(uint64_t* __restrict__ kio,
+                                                         int32_t* __restrict__ vio, int64_t n64,
+                                                         int shift0, int bits, const int32_t* dn) {
+  constexpr int kWaves = kSmallBlock / kWave;
+  __shared__ uint64_t lk[kSortTile];
+  __shared__ int32_t lv[kSortTile];
+  __shared__ uint16_t cnt[kWaves][256];          // the waves' digit counts (256 items each)
+  __shared__ uint32_t start[256];
+  __shared__ uint32_t lds[4];
+  __shared__ unsigned long long diff;
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  const int n = (int)sort_count(n64, dn);
+  if (n <= 1) return;
+  const int first = w * kSmallItems * kWave;
+  uint64_t keys[kSmallItems];
+  int32_t vals[kSmallItems];
+#pragma unroll
+  for (int c = 0; c < kSmallItems; ++c) {
+    const int i = first + c * kWave + lane;
+    keys[c] = i < n ? kio[i] : 0ull;
+    vals[c] = i < n ? vio[i] : 0;
+  }
+  // the bits in which keys differ from the first one
+  if (t == 0) {
+    diff = 0;
+    lk[0] = keys[0];
+  }
+  __syncthreads();
+  uint64_t x = 0;
+#pragma unroll
+  for (int c = 0; c < kSmallItems; ++c)
+    if (first + c * kWave + lane < n) x |= keys[c] ^ lk[0];
+  if (x) atomicOr(&diff, (unsigned long long)x);
+  __syncthreads();
+  const uint64_t differ = diff;
+  uint16_t* mine = cnt[w];
+  for (int shift = shift0; shift < shift0 + bits; shift += 8) {
+    if (((differ >> shift) & 255u) == 0) continue;            // (uniform over the block)
+    for (int k = t; k < kWaves * 256; k += kSmallBlock) cnt[k >> 8][k & 255] = 0;
+    __syncthreads();
+    uint32_t rank[kSmallItems];
+    const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int c = 0; c < kSmallItems; ++c) {
+      const bool valid = first + c * kWave + lane < n;
+      const uint32_t d = (uint32_t)(keys[c] >> shift) & 255u;
+      const uint64_t peers = rs_peers(d, valid);
+      const uint32_t below = (uint32_t)__popcll(peers & lt);
+      uint32_t base = 0;
+      if (valid) base = *(volatile uint16_t*)&mine[d];
+      __builtin_amdgcn_wave_barrier();
+      if (valid && below == 0)
+        *(volatile uint16_t*)&mine[d] = (uint16_t)(base + (uint32_t)__popcll(peers));
+      __builtin_amdgcn_wave_barrier();
+      rank[c] = base + below;
+    }
+    __syncthreads();
+    // per digit: the waves' counts to the counts of the waves before, and the digit's total
+    uint32_t total = 0;
+    if (t < 256) {
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) {
+        const uint32_t v = cnt[k][t];
+        cnt[k][t] = (uint16_t)total;
+        total += v;
+      }
+    }
+    const uint32_t s = rs_scan256(total, lds);
+    if (t < 256) start[t] = s;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kSmallItems; ++c) {
+      if (first + c * kWave + lane >= n) continue;
+      const uint32_t d = (uint32_t)(keys[c] >> shift) & 255u;
+      const uint32_t p = start[d] + mine[d] + rank[c];
+      lk[p] = keys[c];
+      lv[p] = vals[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kSmallItems; ++c) {
+      const int i = first + c * kWave + lane;
+      keys[c] = i < n ? lk[i] : 0ull;
+      vals[c] = i < n ? lv[i] : 0;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < kSmallItems; ++c) {
+    const int i = first + c * kWave + lane;
+    if (i < n) {
+      kio[i] = keys[c];
+      vio[i] = vals[c];
+    }
+  }
+}
+
+// One tile of kSortTile items: ranked by digit (stable) in LDS first, every wave a
+// consecutive quarter with counters of its own, then written out digit run by digit run, so
+// consecutive threads store to consecutive addresses. off: the scanned digit-major
+// histogram (DIRECT false), whose consecutive entries' difference is the tile's count of a
+// digit; or the tile-major one as counted (DIRECT true, up to kDirectTiles tiles), from which
+// every block adds up its own offsets: a sort of few tiles is bound by its launches, and
+// this takes two per pass instead of five (and the tile counts of a device-counted sort).
+constexpr int kDirectTiles = 64;
+
+template <bool DIRECT>
 __global__ void __launch_bounds__(kSortBlock) rs_scatter_k(const uint64_t* kin, const int32_t* vin,
                                                           uint64_t* kout, int32_t* vout, int64_t n,
                                                           int shift, const uint32_t* off, int nb,
                                                           const int32_t* dn, const int32_t* nbd) {
-  if (nbd) nb = *nbd;
+  constexpr int kWaves = kSortBlock / kWave;
   __shared__ uint64_t lk[kSortTile];
   __shared__ int32_t lv[kSortTile];
   __shared__ uint32_t lstart[256];      // tile-local start of each digit's run
   __shared__ uint32_t gstart[256];      // global start of this tile's run of each digit
-  __shared__ uint32_t run[256];         // items of each digit placed so far
-  __shared__ uint32_t wcnt[kSortBlock / kWave][256];
+  __shared__ uint32_t cnt[kWaves][256];
+  __shared__ uint32_t lds[4];
   const int t = threadIdx.x;
   const int w = t / kWave;
   const int lane = t & (kWave - 1);
-  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (kWave - lane));
   n = sort_count(n, dn);
+  if (DIRECT) nb = (int)((n + kSortTile - 1) / kSortTile);
+  else if (nbd) nb = *nbd;
   for (int tile = blockIdx.x; tile < nb; tile += gridDim.x) {   // uniform over the block
     const int64_t base = (int64_t)tile * kSortTile;
     if (base >= n) break;
     const int64_t rem = n - base;
     const int tile_n = rem < kSortTile ? (int)rem : kSortTile;
-    const int64_t h = (int64_t)t * nb + tile;
-    const uint32_t g0 = off[h];
-    const uint32_t g1 = h + 1 < 256 * (int64_t)nb ? off[h + 1] : (uint32_t)n;
-    const uint32_t count = g1 - g0;     // this tile's items of digit t
-    gstart[t] = g0;
-    lstart[t] = count;
-    run[t] = 0;
-    __syncthreads();
-    // inclusive scan of the 256 counts (Hillis-Steele), then exclusive = inclusive - own
-    for (int d = 1; d < 256; d <<= 1) {
-      const uint32_t v = t >= d ? lstart[t - d] : 0u;
-      __syncthreads();
-      lstart[t] += v;
-      __syncthreads();
-    }
-    lstart[t] -= count;
-    // the tile's items in registers first: one memory round trip per tile, not per round
+    // the tile's items in registers: one memory round trip per tile
+    const int first = w * kSortItems * kWave;
     uint64_t keys[kSortItems];
     int32_t vals[kSortItems];
 #pragma unroll
     for (int c = 0; c < kSortItems; ++c) {
-      const int li = c * kSortBlock + t;
+      const int li = first + c * kWave + lane;
       keys[c] = li < tile_n ? kin[base + li] : 0ull;
       vals[c] = li < tile_n ? vin[base + li] : 0;
+    }
+    uint32_t count, g0;                 // this tile's items of digit t, their global start
+    if (DIRECT) {
+      uint32_t before = 0, all = 0;
+      count = 0;
+      for (int q = 0; q < nb; ++q) {
+        const uint32_t h = off[q * 256 + t];
+        before += q < tile ? h : 0u;
+        count = q == tile ? h : count;
+        all += h;
+      }
+      g0 = before + rs_scan256(all, lds);
+      __syncthreads();
+    } else {
+      const int64_t h = (int64_t)t * nb + tile;
+      g0 = off[h];
+      count = (h + 1 < 256 * (int64_t)nb ? off[h + 1] : (uint32_t)n) - g0;
+    }
+    gstart[t] = g0;
+    lstart[t] = rs_scan256(count, lds);
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) cnt[k][t] = 0;
+    __syncthreads();
+    uint32_t rank[kSortItems];
+    rs_rank<kSortItems>(keys, first, tile_n, shift, cnt[w], rank);
+    __syncthreads();
+    uint32_t before = 0;                // the counts of the waves before, per digit
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+      const uint32_t v = cnt[k][t];
+      cnt[k][t] = before;
+      before += v;
     }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kSortItems; ++c) {
-#pragma unroll
-      for (int k = 0; k < kSortBlock / kWave; ++k) wcnt[k][t] = 0;
-      __syncthreads();
-      const int li = c * kSortBlock + t;
-      const bool valid = li < tile_n;
-      const uint64_t key = keys[c];
-      const uint32_t d = (uint32_t)(key >> shift) & 255u;
-      uint64_t peers = __ballot(valid);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bb = __ballot(bit);
-        peers &= bit ? bb : ~bb;
+      if (first + c * kWave + lane >= tile_n) continue;
+      const uint32_t d = (uint32_t)(keys[c] >> shift) & 255u;
+      const uint32_t p = lstart[d] + cnt[w][d] + rank[c];
+      if (p < (uint32_t)kSortTile) {
+        lk[p] = keys[c];
+        lv[p] = vals[c];
       }
-      const uint32_t rank = (uint32_t)__popcll(peers & lt);
-      if (valid && rank == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-      __syncthreads();
-      if (valid) {
-        uint32_t p = lstart[d] + run[d] + rank;
-        for (int k = 0; k < w; ++k) p += wcnt[k][d];
-        if (p < (uint32_t)kSortTile) {
-          lk[p] = key;
-          lv[p] = vals[c];
-        }
-      }
-      __syncthreads();
-      uint32_t add = 0;
-#pragma unroll
-      for (int k = 0; k < kSortBlock / kWave; ++k) add += wcnt[k][t];
-      run[t] += add;
     }
     __syncthreads();
     for (int i = t; i < tile_n; i += kSortBlock) {
@@ -329,23 +494,30 @@ inline size_t radix_sort_ws_bytes(int64_t n) {
   return hist + scan_tmp_bytes<uint32_t>(256 * (nb > 0 ? nb : 1) + 1) + 256;
 }
 
-// Sort (keys, vals) of length n ascending by the low `bits` key bits (a multiple of 8).
-// Buffers k0/v0 hold the input and receive the output; k1/v1 are scratch of size n;
-// `ws` holds radix_sort_ws_bytes(n) bytes. Allocates nothing, so it can be captured.
-// dn (nullable, device): sort only the first min(n, *dn) items, a count known on the
-// device alone; the launches stay sized for n.
+// Sort (keys, vals) of length n ascending by the key bits [shift0, shift0 + bits) (bits a
+// multiple of 8). Buffers k0/v0 hold the input; k1/v1 are scratch of size n; `ws` holds
+// radix_sort_ws_bytes(n) bytes. The output is in k0/v0 or, where `where` is given and set to
+// 1, in k1/v1 (an odd number of passes). Allocates nothing, so it can be captured. dn
+// (nullable, device): sort only the first min(n, *dn) items, a count known on the device
+// alone; the launches stay sized for n.
 inline hipError_t radix_sort_pairs_ws(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1,
-                                      int64_t n, int bits, hipStream_t s, void* ws,
-                                      const int32_t* dn = nullptr) {
+                                      int64_t n, int shift0, int bits, hipStream_t s, void* ws,
+                                      const int32_t* dn = nullptr, int* where = nullptr) {
+  if (where) *where = 0;
   if (n <= 1) return hipSuccess;
+  if (n <= kSortTile) {
+    rs_small_k<<<1, kSmallBlock, 0, s>>>(k0, v0, n, shift0, bits, dn);
+    return hipGetLastError();
+  }
   const int64_t nb = (n + kSortTile - 1) / kSortTile;
+  const bool direct = nb <= kDirectTiles;
   uint32_t* hist = static_cast<uint32_t*>(ws);
   const size_t hist_bytes = ((sizeof(uint32_t) * 256 * (size_t)nb) + 255) & ~(size_t)255;
   void* scan_ws = static_cast<char*>(ws) + hist_bytes;
   // a device-counted sort sizes its histograms by the tiles that hold items
   int32_t* nbd = nullptr;
   int64_t* hn = nullptr;
-  if (dn) {
+  if (dn && !direct) {
     char* tail = static_cast<char*>(scan_ws) + scan_tmp_bytes<uint32_t>(256 * nb + 1);
     hn = reinterpret_cast<int64_t*>(tail);
     nbd = reinterpret_cast<int32_t*>(tail + sizeof(int64_t));
@@ -358,38 +530,32 @@ inline hipError_t radix_sort_pairs_ws(uint64_t* k0, int32_t* v0, uint64_t* k1, i
   hipError_t e = hipSuccess;
   // a device-counted sort holds few tiles with items, mostly: a bounded grid loops
   const unsigned grid = dn ? (unsigned)std::min<int64_t>(nb, kSortGridDn) : (unsigned)nb;
-  for (int shift = 0; shift < bits; shift += 8) {
-    rs_hist_k<<<grid, kSortBlock, 0, s>>>(ka, n, shift, hist, (int)nb, dn, nbd);
-    e = exclusive_scan<uint32_t, uint32_t, Ident<uint32_t>>(hist, hist, 256 * nb, Ident<uint32_t>(),
-                                                            false, s, scan_ws, hn);
-    if (e != hipSuccess) return e;
-    rs_scatter_k<<<grid, kSortBlock, 0, s>>>(ka, va, kb, vb, n, shift, hist, (int)nb, dn, nbd);
+  for (int shift = shift0; shift < shift0 + bits; shift += 8) {
+    if (direct) {
+      rs_hist_k<true><<<grid, kSortBlock, 0, s>>>(ka, n, shift, hist, (int)nb, dn, nullptr);
+      rs_scatter_k<true><<<grid, kSortBlock, 0, s>>>(ka, va, kb, vb, n, shift, hist, (int)nb, dn,
+                                                     nullptr);
+    } else {
+      rs_hist_k<false><<<grid, kSortBlock, 0, s>>>(ka, n, shift, hist, (int)nb, dn, nbd);
+      e = exclusive_scan<uint32_t, uint32_t, Ident<uint32_t>>(hist, hist, 256 * nb,
+                                                              Ident<uint32_t>(), false, s, scan_ws,
+                                                              hn);
+      if (e != hipSuccess) return e;
+      rs_scatter_k<false><<<grid, kSortBlock, 0, s>>>(ka, va, kb, vb, n, shift, hist, (int)nb, dn,
+                                                      nbd);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     uint64_t* tk = ka; ka = kb; kb = tk;
     int32_t* tv = va; va = vb; vb = tv;
   }
-  if (ka != k0) {
-    if (dn) {                           // an odd number of passes: copy the sorted items
-      rs_copy_k<<<grid_cap(n, kSortBlock), kSortBlock, 0, s>>>(ka, va, k0, v0, n, dn);
-      return hipGetLastError();
-    }
-    e = hipMemcpyAsync(k0, ka, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(v0, va, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s);
+  if (ka == k0) return hipSuccess;
+  if (where) {
+    *where = 1;
+    return hipSuccess;
   }
-  return e;
-}
-
-// Sort (keys, vals) of length n ascending by key; `bits` = number of key bits to sort.
-// Buffers k0/v0 hold the input and receive the output; k1/v1 are scratch of size n.
-inline hipError_t radix_sort_pairs(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1, int64_t n,
-                                   int bits, hipStream_t s) {
-  if (n <= 1) return hipSuccess;
-  Temp ws(s);
-  hipError_t e = ws.alloc(radix_sort_ws_bytes(n));
-  if (e != hipSuccess) return e;
-  return radix_sort_pairs_ws(k0, v0, k1, v1, n, bits, s, ws.p);
+  rs_copy_k<<<grid_cap(n, kSortBlock), kSortBlock, 0, s>>>(ka, va, k0, v0, n, dn);
+  return hipGetLastError();
 }
 
 }  // namespace msp

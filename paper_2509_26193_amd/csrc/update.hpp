@@ -186,7 +186,8 @@ inline hipError_t enqueue_plasticity(const PlastWs& w, int64_t n, const PlastCon
       if (e != hipSuccess) return e;
       take_count_k<<<1, 64, 0, s>>>(w.pos, m, w.cnt, w.cnt32);
       cand_write_k<<<gm, kPlastBlock, 0, s>>>(F, w.pos, m, seed, step, w.k0, w.v0);
-      e = radix_sort_pairs_ws(w.k0, w.v0, w.k1, w.v1, m.v, key_bits, s, w.sort_ws, w.cnt32);
+      e = radix_sort_pairs_ws(w.k0, w.v0, w.k1, w.v1, m.v, 0, key_bits, s, w.sort_ws,
+                              w.cnt32);
       if (e != hipSuccess) return e;
       retract_k<<<gm, kPlastBlock, 0, s>>>(w.k0, w.v0, C, w.exc, L, n, w.dead, bound);
       if ((e = hipGetLastError()) != hipSuccess) return e;
