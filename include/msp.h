@@ -431,8 +431,8 @@ msp_status msp_plasticity_record(int64_t n, const int32_t* new_src, const int32_
  *   5. vac_axon, vac_exc, vac_inh [n] int32 = floor(z) - bound of each kind.
  * Errors: MSP_ERR_INVALID for n < 1, m < 0 or m >= 2^31, a null pointer or parameters
  * that are not finite (or growth_onset >= target_calcium). Waits on `s`. Its working
- * memory (about 60 B per synapse) is the one the library keeps per device for
- * searches (see msp_find_targets).
+ * memory (about 25 B per synapse and 24 B per neuron) is the one the library keeps per
+ * device for searches (see msp_find_targets).
  */
 msp_status msp_plasticity_step(int64_t n, const msp_plasticity_params* params, uint64_t seed,
                                uint64_t step, double* z, int32_t* bound, int32_t* syn_src,

@@ -241,8 +241,4 @@ __global__ void formed_k(const int64_t* __restrict__ dst, DevCount S, int64_t ca
   *n_formed = ((*flags & kErrArgs) || f > cap) ? 0 : f;
 }
 
-__global__ void copy_scalar_k(const int64_t* __restrict__ src, int64_t* __restrict__ dst) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
-}
-
 }  // namespace msp

@@ -1205,11 +1205,11 @@ namespace {
 // definition, evaluated once).
 PlastConst plast_const(const msp_plasticity_params& p) {
   PlastConst c;
-  c.scale = (double)p.steps_per_update * p.growth_rate;
-  c.xi = 0.5 * (p.growth_onset + p.target_calcium);
-  c.zeta = (p.target_calcium - p.growth_onset) / (2.0 * std::sqrt(std::log(2.0)));
-  c.ca_mean = p.calcium_mean;
-  c.ca_sd = p.calcium_sd;
+  c.growth.scale = (double)p.steps_per_update * p.growth_rate;
+  c.growth.xi = 0.5 * (p.growth_onset + p.target_calcium);
+  c.growth.zeta = (p.target_calcium - p.growth_onset) / (2.0 * std::sqrt(std::log(2.0)));
+  c.growth.ca_mean = p.calcium_mean;
+  c.growth.ca_sd = p.calcium_sd;
   c.delete_fraction = p.delete_fraction;
   return c;
 }

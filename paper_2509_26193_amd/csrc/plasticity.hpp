@@ -15,8 +15,8 @@
 //   * a synapse (i, g, type) binds one axonal element of i and one dendritic element
 //     of kind 1 + type of g; breaking it frees both; the list keeps its order;
 //   * vacant elements: floor(z) - bound.
-// Selections are sorts of 64-bit keys (priority, or owner and priority) with the
-// synapse index as a stable tie-break, so every choice is exact and reproducible.
+// Selections are by 64-bit keys (priority; or priority and synapse index) with the
+// synapse index as the tie-break, so every choice is exact and reproducible.
 #pragma once
 
 #include "scan.hpp"
@@ -31,23 +31,24 @@ struct SynList {
   uint8_t* type;
 };
 
-__global__ void __launch_bounds__(kPlastBlock) growth_k(double* __restrict__ z, int64_t n,
-                                                       uint64_t seed, DevStep step,
-                                                       double ca_mean, double ca_sd, double xi,
-                                                       double zeta, double scale) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= 3 * n) return;
+struct Growth {
+  double ca_mean, ca_sd, xi, zeta, scale;
+};
+
+// Element count g (kind g / n of neuron g % n) after the growth.
+__device__ __forceinline__ void grow(double* __restrict__ z, int64_t g, int64_t n, uint64_t seed,
+                                     uint64_t step, const Growth& c) {
   const int64_t k = g / n, j = g - k * n;
-  uint64_t c0 = (uint64_t)j, c1 = (uint64_t)k, c2 = step.get(), c3 = 0;
+  uint64_t c0 = (uint64_t)j, c1 = (uint64_t)k, c2 = step, c3 = 0;
   philox4x64_10(c0, c1, c2, c3, seed, 2);
   const double u1 = (double)((c0 >> 11) + 1) * 0x1p-53;     // (0, 1]
   const double u2 = (double)(c1 >> 11) * 0x1p-53;           // [0, 1)
   const double two_pi = 6.283185307179586476925286766559;
   const double gauss = sqrt(-2.0 * log(u1)) * cos(two_pi * u2);
-  const double ca = ca_mean + ca_sd * gauss;
-  const double r = (ca - xi) / zeta;
+  const double ca = c.ca_mean + c.ca_sd * gauss;
+  const double r = (ca - c.xi) / c.zeta;
   const double e = exp(-(r * r));
-  const double zz = z[g] + scale * (2.0 * e - 1.0);
+  const double zz = z[g] + c.scale * (2.0 * e - 1.0);
   z[g] = zz > 0.0 ? zz : 0.0;
 }
 
@@ -56,26 +57,6 @@ __device__ __forceinline__ void unbind(const SynList& L, int64_t s, int64_t n, i
   atomicSub(&bound[L.src[s]], 1);
   atomicSub(&bound[(1 + (int64_t)L.type[s]) * n + L.tgt[s]], 1);
 }
-
-__global__ void __launch_bounds__(kPlastBlock) del_keys_k(uint64_t* __restrict__ key,
-                                                         int32_t* __restrict__ val, DevCount m,
-                                                         uint64_t seed, DevStep step) {
-  const int64_t m_ = m.get();
-  const uint64_t st = step.get();
-  for (int64_t s = gtid(); s < m_; s += gstride()) {
-    key[s] = philox_word0(seed, 3, (uint64_t)s, st, 0, 0);
-    val[s] = (int32_t)s;
-  }
-}
-
-// Deletion as a selection, not a sort: the `want` synapses of smallest (priority,
-// index) go. Most significant digit first, each pass narrows the candidates to the
-// keys that share the digits chosen so far, and counts the candidates' next digit.
-struct DelSelect {
-  uint64_t prefix;              // digits chosen so far (the threshold key, at the end)
-  uint64_t mask;                // their bits
-  int64_t want;                 // synapses still to choose among the candidates
-};
 
 // Synapses a deletion removes from a list of m: round(frac m), halves up, at most m
 // (the product and the sum rounded separately, as on the host).
@@ -86,157 +67,404 @@ __host__ __device__ inline int64_t delete_count(double frac, int64_t m) {
   return c < m ? c : m;
 }
 
-__global__ void del_select_init_k(DelSelect* st, double frac, DevCount m, uint32_t* hist) {
-  if (threadIdx.x == 0) {
-    st->prefix = 0;
-    st->mask = 0;
-    st->want = delete_count(frac, m.get());
-  }
-  hist[threadIdx.x] = 0;        // 256 threads
-}
+// Deletion as a selection: the `want` synapses of smallest (priority, index) go. The
+// priorities are uniform 64-bit numbers, so the want-th smallest lies within a few standard
+// deviations of want / m: one pass draws all priorities, counts those below that range
+// and keeps those in it (their number grows as sqrt(m)), one block finds the want-th
+// smallest among the kept ones, and one pass marks. (Eight passes of digit histograms over
+// all priorities, a pick after each and a scan of the ties took 22 launches, 0.3 ms at 2M
+// neurons.) Whatever the priorities, the choice is exact: where the range misses the
+// want-th smallest or a block's room overflows, the one block searches all priorities.
+constexpr int kDelRoom = 256;              // kept priorities per block
+constexpr int kDelAll = 4096;              // up to this many synapses, all are kept
+constexpr int kDelSigma = 7;               // half width of the range, standard deviations
 
-// Histogram of digit (key >> shift) & 255 over the keys that match the chosen digits.
-__global__ void __launch_bounds__(kPlastBlock) del_select_hist_k(const uint64_t* __restrict__ key,
-                                                                DevCount mc, const DelSelect* st,
-                                                                int shift, uint32_t* hist) {
-  __shared__ uint32_t h[256];
-  for (int d = threadIdx.x; d < 256; d += blockDim.x) h[d] = 0;
-  __syncthreads();
-  const uint64_t prefix = st->prefix, mask = st->mask;
-  const int64_t m = st->want > 0 ? mc.get() : 0;
-  for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < m;
-       s += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t k = key[s];
-    if ((k & mask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < 256; d += blockDim.x)
-    if (h[d]) atomicAdd(&hist[d], h[d]);
-}
-
-// One block of 256 threads: the digit whose candidates hold the want-th smallest key;
-// the candidates with smaller digits are all chosen. Clears the histogram.
-__global__ void __launch_bounds__(256) del_select_pick_k(DelSelect* st, uint32_t* hist,
-                                                         int shift) {
-  __shared__ int64_t c[256];
-  const int d = threadIdx.x;
-  const int64_t h = hist[d];
-  c[d] = h;
-  __syncthreads();
-  for (int o = 1; o < 256; o <<= 1) {             // inclusive scan (Hillis-Steele)
-    const int64_t v = d >= o ? c[d - o] : 0;
-    __syncthreads();
-    c[d] += v;
-    __syncthreads();
-  }
-  const int64_t before = c[d] - h;
-  const int64_t want = st->want;
-  __syncthreads();
-  if (h > 0 && before < want && want <= c[d]) {
-    st->prefix |= (uint64_t)d << shift;
-    st->mask |= (uint64_t)255 << shift;
-    st->want = want - before;
-  }
-  hist[d] = 0;
-}
-
-// Keys equal to the threshold (in index order, so ties go as a stable sort would).
-struct DelTie {
-  const DelSelect* st;
-  __device__ int32_t operator()(uint64_t k, int64_t) const { return k == st->prefix ? 1 : 0; }
+struct DelSelect {
+  uint64_t key;                 // synapses below (key, index) go, that one included
+  int64_t index;                // -1: none goes
 };
 
-// Below the threshold key, or among its first `want` ties (tie_pos: exclusive scan of
-// the ties), a synapse goes.
-__global__ void __launch_bounds__(kPlastBlock) del_select_mark_k(
-    const uint64_t* __restrict__ key, DevCount m, const DelSelect* st,
-    const int32_t* __restrict__ tie_pos, SynList L, int64_t n, uint8_t* __restrict__ dead,
-    int32_t* bound) {
-  const int64_t want = st->want;
-  if (want <= 0) return;
-  const int64_t m_ = m.get();
-  const uint64_t kt = st->prefix;
-  for (int64_t s = gtid(); s < m_; s += gstride()) {
-    const uint64_t k = key[s];
-    if (k < kt || (k == kt && tie_pos[s] < want)) {
-      dead[s] = 1;
-      unbind(L, s, n, bound);
+struct DelWs {
+  DelSelect* st;
+  int64_t* below;               // [blocks] priorities below the range
+  int32_t* kept;                // [blocks] priorities in the range (more than kDelRoom: overflow)
+  uint64_t* ckey;               // [blocks][kDelRoom]
+  int32_t* cidx;
+};
+
+// The range [lo, hi] of priorities that are kept (hi included).
+__device__ __forceinline__ void del_range(int64_t want, int64_t m, uint64_t& lo, uint64_t& hi) {
+  lo = 0;
+  hi = ~0ull;
+  if (m <= kDelAll) return;
+  const double p = (double)want / (double)m;
+  const double w = kDelSigma * sqrt(p * (1.0 - p) / (double)m) + 64.0 / (double)m;
+  if (p - w > 0.0) lo = (uint64_t)((p - w) * 0x1p64);
+  if (p + w < 1.0) hi = (uint64_t)((p + w) * 0x1p64);
+}
+
+// Growth of all element counts, then (frac > 0) the priorities of all m synapses, each
+// block's kept ones and counts. Bound by the random numbers' 64-bit products.
+__global__ void __launch_bounds__(kPlastBlock) grow_draw_k(double* __restrict__ z, int64_t n,
+                                                          Growth c, double frac, DevCount mc,
+                                                          uint64_t seed, DevStep step,
+                                                          uint64_t* __restrict__ key, DelWs W) {
+  __shared__ int32_t nkept;
+  __shared__ int32_t nbelow[kPlastBlock / kWave];
+  if (threadIdx.x == 0) nkept = 0;
+  __syncthreads();
+  const uint64_t st = step.get();
+  for (int64_t g = gtid(); g < 3 * n; g += gstride()) grow(z, g, n, seed, st, c);
+  const int64_t m = mc.get();
+  if (!(frac > 0.0) || !W.st) return;
+  uint64_t lo, hi;
+  del_range(delete_count(frac, m), m, lo, hi);
+  int32_t mine = 0;
+  for (int64_t s = gtid(); s < m; s += gstride()) {
+    const uint64_t k = philox_word0(seed, 3, (uint64_t)s, st, 0, 0);
+    key[s] = k;
+    mine += k < lo ? 1 : 0;
+    if (k >= lo && k <= hi) {
+      const int at = atomicAdd(&nkept, 1);
+      if (at < kDelRoom) {
+        W.ckey[(int64_t)blockIdx.x * kDelRoom + at] = k;
+        W.cidx[(int64_t)blockIdx.x * kDelRoom + at] = (int32_t)s;
+      }
     }
   }
+  for (int o = 1; o < kWave; o <<= 1) mine += __shfl_xor(mine, o, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) nbelow[threadIdx.x / kWave] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t b = 0;
+    for (int w = 0; w < kPlastBlock / kWave; ++w) b += nbelow[w];
+    W.below[blockIdx.x] = b;
+    W.kept[blockIdx.x] = nkept;
+  }
+}
+
+constexpr int kPickBlock = 1024;
+constexpr int kPickBins = 4096;
+
+// The value of each thread summed over the block; synchronises.
+__device__ __forceinline__ int64_t pick_sum(int64_t v, int64_t* lds) {
+  for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
+  __syncthreads();
+  if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = v;
+  __syncthreads();
+  int64_t s = 0;
+  for (int w = 0; w < kPickBlock / kWave; ++w) s += lds[w];
+  return s;
+}
+
+// The bin that holds the r-th item (r from 1) of a histogram, and the items before it.
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, int64_t r, int64_t* lds, int* bin,
+                                         int64_t* before) {
+  constexpr int kPer = kPickBins / kPickBlock;
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  int64_t s = 0;
+  for (int q = 0; q < kPer; ++q) s += hist[t * kPer + q];
+  int64_t x = s;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int64_t y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  __syncthreads();
+  if (lane == kWave - 1) lds[w] = x;
+  __syncthreads();
+  int64_t at = x - s;
+  for (int k = 0; k < w; ++k) at += lds[k];
+  for (int q = 0; q < kPer; ++q) {
+    const int64_t h = hist[t * kPer + q];
+    if (at < r && r <= at + h) {
+      *bin = t * kPer + q;
+      *before = at;
+    }
+    at += h;
+  }
+  __syncthreads();
+}
+
+// One block: the want-th smallest (priority, index).
+__global__ void __launch_bounds__(kPickBlock) del_pick_k(double frac, DevCount mc, int blocks,
+                                                        const uint64_t* __restrict__ key,
+                                                        DelWs W) {
+  __shared__ uint32_t hist[kPickBins];
+  __shared__ int64_t lds[kPickBlock / kWave];
+  __shared__ uint64_t lk[kPickBlock];
+  __shared__ int32_t li[kPickBlock];
+  __shared__ int bin;
+  __shared__ int64_t before;
+  __shared__ int32_t nlist;
+  __shared__ int32_t first[kStrideGrid + 1];     // kept priorities of the blocks before
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  const int64_t m = mc.get();
+  const int64_t want = delete_count(frac, m);
+  if (want <= 0) {
+    if (t == 0) *W.st = DelSelect{0, -1};
+    return;
+  }
+  uint64_t lo, hi;
+  del_range(want, m, lo, hi);
+  constexpr int kPer = (int)kStrideGrid / kPickBlock;           // consecutive blocks of a thread
+  int64_t nb = 0, nk = 0, over = 0;
+  int32_t kept[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int b = t * kPer + q;
+    kept[q] = b < blocks ? W.kept[b] : 0;
+    nb += b < blocks ? W.below[b] : 0;
+    over += kept[q] > kDelRoom ? 1 : 0;
+    nk += kept[q];
+  }
+  int64_t x = nk;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int64_t y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  if (lane == kWave - 1) lds[w] = x;
+  __syncthreads();
+  int64_t at = x - nk;
+  for (int k = 0; k < w; ++k) at += lds[k];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    first[t * kPer + q] = (int32_t)at;
+    at += kept[q];
+  }
+  if (t == kPickBlock - 1) first[kStrideGrid] = (int32_t)at;
+  nb = pick_sum(nb, lds);
+  over = pick_sum(over, lds);
+  nk = first[kStrideGrid];
+  const int64_t r = want - nb;
+  // the i-th kept priority of all: its place in the blocks' rooms
+  auto place = [&](int i) -> int64_t {
+    int lo_ = 0, hi_ = (int)kStrideGrid - 1;
+    while (lo_ < hi_) {
+      const int mid = (lo_ + hi_ + 1) >> 1;
+      if (first[mid] <= i) lo_ = mid; else hi_ = mid - 1;
+    }
+    return (int64_t)lo_ * kDelRoom + (i - first[lo_]);
+  };
+  if (over == 0 && r >= 1 && r <= nk) {
+    // bins of equal width over the range, then the few in the one that holds the r-th
+    const uint64_t width = hi - lo;
+    int sh = 0;
+    while ((width >> sh) >= kPickBins) ++sh;
+    for (int q = t; q < kPickBins; q += kPickBlock) hist[q] = 0;
+    if (t == 0) nlist = 0;
+    __syncthreads();
+    for (int i = t; i < (int)nk; i += kPickBlock)
+      atomicAdd(&hist[(W.ckey[place(i)] - lo) >> sh], 1u);
+    __syncthreads();
+    pick_bin(hist, r, lds, &bin, &before);
+    for (int i = t; i < (int)nk; i += kPickBlock) {
+      const int64_t p = place(i);
+      const uint64_t k = W.ckey[p];
+      if ((int)((k - lo) >> sh) != bin) continue;
+      const int l = atomicAdd(&nlist, 1);
+      if (l < kPickBlock) {
+        lk[l] = k;
+        li[l] = W.cidx[p];
+      }
+    }
+    __syncthreads();
+    if (nlist <= kPickBlock) {
+      if (t < nlist) {
+        int64_t rank = 0;
+        for (int q = 0; q < nlist; ++q)
+          rank += (lk[q] < lk[t] || (lk[q] == lk[t] && li[q] < li[t])) ? 1 : 0;
+        if (before + rank == r - 1) *W.st = DelSelect{lk[t], li[t]};
+      }
+      return;
+    }
+  }
+  // all priorities, most significant digits first, then the index among equal ones
+  uint64_t prefix = 0, mask = 0;
+  int64_t left = want;
+  for (int shift = 52; shift > -12; shift -= 12) {
+    const int s0 = shift < 0 ? 0 : shift;
+    const uint64_t digit = shift < 0 ? (1u << (12 + shift)) - 1 : kPickBins - 1;
+    for (int q = t; q < kPickBins; q += kPickBlock) hist[q] = 0;
+    __syncthreads();
+    for (int64_t s = t; s < m; s += kPickBlock) {
+      const uint64_t k = key[s];
+      if ((k & mask) == prefix) atomicAdd(&hist[(k >> s0) & digit], 1u);
+    }
+    __syncthreads();
+    pick_bin(hist, left, lds, &bin, &before);
+    prefix |= (uint64_t)bin << s0;
+    mask |= digit << s0;
+    left -= before;
+    __syncthreads();
+  }
+  for (int64_t s0 = 0; s0 < m && left > 0; s0 += kPickBlock) {
+    const int64_t s = s0 + t;
+    const bool eq = s < m && key[s] == prefix;
+    const int64_t c = pick_sum(eq ? 1 : 0, lds);
+    if (c < left) {
+      left -= c;
+      continue;
+    }
+    // the left-th of this chunk
+    const uint64_t b = __ballot(eq);
+    __syncthreads();
+    if (lane == 0) lds[w] = __popcll(b);
+    __syncthreads();
+    int64_t rank = __popcll(b & ((1ull << lane) - 1ull));
+    for (int k = 0; k < w; ++k) rank += lds[k];
+    if (eq && rank == left - 1) *W.st = DelSelect{prefix, s};
+    break;
+  }
+}
+
+// Marks the deleted synapses (st null: none, all marks cleared) and frees their elements.
+__global__ void __launch_bounds__(kPlastBlock) del_mark_k(const uint64_t* __restrict__ key,
+                                                         DevCount mc, const DelSelect* st,
+                                                         SynList L, int64_t n,
+                                                         uint8_t* __restrict__ dead,
+                                                         int32_t* bound) {
+  const int64_t m = mc.get();
+  const DelSelect d = st ? *st : DelSelect{0, -1};
+  for (int64_t s = gtid(); s < m; s += gstride()) {
+    bool go = false;
+    if (d.index >= 0) {
+      const uint64_t k = key[s];
+      go = k < d.key || (k == d.key && s <= d.index);
+    }
+    dead[s] = go ? 1 : 0;
+    if (go) unbind(L, s, n, bound);
+  }
+}
+
+// Retraction. Kind 0 (axons) goes first: it frees dendritic elements too. Kinds 1 and 2 go
+// together, their owners being different arrays: a synapse has one dendritic element, of
+// the kind its type says. Of an owner's live synapses of the kind, the `excess` of smallest
+// (priority, index) go. The candidates (the synapses of owners with an excess) are counted
+// per owner, laid out by owner (a scan and a scatter), and ranked within their owner, in
+// place of a sort of them all by (owner, priority) for each kind: 6 launches twice instead
+// of 18 to 45 three times.
+struct RetractWs {
+  int32_t* exc;                 // [owners] elements to retract
+  int32_t* cnt;                 // [owners] candidates
+  int32_t* off;                 // [owners] candidates of the owners before
+  uint8_t* flag;                // [m] candidate
+  int32_t* within;              // [m] place among the owner's candidates
+  uint64_t* seg;                // [candidates] (priority << 32 | synapse), by owner
+  int32_t* nlarge;              // [1] owners with more than kSegSmall candidates,
+  int32_t* large;               // [m / kSegSmall + 1] and which
+};
+constexpr int kSegSmall = 64;   // candidates of an owner ranked by one thread each
+
+// Owner of synapse s: kind 0: its source; kinds 1 and 2 (k = 1): its target in its type's
+// array (-1: a type that binds no element).
+__device__ __forceinline__ int64_t owner_of(const SynList& L, int64_t s, int64_t n, int k) {
+  if (k == 0) return L.src[s];
+  const int t = (int)L.type[s];
+  return t > 1 ? -1 : t * n + L.tgt[s];
 }
 
 __global__ void __launch_bounds__(kPlastBlock) excess_k(const int32_t* __restrict__ bound_k,
-                                                       const double* __restrict__ z_k, int64_t n,
-                                                       int32_t* __restrict__ exc) {
+                                                       const double* __restrict__ z_k,
+                                                       int64_t owners, RetractWs R) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  exc[j] = bound_k[j] - (int32_t)floor(z_k[j]);
+  if (j == 0) *R.nlarge = 0;
+  if (j >= owners) return;
+  R.exc[j] = bound_k[j] - (int32_t)floor(z_k[j]);
+  R.cnt[j] = 0;
 }
 
-// Owner of synapse s for element kind k, or -1 if s binds no element of that kind.
-__device__ __forceinline__ int32_t owner_of(const SynList& L, int64_t s, int k) {
-  if (k == 0) return L.src[s];
-  return (int)L.type[s] == k - 1 ? L.tgt[s] : -1;
-}
-
-struct RetractFlag {            // live synapse of a neuron with an excess of kind k
-  SynList L;
-  const uint8_t* dead;
-  const int32_t* exc;
-  int k;
-  __device__ int32_t operator()(int32_t, int64_t s) const {
-    if (dead[s]) return 0;
-    const int32_t o = owner_of(L, s, k);
-    return (o >= 0 && exc[o] > 0) ? 1 : 0;
+__global__ void __launch_bounds__(kPlastBlock) retract_count_k(SynList L, int64_t n, int k,
+                                                              const uint8_t* __restrict__ dead,
+                                                              DevCount mc, RetractWs R) {
+  const int64_t m = mc.get();
+  for (int64_t s = gtid(); s < m; s += gstride()) {
+    bool f = false;
+    if (!dead[s]) {
+      const int64_t o = owner_of(L, s, n, k);
+      f = o >= 0 && R.exc[o] > 0;
+      if (f) R.within[s] = atomicAdd(&R.cnt[o], 1);
+    }
+    R.flag[s] = f ? 1 : 0;
   }
-};
-
-// The candidate flags of one kind, once (the scan and the key pass read the bytes).
-__global__ void __launch_bounds__(kPlastBlock) retract_flag_k(RetractFlag F, DevCount m,
-                                                             uint8_t* __restrict__ flag) {
-  const int64_t m_ = m.get();
-  for (int64_t s = gtid(); s < m_; s += gstride()) flag[s] = (uint8_t)F(0, s);
 }
 
-struct ByteCount {
-  __device__ int32_t operator()(uint8_t a, int64_t) const { return (int32_t)a; }
-};
-
-__global__ void __launch_bounds__(kPlastBlock) cand_write_k(RetractFlag F, const int32_t* __restrict__ pos,
-                                                           DevCount m, uint64_t seed, DevStep step,
-                                                           uint64_t* __restrict__ key,
-                                                           int32_t* __restrict__ val) {
-  const int64_t m_ = m.get();
+__global__ void __launch_bounds__(kPlastBlock) retract_lay_k(SynList L, int64_t n, int k,
+                                                            DevCount mc, uint64_t seed,
+                                                            DevStep step, RetractWs R) {
+  const int64_t m = mc.get();
   const uint64_t st = step.get();
-  for (int64_t s = gtid(); s < m_; s += gstride()) {
-    if (pos[s + 1] == pos[s]) continue;       // not a candidate (pos: the flags' scan)
-    const int32_t o = owner_of(F.L, s, F.k);
-    const uint64_t q = philox_word0(seed, 4, (uint64_t)s, st, (uint64_t)F.k, 0) >> 32;
-    key[pos[s]] = ((uint64_t)(uint32_t)o << 32) | q;
-    val[pos[s]] = (int32_t)s;
+  for (int64_t s = gtid(); s < m; s += gstride()) {
+    if (!R.flag[s]) continue;
+    const int64_t o = owner_of(L, s, n, k);
+    const uint64_t kind = k == 0 ? 0 : 1 + (uint64_t)L.type[s];
+    const uint64_t q = philox_word0(seed, 4, (uint64_t)s, st, kind, 0) >> 32;
+    const int32_t at = R.within[s];
+    R.seg[(int64_t)R.off[o] + at] = (q << 32) | (uint64_t)s;
+    if (at == 0 && R.cnt[o] > kSegSmall) R.large[atomicAdd(R.nlarge, 1)] = (int32_t)o;
   }
 }
 
-// Candidates sorted by (owner, priority, s): the first exc[owner] of each owner go.
-__global__ void __launch_bounds__(kPlastBlock) retract_k(const uint64_t* __restrict__ key,
-                                                        const int32_t* __restrict__ val,
-                                                        DevCount cnt, const int32_t* __restrict__ exc,
-                                                        SynList L, int64_t n,
-                                                        uint8_t* __restrict__ dead, int32_t* bound) {
-  const int64_t c = cnt.get();
-  for (int64_t p = gtid(); p < c; p += gstride()) {
-    const uint64_t o = key[p] >> 32;
-    // first candidate of this owner
-    int64_t lo = 0, hi = p;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((key[mid] >> 32) < o) lo = mid + 1; else hi = mid;
+__device__ __forceinline__ void retract_one(const SynList& L, int64_t s, int64_t n,
+                                            uint8_t* dead, int32_t* bound) {
+  dead[s] = 1;
+  unbind(L, s, n, bound);
+}
+
+// Each candidate's rank among its owner's, one thread each; the owners with many
+// candidates a block each (the excess-th smallest by digits of 8 bits, most significant
+// first).
+__global__ void __launch_bounds__(kPlastBlock) retract_k(SynList L, int64_t n, int k, DevCount mc,
+                                                        uint8_t* __restrict__ dead, int32_t* bound,
+                                                        RetractWs R) {
+  __shared__ uint32_t hist[256];
+  __shared__ uint64_t prefix;
+  __shared__ int32_t left;
+  const int64_t m = mc.get();
+  for (int64_t s = gtid(); s < m; s += gstride()) {
+    if (!R.flag[s]) continue;
+    const int64_t o = owner_of(L, s, n, k);
+    const int32_t c = R.cnt[o], e = R.exc[o];
+    if (c > kSegSmall) continue;
+    const uint64_t* seg = R.seg + R.off[o];
+    int32_t rank = 0;
+    if (c > e) {
+      const uint64_t me = seg[R.within[s]];
+      for (int32_t q = 0; q < c; ++q) rank += seg[q] < me ? 1 : 0;
     }
-    if (p - lo < (int64_t)exc[o]) {
-      const int64_t s = val[p];
-      dead[s] = 1;
-      unbind(L, s, n, bound);
+    if (rank < e) retract_one(L, s, n, dead, bound);
+  }
+  const int32_t nlarge = *R.nlarge;
+  const int t = (int)threadIdx.x;
+  for (int32_t q = blockIdx.x; q < nlarge; q += gridDim.x) {    // uniform over the block
+    const int64_t o = R.large[q];
+    const int32_t c = R.cnt[o], e = R.exc[o];
+    const uint64_t* seg = R.seg + R.off[o];
+    uint64_t mask = 0;
+    if (t == 0) {
+      prefix = 0;
+      left = e;
     }
+    for (int shift = 56; shift >= 0 && e < c; shift -= 8) {
+      hist[t] = 0;
+      __syncthreads();
+      const uint64_t pre = prefix;
+      for (int32_t i = t; i < c; i += kPlastBlock)
+        if ((seg[i] & mask) == pre) atomicAdd(&hist[(seg[i] >> shift) & 255u], 1u);
+      __syncthreads();
+      if (t == 0) {
+        int32_t l = left;
+        int d = 0;
+        while (d < 255 && (int32_t)hist[d] < l) l -= (int32_t)hist[d++];
+        left = l;
+        prefix = pre | ((uint64_t)d << shift);
+      }
+      mask |= (uint64_t)255 << shift;
+      __syncthreads();
+    }
+    const uint64_t last = e < c ? prefix : ~0ull;
+    for (int32_t i = t; i < c; i += kPlastBlock)
+      if (seg[i] <= last) retract_one(L, (int64_t)(uint32_t)seg[i], n, dead, bound);
+    __syncthreads();
   }
 }
 
@@ -247,8 +475,9 @@ struct LiveFlag {
 
 __global__ void __launch_bounds__(kPlastBlock) compact_k(SynList in, const uint8_t* __restrict__ dead,
                                                         const int32_t* __restrict__ pos, DevCount m,
-                                                        SynList out) {
+                                                        SynList out, int64_t* survivors) {
   const int64_t m_ = m.get();
+  if (gtid() == 0) *survivors = pos[m_];
   for (int64_t s = gtid(); s < m_; s += gstride()) {
     if (dead[s]) continue;
     const int64_t p = pos[s];
@@ -268,21 +497,13 @@ __global__ void __launch_bounds__(kPlastBlock) copy_list_k(SynList from, DevCoun
   }
 }
 
-// A count the device found (a scan total at position *at of `pos`) as a 64-bit and a
-// 32-bit scalar.
-__global__ void take_count_k(const int32_t* __restrict__ pos, DevCount at, int64_t* c64,
-                             int32_t* c32) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int32_t c = pos[at.get()];
-  if (c64) *c64 = c;
-  if (c32) *c32 = c;
-}
-
 __global__ void __launch_bounds__(kPlastBlock) vacancy_k(const double* __restrict__ z,
                                                         const int32_t* __restrict__ bound,
                                                         int64_t n, int32_t* va, int32_t* ve,
-                                                        int32_t* vi) {
+                                                        int32_t* vi, const int64_t* m,
+                                                        int64_t* m_out) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g == 0) *m_out = m ? *m : 0;       // the list's length, once nothing reads the old one
   if (g >= 3 * n) return;
   const int64_t k = g / n, j = g - k * n;
   int32_t* out = k == 0 ? va : k == 1 ? ve : vi;
@@ -338,11 +559,6 @@ __global__ void record_end_k(DevCount cnt, int64_t* m, int64_t cap) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const int64_t c = cnt.get();
   if (*m + c <= cap) *m += c;
-}
-
-__global__ void __launch_bounds__(kPlastBlock) fill_u8_k(uint8_t* p, DevCount n, uint8_t v) {
-  const int64_t c = n.get();
-  for (int64_t i = gtid(); i < c; i += gstride()) p[i] = v;
 }
 
 }  // namespace msp

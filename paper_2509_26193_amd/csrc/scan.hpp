@@ -66,14 +66,27 @@ __global__ void __launch_bounds__(kScanBlock) scan_reduce_k(const Tin* in, int64
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// out[i] = sum_{k<i} f(in[k]) + offsets[block]; if total_out, out[n] = grand total.
+// out[i] = sum_{k<i} f(in[k]) + the block's offset; if write_total, out[n] = grand total.
+// offsets: the scanned block sums (nsums 0), or the block sums themselves, of which every
+// block adds up those before it (nsums of them, up to kScanDirect: a launch fewer, which is
+// what a scan of few items is bound by; 4 096 sums are 16 loads per thread).
+constexpr int kScanDirect = 4096;
+
 template <class T, class Tin, class F>
 __global__ void __launch_bounds__(kScanBlock) scan_apply_k(const Tin* in, int64_t n, T* out,
-                                                          const T* offsets, F f, int write_total,
-                                                          const int64_t* dn) {
+                                                          const T* offsets, int nsums, F f,
+                                                          int write_total, const int64_t* dn) {
   __shared__ T lds4[kScanBlock / kWave];
   n = scan_count(n, dn);
   if ((int64_t)blockIdx.x * kScanTile > n) return;   // nothing to write (uniform)
+  T before = 0;
+  if (nsums > 0) {
+    T part = 0;
+    for (int q = threadIdx.x; q < (int)blockIdx.x; q += kScanBlock) part += offsets[q];
+    (void)block_exclusive_scan<T>(part, lds4, &before);
+  } else if (offsets) {
+    before = offsets[blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   T v[kScanItems];
   T s = 0;
@@ -85,7 +98,7 @@ __global__ void __launch_bounds__(kScanBlock) scan_apply_k(const Tin* in, int64_
   }
   T tot;
   T pre = block_exclusive_scan<T>(s, lds4, &tot);
-  pre += offsets ? offsets[blockIdx.x] : T(0);
+  pre += before;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     int64_t idx = base + k;
@@ -136,8 +149,8 @@ hipError_t exclusive_scan(const Tin* in, T* out, int64_t n, F f, bool write_tota
   // with a device count the launch also covers position n, where the total may go
   const int64_t nb = (n + (dn ? 1 : 0) + kScanTile - 1) / kScanTile;
   if (nb == 1) {
-    scan_apply_k<T, Tin, F><<<1, kScanBlock, 0, s>>>(in, n, out, nullptr, f, write_total ? 1 : 0,
-                                                     dn);
+    scan_apply_k<T, Tin, F><<<1, kScanBlock, 0, s>>>(in, n, out, nullptr, 0, f,
+                                                     write_total ? 1 : 0, dn);
     return hipGetLastError();
   }
   Temp own(s);
@@ -154,9 +167,13 @@ hipError_t exclusive_scan(const Tin* in, T* out, int64_t n, F f, bool write_tota
   scan_reduce_k<T, Tin, F><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, sums, f, dn);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = exclusive_scan<T, T, Ident<T>>(sums, sums, nb, Ident<T>(), false, s, rest);
-  if (e != hipSuccess) return e;
-  scan_apply_k<T, Tin, F><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, out, sums, f,
+  const bool direct = nb <= kScanDirect;
+  if (!direct) {
+    e = exclusive_scan<T, T, Ident<T>>(sums, sums, nb, Ident<T>(), false, s, rest);
+    if (e != hipSuccess) return e;
+  }
+  scan_apply_k<T, Tin, F><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, out, sums,
+                                                             direct ? (int)nb : 0, f,
                                                              write_total ? 1 : 0, dn);
   return hipGetLastError();
 }

@@ -96,49 +96,48 @@ inline hipError_t enqueue_commit(const CommitWs& w, const int32_t* target,
 
 // ---------------------------------------------------------------------------- plasticity
 struct PlastConst {
-  double ca_mean, ca_sd, xi, zeta, scale;   // growth rule (see growth_k)
+  Growth growth;                            // growth rule (see grow)
   double delete_fraction;
 };
 
 // Working memory of a plasticity step over a list of up to cap_m synapses.
 struct PlastWs {
   uint8_t* dead;
-  uint8_t* cflag;               // retraction candidates of one kind
-  uint64_t* k0;
-  uint64_t* k1;
-  int32_t* v0;
-  int32_t* v1;
-  int32_t* pos;                 // [cap_m + 1]
-  int32_t* exc;                 // [n]
-  void* sort_ws;
+  uint64_t* key;                // [cap_m] deletion priorities, then the retraction candidates
+  int32_t* pos;                 // [cap_m + 1] places among the candidates, then the survivors
+  DelWs del;
+  RetractWs ret;                // (2n owners)
   void* scan_ws;
   SynList O;                    // the survivors, compacted
-  DelSelect* st;
-  uint32_t* hist;               // [256]
-  int64_t* cnt;                 // [2] retraction candidates, survivors
-  int32_t* cnt32;               // [1] retraction candidates (the sort's count)
+  int64_t* cnt;                 // [1] survivors
 };
 
 inline PlastWs plast_ws(void* base, int64_t n, int64_t cap_m, size_t* bytes) {
   Carver c{static_cast<char*>(base)};
+  const int64_t blocks = kStrideGrid;
   PlastWs w;
   w.dead = c.take<uint8_t>(cap_m);
-  w.cflag = c.take<uint8_t>(cap_m);
-  w.k0 = c.take<uint64_t>(cap_m);
-  w.k1 = c.take<uint64_t>(cap_m);
-  w.v0 = c.take<int32_t>(cap_m);
-  w.v1 = c.take<int32_t>(cap_m);
+  w.key = c.take<uint64_t>(cap_m);
   w.pos = c.take<int32_t>(cap_m + 1);
-  w.exc = c.take<int32_t>(n);
-  w.sort_ws = c.take_bytes(radix_sort_ws_bytes(cap_m));
-  w.scan_ws = c.take_bytes(scan_tmp_bytes<int32_t>(cap_m + 1));
+  w.del.st = c.take<DelSelect>(1);
+  w.del.below = c.take<int64_t>(blocks);
+  w.del.kept = c.take<int32_t>(blocks);
+  w.del.ckey = c.take<uint64_t>(blocks * kDelRoom);
+  w.del.cidx = c.take<int32_t>(blocks * kDelRoom);
+  w.ret.exc = c.take<int32_t>(2 * n);
+  w.ret.cnt = c.take<int32_t>(2 * n);
+  w.ret.off = c.take<int32_t>(2 * n);
+  w.ret.flag = c.take<uint8_t>(cap_m);
+  w.ret.within = w.pos;
+  w.ret.seg = w.key;
+  w.ret.nlarge = c.take<int32_t>(1);
+  w.ret.large = c.take<int32_t>(cap_m / kSegSmall + 1);
+  w.scan_ws = c.take_bytes(std::max(scan_tmp_bytes<int32_t>(cap_m + 1),
+                                    scan_tmp_bytes<int32_t>(2 * n)));
   w.O.src = c.take<int32_t>(cap_m);
   w.O.tgt = c.take<int32_t>(cap_m);
   w.O.type = c.take<uint8_t>(cap_m);
-  w.st = c.take<DelSelect>(1);
-  w.hist = c.take<uint32_t>(256);
-  w.cnt = c.take<int64_t>(2);
-  w.cnt32 = c.take<int32_t>(1);
+  w.cnt = c.take<int64_t>(1);
   *bytes = c.off;
   return w;
 }
@@ -150,60 +149,41 @@ inline hipError_t enqueue_plasticity(const PlastWs& w, int64_t n, const PlastCon
                                      uint64_t seed, DevStep step, double* z, int32_t* bound,
                                      SynList L, DevCount m, int64_t* m_out, int32_t* vac_axon,
                                      int32_t* vac_exc, int32_t* vac_inh, hipStream_t s) {
-  growth_k<<<grid_for(3 * n, kPlastBlock), kPlastBlock, 0, s>>>(z, n, seed, step, c.ca_mean,
-                                                               c.ca_sd, c.xi, c.zeta, c.scale);
+  const unsigned gm = grid_cap(m.v, kPlastBlock);
+  const bool del = m.v > 0 && c.delete_fraction > 0.0;
+  // (the blocks that draw priorities are those of a launch over the list, bounded alike)
+  const unsigned gg = std::max(gm, grid_cap(3 * n, kPlastBlock));
+  DelWs dw = w.del;
+  if (!del) dw.st = nullptr;
+  grow_draw_k<<<gg, kPlastBlock, 0, s>>>(z, n, c.growth, c.delete_fraction, m, seed, step, w.key,
+                                         dw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  const int64_t* survivors = nullptr;
   if (m.v > 0) {
-    const unsigned gm = grid_cap(m.v, kPlastBlock);
-    fill_u8_k<<<gm, kPlastBlock, 0, s>>>(w.dead, m, 0);
-    if (c.delete_fraction > 0.0) {
-      // the round(frac m) synapses of smallest (priority, index): a radix selection of
-      // the threshold key, most significant digit first, then one marking pass
-      del_keys_k<<<gm, kPlastBlock, 0, s>>>(w.k0, w.v0, m, seed, step);
-      del_select_init_k<<<1, 256, 0, s>>>(w.st, c.delete_fraction, m, w.hist);
-      for (int shift = 56; shift >= 0; shift -= 8) {
-        del_select_hist_k<<<gm, kPlastBlock, 0, s>>>(w.k0, m, w.st, shift, w.hist);
-        del_select_pick_k<<<1, 256, 0, s>>>(w.st, w.hist, shift);
-      }
-      e = exclusive_scan<int32_t, uint64_t, DelTie>(w.k0, w.pos, m.v, DelTie{w.st}, false, s,
-                                                     w.scan_ws, m.p);
+    if (del) del_pick_k<<<1, kPickBlock, 0, s>>>(c.delete_fraction, m, (int)gg, w.key, w.del);
+    del_mark_k<<<gm, kPlastBlock, 0, s>>>(w.key, m, dw.st, L, n, w.dead, bound);
+    for (int k = 0; k < 2; ++k) {
+      const int64_t owners = k == 0 ? n : 2 * n;
+      excess_k<<<grid_for(owners, kPlastBlock), kPlastBlock, 0, s>>>(bound + k * n, z + k * n,
+                                                                    owners, w.ret);
+      retract_count_k<<<gm, kPlastBlock, 0, s>>>(L, n, k, w.dead, m, w.ret);
+      e = exclusive_scan<int32_t, int32_t, Ident<int32_t>>(w.ret.cnt, w.ret.off, owners,
+                                                           Ident<int32_t>(), false, s, w.scan_ws);
       if (e != hipSuccess) return e;
-      del_select_mark_k<<<gm, kPlastBlock, 0, s>>>(w.k0, m, w.st, w.pos, L, n, w.dead, bound);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    int owner_bits = 1;
-    while (owner_bits < 31 && ((int64_t)1 << owner_bits) < n) ++owner_bits;
-    const int key_bits = (32 + owner_bits + 7) / 8 * 8;
-    const DevCount C{m.v, w.cnt};
-    for (int k = 0; k < 3; ++k) {
-      excess_k<<<grid_for(n, kPlastBlock), kPlastBlock, 0, s>>>(bound + k * n, z + k * n, n,
-                                                               w.exc);
-      const RetractFlag F{L, w.dead, w.exc, k};
-      retract_flag_k<<<gm, kPlastBlock, 0, s>>>(F, m, w.cflag);
-      e = exclusive_scan<int32_t, uint8_t, ByteCount>(w.cflag, w.pos, m.v, ByteCount(), true, s,
-                                                      w.scan_ws, m.p);
-      if (e != hipSuccess) return e;
-      take_count_k<<<1, 64, 0, s>>>(w.pos, m, w.cnt, w.cnt32);
-      cand_write_k<<<gm, kPlastBlock, 0, s>>>(F, w.pos, m, seed, step, w.k0, w.v0);
-      e = radix_sort_pairs_ws(w.k0, w.v0, w.k1, w.v1, m.v, 0, key_bits, s, w.sort_ws,
-                              w.cnt32);
-      if (e != hipSuccess) return e;
-      retract_k<<<gm, kPlastBlock, 0, s>>>(w.k0, w.v0, C, w.exc, L, n, w.dead, bound);
+      retract_lay_k<<<gm, kPlastBlock, 0, s>>>(L, n, k, m, seed, step, w.ret);
+      retract_k<<<gm, kPlastBlock, 0, s>>>(L, n, k, m, w.dead, bound, w.ret);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     e = exclusive_scan<int32_t, int32_t, LiveFlag>(nullptr, w.pos, m.v, LiveFlag{w.dead}, true, s,
                                                    w.scan_ws, m.p);
     if (e != hipSuccess) return e;
-    take_count_k<<<1, 64, 0, s>>>(w.pos, m, w.cnt + 1, nullptr);
-    compact_k<<<gm, kPlastBlock, 0, s>>>(L, w.dead, w.pos, m, w.O);
-    copy_list_k<<<gm, kPlastBlock, 0, s>>>(w.O, DevCount{m.v, w.cnt + 1}, L);
-    copy_scalar_k<<<1, 64, 0, s>>>(w.cnt + 1, m_out);
-  } else {
-    fill_i64_k<<<1, 64, 0, s>>>(m_out, 1, 0);
+    compact_k<<<gm, kPlastBlock, 0, s>>>(L, w.dead, w.pos, m, w.O, w.cnt);
+    copy_list_k<<<gm, kPlastBlock, 0, s>>>(w.O, DevCount{m.v, w.cnt}, L);
+    survivors = w.cnt;
   }
   vacancy_k<<<grid_for(3 * n, kPlastBlock), kPlastBlock, 0, s>>>(z, bound, n, vac_axon, vac_exc,
-                                                                vac_inh);
+                                                                vac_inh, survivors, m_out);
   return hipGetLastError();
 }
 
