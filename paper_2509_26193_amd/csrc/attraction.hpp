@@ -22,6 +22,7 @@
 #pragma once
 
 #include "batch.hpp"
+#include "refresh.hpp"
 
 namespace msp {
 
@@ -265,54 +266,104 @@ __global__ void fill_f64_k(double* p, int64_t n, double v) {
 }
 
 // Top-down: H(child) = H(node) + G(child) / v(child), per type; the root's H is
-// G(root) / v(root) (zero: the root is never accepted). One launch per depth.
-__global__ void push_level_k(const int32_t* __restrict__ nodes, int64_t cnt,
-                             const NodeRec* __restrict__ r0, const NodeRec* __restrict__ r1,
-                             const double* __restrict__ G, double* __restrict__ H, int64_t N) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= cnt) return;
-  const int32_t x = nodes[q];
-  const uint32_t meta = r0[x].meta;
-  if (meta & kLeafBit) return;
-  const int32_t end = (int32_t)(meta & kSkipMask);
+// G(root) / v(root) (zero: the root is never accepted).
+__device__ __forceinline__ void push_node(int32_t x, const int32_t (&kids)[8],
+                                          const NodeRec* __restrict__ r0,
+                                          const NodeRec* __restrict__ r1,
+                                          const double* __restrict__ G, double* H, int64_t N) {
+#pragma unroll
   for (int t = 0; t < 2; ++t) {
     const NodeRec* r = t ? r1 : r0;
     const double* Gt = G + (int64_t)t * N * 3;
     double* Ht = H + (int64_t)t * N * 3;
     const double hx = Ht[3 * (int64_t)x], hy = Ht[3 * (int64_t)x + 1], hz = Ht[3 * (int64_t)x + 2];
-    int32_t c = x + 1;
-    while (c < end) {
-      const NodeRec rc = r[c];
-      double ax = hx, ay = hy, az = hz;
-      if (rc.v > 0) {
-        const double iv = 1.0 / (double)rc.v;
-        ax += Gt[3 * (int64_t)c] * iv;
-        ay += Gt[3 * (int64_t)c + 1] * iv;
-        az += Gt[3 * (int64_t)c + 2] * iv;
-      }
-      Ht[3 * (int64_t)c] = ax;
-      Ht[3 * (int64_t)c + 1] = ay;
-      Ht[3 * (int64_t)c + 2] = az;
-      c = (rc.meta & kLeafBit) ? c + 1 : (int32_t)(rc.meta & kSkipMask);
+    int32_t v[8];
+    double g[8][3];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {          // all children's loads in flight at once
+      const int64_t c = kids[k] < 0 ? kids[0] : kids[k];
+      v[k] = r[c].v;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) g[k][a] = Gt[3 * c + a];
     }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (kids[k] < 0) break;
+      const int64_t c = kids[k];
+      double ax = hx, ay = hy, az = hz;
+      if (v[k] > 0) {
+        const double iv = 1.0 / (double)v[k];
+        ax += g[k][0] * iv;
+        ay += g[k][1] * iv;
+        az += g[k][2] * iv;
+      }
+      Ht[3 * c] = ax;
+      Ht[3 * c + 1] = ay;
+      Ht[3 * c + 2] = az;
+    }
+  }
+}
+
+// The chunks' passes top-down: the nodes that cross runs of chunks, then chunk ends, then
+// those inside (the refresh's kernels in the other order).
+__global__ void __launch_bounds__(kCross2Block) push_cross_k(
+    const int32_t* __restrict__ cross, const int32_t* __restrict__ kids_of, int count,
+    const NodeRec* __restrict__ r0, const NodeRec* __restrict__ r1, const double* __restrict__ G,
+    double* H, int64_t N) {
+  const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  CrossNode next(cross, kids_of, count, c, 0);
+  for (int d = 0; d <= kMaxDepth; ++d) {
+    const CrossNode at = next;
+    if (d < kMaxDepth) next = CrossNode(cross, kids_of, count, c, d + 1);
+    if (!__syncthreads_or(at.x >= 0)) continue;
+    if (at.x >= 0) push_node(at.x, at.kids, r0, r1, G, H, N);
+  }
+}
+
+__global__ void __launch_bounds__(512) push_chunk_k(Chunks C, const NodeRec* __restrict__ r0,
+                                                   const NodeRec* __restrict__ r1,
+                                                   const double* __restrict__ G, double* H,
+                                                   int64_t N) {
+  __shared__ int32_t skips[kSkipRoom];
+  const int32_t x0 = C.x[blockIdx.x], x1 = C.x[blockIdx.x + 1];
+  for (int32_t x = x0 + (int)threadIdx.x; x < x1 && x - x0 < kSkipRoom; x += blockDim.x)
+    skips[x - x0] = C.skip[x];
+  __syncthreads();
+  const ChunkSkips S{skips, C.skip, x0};
+  const int32_t* off = C.off + (int64_t)blockIdx.x * (kDepths + 1);
+  const int32_t* nodes = C.nodes + x0;
+  for (int k = kDepths; k >= 1; --k) {
+    const int32_t lo = off[k - 1], hi = off[k];
+    if (hi == lo) continue;                        // (uniform over the block)
+    for (int32_t q = lo + (int)threadIdx.x; q < hi; q += blockDim.x) {
+      int32_t kids[8];
+      S.kids(nodes[q], S(nodes[q]), kids);
+      push_node(nodes[q], kids, r0, r1, G, H, N);
+    }
+    __syncthreads();
   }
 }
 
 // Neurons: dpos_j += sum_t v_j^t H^t(leaf of j); then convert to float32.
 __global__ void push_leaves_k(const int32_t* __restrict__ leaf_of, const int32_t* __restrict__ nbeg,
                               const int32_t* __restrict__ nend, const int32_t* __restrict__ order,
+                              const NodeRec* __restrict__ r0, const NodeRec* __restrict__ r1,
                               const int32_t* __restrict__ vs0, const int32_t* __restrict__ vs1,
                               const double* __restrict__ H, int64_t N, int64_t n,
                               const double* __restrict__ dpos64, float* __restrict__ dpos) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
   const int32_t x = leaf_of[j];
-  // the neuron's position in sorted order, to read its per-type counts
-  int32_t p = nbeg[x];
-  while (p < nend[x] && order[p] != (int32_t)j) ++p;
+  // in a bucket, the neuron's position in sorted order, to read its per-type counts
+  const bool bucket = (r0[x].meta & kBucketBit) != 0;
+  int32_t p = 0;
+  if (bucket) {
+    p = nbeg[x];
+    while (p < nend[x] && order[p] != (int32_t)j) ++p;
+  }
   double a[3] = {dpos64[3 * j], dpos64[3 * j + 1], dpos64[3 * j + 2]};
   for (int t = 0; t < 2; ++t) {
-    const int32_t v = t ? vs1[p] : vs0[p];
+    const int32_t v = bucket ? (t ? vs1[p] : vs0[p]) : (t ? r1[x].v : r0[x].v);
     if (v <= 0) continue;
     const double* Ht = H + (int64_t)t * N * 3 + 3 * (int64_t)x;
     for (int k = 0; k < 3; ++k) a[k] += (double)v * Ht[k];

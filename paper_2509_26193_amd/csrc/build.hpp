@@ -114,20 +114,46 @@ __device__ __forceinline__ uint64_t prefix_of(uint64_t key, int k) {
   return k == 0 ? 0ull : key >> (3 * (kMaxDepth - k));
 }
 
-__global__ void __launch_bounds__(kBuildBlock) nodes_k(const uint64_t* __restrict__ keys,
-                                                      const int32_t* __restrict__ order, int64_t n,
-                                                      const int32_t* __restrict__ base,
-                                                      int32_t* skip, uint8_t* depth, int32_t* nbeg,
-                                                      int32_t* nend, int32_t* leaf_of,
-                                                      int32_t* leaf_at) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The nodes that start at sorted neuron m, one thread per m: topology, search records
+// (an inner node's meta word holds its subtree end and depth, a leaf's its neuron, a
+// bucket leaf's its own index; counts start at 0; a leaf's position stays as it is) and the
+// record after the last. The block's keys and the next ones lie in LDS, where most
+// cells end (a cell's end is galloped for, then bisected). Bound by its gathers and scatters
+// by id and by the records written (64 B per node): 8M neurons 0.80 ms, where one kernel for
+// the topology (every probe a dependent load) and one for the records took 0.70 ms and left
+// the positions' gather to every refresh.
+constexpr int kKeyWindow = 4 * kBuildBlock;
+
+__global__ void __launch_bounds__(kBuildBlock) nodes_k(
+    const uint64_t* __restrict__ keys, const int32_t* __restrict__ order,
+    const double* __restrict__ pos, int64_t n, const int32_t* __restrict__ base, int32_t* skip,
+    uint8_t* depth, int32_t* nbeg, int32_t* nend, int32_t* leaf_of, int32_t* leaf_at, NodeRec* r0,
+    NodeRec* r1) {
+  __shared__ uint64_t win[kKeyWindow];
+  const int64_t m0 = (int64_t)blockIdx.x * kBuildBlock;
+#pragma unroll
+  for (int q = 0; q < kKeyWindow / kBuildBlock; ++q) {
+    const int64_t i = m0 + q * kBuildBlock + threadIdx.x;
+    win[q * kBuildBlock + threadIdx.x] = i < n ? keys[i] : 0ull;
+  }
+  __syncthreads();
+  const int64_t m = m0 + threadIdx.x;
   if (m >= n) return;
-  const int cl = m == 0 ? -1 : common_digits(keys[m - 1], keys[m]);
-  const int cr = m == n - 1 ? -1 : common_digits(keys[m], keys[m + 1]);
+  auto key = [&](int64_t i) -> uint64_t { return i < m0 + kKeyWindow ? win[i - m0] : keys[i]; };
+  const uint64_t km = win[threadIdx.x];
+  const int cl = m == 0 ? -1 : common_digits(threadIdx.x ? win[threadIdx.x - 1] : keys[m - 1], km);
+  const int cr = m == n - 1 ? -1 : common_digits(km, key(m + 1));
   const int klo = cl + 1;
   const int khi = min(kMaxDepth, max(cl, cr) + 1);
+  NodeRec r;
+  r.v = 0;
+  if (m == n - 1) {                      // the record after the last node
+    r.x = r.y = r.z = 0.0;
+    r.meta = 0;
+    r0[base[n]] = r;
+    r1[base[n]] = r;
+  }
   if (khi < klo) return;
-  const uint64_t km = keys[m];
   int64_t end = m + 1;              // ranges grow as the depth decreases
   for (int k = khi; k >= klo; --k) {
     int64_t e;
@@ -135,147 +161,124 @@ __global__ void __launch_bounds__(kBuildBlock) nodes_k(const uint64_t* __restric
       e = n;
     } else {
       const uint64_t P = prefix_of(km, k);
-      if (end >= n || prefix_of(keys[end], k) != P) {
+      if (end >= n || prefix_of(key(end), k) != P) {
         e = end;
       } else {                     // gallop then bisect for the first key outside the cell
         int64_t lo = end, step = 1;
-        while (lo + step < n && prefix_of(keys[lo + step], k) == P) {
+        while (lo + step < n && prefix_of(key(lo + step), k) == P) {
           lo += step;
           step <<= 1;
         }
         int64_t hi = lo + step < n ? lo + step : n;
         while (hi - lo > 1) {
           const int64_t mid = lo + (hi - lo) / 2;
-          if (prefix_of(keys[mid], k) == P) lo = mid; else hi = mid;
+          if (prefix_of(key(mid), k) == P) lo = mid; else hi = mid;
         }
         e = hi;
       }
     }
     end = e;
-    const int64_t idx = (int64_t)base[m] + (k - klo);
-    skip[idx] = base[e];
+    const int32_t idx = base[m] + (k - klo);
+    const int32_t sk = base[e];
+    skip[idx] = sk;
     depth[idx] = (uint8_t)k;
     nbeg[idx] = (int32_t)m;
     nend[idx] = (int32_t)e;
-    const bool leaf = (e - m == 1) || k == kMaxDepth;
-    if (leaf)
+    r.x = r.y = r.z = 0.0;
+    if (e - m == 1) {
+      const int32_t id = order[m];
+      leaf_of[id] = idx;
+      leaf_at[m] = idx;
+      r.x = pos[3 * (int64_t)id];
+      r.y = pos[3 * (int64_t)id + 1];
+      r.z = pos[3 * (int64_t)id + 2];
+      r.meta = kLeafBit | (uint32_t)id;
+    } else if (k == kMaxDepth) {
       for (int64_t p = m; p < e; ++p) {
-        leaf_of[order[p]] = (int32_t)idx;
-        leaf_at[p] = (int32_t)idx;
+        leaf_of[order[p]] = idx;
+        leaf_at[p] = idx;
       }
+      r.meta = kLeafBit | kBucketBit | (uint32_t)idx;
+    } else {
+      r.meta = ((uint32_t)sk & kSkipMask) | ((uint32_t)k << kSkipBits);
+    }
+    r0[idx] = r;
+    r1[idx] = r;
   }
 }
 
-// Lanes of the wave holding the same depth as this lane (5-bit values; inactive
-// lanes and lanes with d < 0 are excluded).
-__device__ __forceinline__ uint64_t same_depth_lanes(int d) {
-  uint64_t peers = __ballot(d >= 0);
-#pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    const bool bit = (d >> b) & 1;
-    const uint64_t m = __ballot(bit);
-    peers &= bit ? m : ~m;
-  }
-  return peers;
-}
+// The passes over the tree go by chunks of 2^log sorted neurons. The inner nodes whose
+// neurons all lie in a chunk are listed by depth, deepest first: one block takes them
+// bottom-up (or top-down) with barriers between the depths. A node that starts in the chunk
+// and ends beyond it contains the neuron at the chunk's end, so there is at most one per
+// depth (cross); those that end within the same run of kSuper chunks are taken by a block
+// per run, a chunk per thread and depth by depth, the others by one block for all runs
+// (cross2). A pass over the tree is thus one launch for up to 4 096 neurons, two up to
+// 131 072 and three beyond, instead of one per depth; small trees are bound by that.
+constexpr int kChunkLog = 10;
+constexpr int kChunkLogOne = 12;           // trees of up to 2^12 neurons are one chunk
+constexpr int kSuper = 128;
+constexpr int kDepths = kMaxDepth + 1;
 
-// Nodes per block of the per-depth passes: enough that the per-block global atomics
-// (one per depth) do not queue up on the few hot depth counters.
-constexpr int kLevelItems = 16;
+inline int chunk_log(int64_t n) { return n <= ((int64_t)1 << kChunkLogOne) ? kChunkLogOne : kChunkLog; }
 
-// Inner nodes per depth (leaves are refreshed in sorted order, not by depth): one LDS
-// atomic per distinct depth and wave, one global atomic per depth and block of
-// kBuildBlock * kLevelItems nodes. A leaf is a node whose subtree ends right after it.
-__device__ __forceinline__ int inner_depth(const uint8_t* depth, const int32_t* skip, int64_t x,
-                                           int64_t N) {
-  return (x < N && skip[x] != (int32_t)(x + 1)) ? (int)depth[x] : -1;
-}
-
-__global__ void __launch_bounds__(kBuildBlock) level_count_k(const uint8_t* __restrict__ depth,
-                                                            const int32_t* __restrict__ skip,
-                                                            int64_t N, int32_t* level_cnt) {
-  __shared__ int32_t c[kMaxDepth + 1];
-  if (threadIdx.x <= kMaxDepth) c[threadIdx.x] = 0;
-  __syncthreads();
-  const int lane = (int)(threadIdx.x & (kWave - 1));
-  const int64_t base = (int64_t)blockIdx.x * kBuildBlock * kLevelItems + threadIdx.x;
-  for (int k = 0; k < kLevelItems; ++k) {
-    const int64_t x = base + (int64_t)k * kBuildBlock;
-    const int d = inner_depth(depth, skip, x, N);
-    const uint64_t peers = same_depth_lanes(d);
-    if (d >= 0 && lane == __ffsll((unsigned long long)peers) - 1) atomicAdd(&c[d], __popcll(peers));
+__global__ void __launch_bounds__(kBuildBlock) chunks_k(
+    const uint8_t* __restrict__ depth, const int32_t* __restrict__ skip,
+    const int32_t* __restrict__ base, int64_t n, int log, int nch, int nsup, int32_t* chunk_x,
+    int32_t* chunk_off, int32_t* chunk_nodes, int32_t* cross, int32_t* cross2, int32_t* cross_kids,
+    int32_t* cross2_kids) {
+  __shared__ int32_t cnt[kDepths], at[kDepths], cr[kDepths], cr2[kDepths];
+  const int c = (int)blockIdx.x, t = (int)threadIdx.x;
+  const int64_t p0 = (int64_t)c << log, p1 = p0 + ((int64_t)1 << log);
+  const int32_t x0 = base[p0], x1 = base[p1 < n ? p1 : n];
+  const int64_t p2 = (int64_t)(c / kSuper + 1) * kSuper << log;
+  const int32_t x2 = base[p2 < n ? p2 : n];        // the end of the chunk's run of chunks
+  if (t < kDepths) {
+    cnt[t] = 0;
+    cr[t] = cr2[t] = -1;
   }
   __syncthreads();
-  if (threadIdx.x <= kMaxDepth && c[threadIdx.x]) atomicAdd(&level_cnt[threadIdx.x], c[threadIdx.x]);
-}
-
-// Group inner node ids by depth (order within a depth is arbitrary: the refresh of one
-// depth treats its nodes independently). Same blocking as level_count_k.
-__global__ void __launch_bounds__(kBuildBlock) level_scatter_k(const uint8_t* __restrict__ depth,
-                                                              const int32_t* __restrict__ skip,
-                                                              int64_t N, int32_t* cursor,
-                                                              int32_t* level_nodes) {
-  __shared__ int32_t c[kMaxDepth + 1];
-  __shared__ int32_t base_d[kMaxDepth + 1];
-  if (threadIdx.x <= kMaxDepth) c[threadIdx.x] = 0;
-  __syncthreads();
-  const int lane = (int)(threadIdx.x & (kWave - 1));
-  const int64_t base = (int64_t)blockIdx.x * kBuildBlock * kLevelItems + threadIdx.x;
-  int d[kLevelItems];
-  int r[kLevelItems];
-#pragma unroll
-  for (int k = 0; k < kLevelItems; ++k) {
-    const int64_t x = base + (int64_t)k * kBuildBlock;
-    d[k] = inner_depth(depth, skip, x, N);
-    const uint64_t peers = same_depth_lanes(d[k]);
-    const int leader = __ffsll((unsigned long long)peers) - 1;
-    int r0 = 0;
-    if (d[k] >= 0 && lane == leader) r0 = atomicAdd(&c[d[k]], __popcll(peers));
-    r[k] = __shfl(r0, leader < 0 ? 0 : leader, kWave) + __popcll(peers & ((1ull << lane) - 1ull));
+  for (int32_t x = x0 + t; x < x1; x += kBuildBlock) {
+    const int32_t sk = skip[x];
+    if (sk == x + 1) continue;                     // a leaf
+    const int d = depth[x];
+    if (sk <= x1) atomicAdd(&cnt[d], 1);
+    else if (sk <= x2) cr[d] = x;
+    else cr2[d] = x;
   }
   __syncthreads();
-  if (threadIdx.x <= kMaxDepth && c[threadIdx.x])
-    base_d[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], c[threadIdx.x]);
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kLevelItems; ++k)
-    if (d[k] >= 0) level_nodes[base_d[d[k]] + r[k]] = (int32_t)(base + (int64_t)k * kBuildBlock);
-}
-
-// Start of each depth's run in level_nodes: the exclusive prefix of the per-depth
-// counts (one thread; kMaxDepth + 1 values).
-__global__ void level_cursor_k(const int32_t* __restrict__ counts, int32_t* __restrict__ cursor) {
-  int32_t acc = 0;
-  for (int k = 0; k <= kMaxDepth; ++k) {
-    cursor[k] = acc;
-    acc += counts[k];
+  if (t < kDepths) {
+    int32_t before = 0;                            // deepest first
+    for (int d = kMaxDepth; d > t; --d) before += cnt[d];
+    at[t] = before;
+    chunk_off[(int64_t)c * (kDepths + 1) + (kMaxDepth - t)] = before;
+    if (t == 0) chunk_off[(int64_t)c * (kDepths + 1) + kDepths] = before + cnt[0];
+    cross[(int64_t)t * nch + c] = cr[t];
+    const int32_t two = cr2[t];
+    if (two >= 0) cross2[(int64_t)t * nsup + c / kSuper] = two;
+    // the children of either
+    const int32_t x = two >= 0 ? two : cr[t];
+    if (x >= 0) {
+      int32_t* kids = two >= 0 ? cross2_kids + 8 * ((int64_t)t * nsup + c / kSuper)
+                               : cross_kids + 8 * ((int64_t)t * nch + c);
+      const int32_t end = skip[x];
+      int32_t y = x + 1;
+      for (int k = 0; k < 8; ++k) {
+        kids[k] = y < end ? y : -1;
+        y = y < end ? skip[y] : y;
+      }
+    }
   }
-}
-
-// Per-type records start with count 0 and the node's meta word: an inner node keeps
-// its subtree end and depth, a leaf its neuron id, a bucket leaf its own index.
-__global__ void __launch_bounds__(kBuildBlock) init_meta_k(const int32_t* __restrict__ skip,
-                                                          const uint8_t* __restrict__ depth,
-                                                          const int32_t* __restrict__ nbeg,
-                                                          const int32_t* __restrict__ nend,
-                                                          const int32_t* __restrict__ order,
-                                                          int64_t N, NodeRec* r0, NodeRec* r1) {
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= N) return;
-  const int32_t sk = skip[x];
-  uint32_t meta;
-  if (sk != x + 1)
-    meta = ((uint32_t)sk & kSkipMask) | ((uint32_t)depth[x] << kSkipBits);
-  else if (nend[x] - nbeg[x] == 1)
-    meta = kLeafBit | (uint32_t)order[nbeg[x]];
-  else
-    meta = kLeafBit | kBucketBit | (uint32_t)x;
-  NodeRec r;
-  r.x = r.y = r.z = 0.0;
-  r.v = 0;
-  r.meta = meta;
-  r0[x] = r;
-  r1[x] = r;
+  if (t == 0) {
+    chunk_x[c] = x0;
+    if (c == nch - 1) chunk_x[nch] = x1;
+  }
+  __syncthreads();
+  for (int32_t x = x0 + t; x < x1; x += kBuildBlock) {
+    const int32_t sk = skip[x];
+    if (sk == x + 1 || sk > x1) continue;
+    chunk_nodes[x0 + atomicAdd(&at[(int)depth[x]], 1)] = x;
+  }
 }
 
 // Boxes of runs of consecutive sorted neurons, in grid cells: runs of 2^run_log(n)

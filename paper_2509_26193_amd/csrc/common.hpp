@@ -63,10 +63,19 @@ struct msp_octree_s {
   uint8_t* depth;        // [N]
   int32_t* nbeg;         // [N] range in `order`
   int32_t* nend;         // [N]
-  int32_t* level_nodes;  // [N] inner node ids grouped by depth
-  int64_t level_off[msp::kMaxDepth + 2];   // runs of level_nodes (inner nodes only)
+  // the inner nodes by chunks of sorted neurons, for the passes over the tree (see chunks_k)
+  int32_t chunk_log;     // 2^chunk_log neurons per chunk
+  int32_t nch, nsup;     // chunks, runs of kSuper chunks
+  int32_t* chunk_x;      // [nch + 1] first node that starts in the chunk
+  int32_t* chunk_off;    // [nch][kMaxDepth + 2] lists of the nodes inside, deepest first
+  int32_t* chunk_nodes;  // [N] those lists, a chunk's from its first node on
+  int32_t* cross;        // [kMaxDepth + 1][nch] node that leaves the chunk at its end, or -1
+  int32_t* cross2;       // [kMaxDepth + 1][nsup] and its run of chunks
+  int32_t* cross_kids;   // [kMaxDepth + 1][nch][8] children of a crossing node (-1: none)
+  int32_t* cross2_kids;  // [kMaxDepth + 1][nsup][8]
   msp::NodeRec* rec[2];  // [N + 1] per type (index N: zero sentinel, never visited)
   int32_t* vs[2];        // [n] per type: counts in sorted order (bucket members)
+  int2* both;            // [n] by id: both types' counts (large trees; null: none)
   float* box[2];         // boxes of runs of sorted neurons (see boxes_k): 6 arrays each
   int32_t* err;          // [1] sticky device error flags
   bool refreshed;

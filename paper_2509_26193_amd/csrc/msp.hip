@@ -33,6 +33,7 @@ void carve_neurons(msp_octree_s* t, char* base, size_t* bytes) {
   t->leaf_at = c.take<int32_t>(n);
   t->vs[0] = c.take<int32_t>(n);
   t->vs[1] = c.take<int32_t>(n);
+  t->both = n > kPairMin ? c.take<int2>(n) : nullptr;
   const int log = run_log(n);
   t->box[0] = c.take<float>(6 * runs_of(n, log));
   t->box[1] = c.take<float>(6 * runs_of(n, log + 6));
@@ -50,7 +51,16 @@ void carve_nodes(msp_octree_s* t, char* base, size_t* bytes) {
   t->skip = c.take<int32_t>(N);
   t->nbeg = c.take<int32_t>(N);
   t->nend = c.take<int32_t>(N);
-  t->level_nodes = c.take<int32_t>(N);
+  t->chunk_log = chunk_log(t->n);
+  t->nch = (int32_t)runs_of(t->n, t->chunk_log);
+  t->nsup = (t->nch + kSuper - 1) / kSuper;
+  t->chunk_x = c.take<int32_t>(t->nch + 1);
+  t->chunk_off = c.take<int32_t>((int64_t)t->nch * (kDepths + 1));
+  t->chunk_nodes = c.take<int32_t>(N);
+  t->cross = c.take<int32_t>((int64_t)t->nch * kDepths);
+  t->cross2 = c.take<int32_t>((int64_t)t->nsup * kDepths);
+  t->cross_kids = c.take<int32_t>((int64_t)t->nch * kDepths * 8);
+  t->cross2_kids = c.take<int32_t>((int64_t)t->nsup * kDepths * 8);
   t->depth = c.take<uint8_t>(N);
   *bytes = c.off;
 }
@@ -263,21 +273,24 @@ hipError_t noalloc_scratch(int device, void** out) {
 }
 
 // The octree's per-type vacancy counts and centroids from the vacant dendritic
-// elements: leaves first, then the inner nodes level by level, deepest first.
+// elements: by chunks, then the nodes that cross them, bottom-up.
 hipError_t enqueue_refresh(msp_octree_s* t, const int32_t* vac_exc, const int32_t* vac_inh,
                            hipStream_t s) {
-  refresh_leaves_k<<<grid_for(t->n, kRefreshBlock), kRefreshBlock, 0, s>>>(
-      t->n, t->rec[0], t->rec[1], t->leaf_at, t->nbeg, t->nend, t->order, t->pos, vac_exc,
-      vac_inh, t->vs[0], t->vs[1], t->err);
-  hipError_t e = hipGetLastError();
-  for (int k = kMaxDepth; k >= 0 && e == hipSuccess; --k) {
-    const int64_t cnt = t->level_off[k + 1] - t->level_off[k];
-    if (cnt == 0) continue;
-    refresh_level_k<<<grid_for(cnt, kRefreshBlock), kRefreshBlock, 0, s>>>(
-        t->level_nodes + t->level_off[k], cnt, t->rec[0], t->rec[1], t->err);
-    e = hipGetLastError();
-  }
-  return e;
+  const Chunks C = chunks_of(t);
+  if (t->both)
+    pair_counts_k<<<grid_for(t->n, kRefreshBlock), kRefreshBlock, 0, s>>>(vac_exc, vac_inh, t->n,
+                                                                          t->both);
+  (t->both ? refresh_chunk_k<true> : refresh_chunk_k<false>)
+      <<<(unsigned)C.nch, C.nch == 1 ? 1024 : 512, 0, s>>>(
+          t->n, C, t->rec[0], t->rec[1], t->leaf_at, t->order, t->pos, vac_exc, vac_inh, t->both,
+          t->vs[0], t->vs[1], t->err);
+  if (C.nch > 1)
+    refresh_cross_k<<<(unsigned)C.nsup, kSuper, 0, s>>>(C.cross, C.cross_kids, C.skip, C.nch,
+                                                        t->rec[0], t->rec[1], t->err);
+  if (C.nsup > 1)
+    refresh_cross_k<<<1, kCross2Block, 0, s>>>(C.cross2, C.cross2_kids, C.skip, C.nsup, t->rec[0],
+                                               t->rec[1], t->err);
+  return hipGetLastError();
 }
 
 // The search's descriptor and neuron bases written by a kernel (arguments by value):
@@ -376,20 +389,17 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
     const size_t b_k1 = align_up(sizeof(uint64_t) * n), b_v1 = align_up(sizeof(int32_t) * n),
                  b_ws = align_up(radix_sort_ws_bytes(n)), b_cnt = align_up(sizeof(int32_t) * n),
                  b_base = align_up(sizeof(int32_t) * (n + 1)),
-                 b_lvl = align_up(sizeof(int32_t) * 2 * (kMaxDepth + 1)),
                  b_out = align_up(2 * sizeof(int32_t)), b_scan = align_up(scan_tmp_bytes<int32_t>(n));
     Temp tmp(s);
-    TRY(tmp.alloc(b_k1 + b_v1 + b_ws + b_cnt + b_base + b_lvl + b_out + b_scan));
+    TRY(tmp.alloc(b_k1 + b_v1 + b_ws + b_cnt + b_base + b_out + b_scan));
     char* tp = tmp.as<char>();
     uint64_t* k1 = reinterpret_cast<uint64_t*>(tp);
     int32_t* v1 = reinterpret_cast<int32_t*>(tp + b_k1);
     void* sort_ws = tp + b_k1 + b_v1;
     int32_t* cntp = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws);
     int32_t* basep = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt);
-    int32_t* lcnt = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt + b_base);
-    int32_t* outside = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt + b_base +
-                                                  b_lvl);
-    void* scan_ws = tp + b_k1 + b_v1 + b_ws + b_cnt + b_base + b_lvl + b_out;
+    int32_t* outside = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt + b_base);
+    void* scan_ws = tp + b_k1 + b_v1 + b_ws + b_cnt + b_base + b_out;
     TRY(hipMemsetAsync(outside, 0, 2 * sizeof(int32_t), s));
     keys_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(pos, n, box_min[0], box_min[1],
                                                             box_min[2], box_edge, t->pos, t->keys,
@@ -429,38 +439,22 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
     carve_nodes(t, nullptr, &bytes);
     TRY(pool_alloc(&t->slab_N, bytes, s));
     carve_nodes(t, static_cast<char*>(t->slab_N), &bytes);
-    TRY(hipMemsetAsync(t->rec[0] + N, 0, sizeof(NodeRec), s));
-    TRY(hipMemsetAsync(t->rec[1] + N, 0, sizeof(NodeRec), s));
-    TRY(hipMemsetAsync(lcnt, 0, sizeof(int32_t) * 2 * (kMaxDepth + 1), s));
-    nodes_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, t->order, n,
-                                                             basep, t->skip, t->depth,
-                                                             t->nbeg, t->nend, t->leaf_of,
-                                                             t->leaf_at);
+    nodes_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, t->order, t->pos, n, basep,
+                                                             t->skip, t->depth, t->nbeg, t->nend,
+                                                             t->leaf_of, t->leaf_at, t->rec[0],
+                                                             t->rec[1]);
     TRY(hipGetLastError());
     const int log = run_log(n);
     boxes_k<<<(unsigned)runs_of(n, log + 6), kBuildBlock, 0, s>>>(
         t->keys, n, log, runs_of(n, log), runs_of(n, log + 6), t->box[0], t->box[1]);
     TRY(hipGetLastError());
-    level_count_k<<<grid_for(N, kBuildBlock * kLevelItems), kBuildBlock, 0, s>>>(t->depth, t->skip,
-                                                                                N, lcnt);
-    TRY(hipGetLastError());
-    int32_t hc[kMaxDepth + 1];
-    TRY(hipMemcpyAsync(hc, lcnt, sizeof(hc), hipMemcpyDeviceToHost, s));
-    TRY(hipStreamSynchronize(s));
-    t->level_off[0] = 0;
-    for (int k = 0; k <= kMaxDepth; ++k) t->level_off[k + 1] = t->level_off[k] + hc[k];
-    if (t->level_off[kMaxDepth + 1] > N) {
-      release(t);
-      return MSP_ERR_HIP;
-    }
-    int32_t* cursor = lcnt + (kMaxDepth + 1);
-    level_cursor_k<<<1, 1, 0, s>>>(lcnt, cursor);
-    level_scatter_k<<<grid_for(N, kBuildBlock * kLevelItems), kBuildBlock, 0, s>>>(
-        t->depth, t->skip, N, cursor, t->level_nodes);
-    TRY(hipGetLastError());
-    init_meta_k<<<grid_for(N, kBuildBlock), kBuildBlock, 0, s>>>(t->skip, t->depth, t->nbeg,
-                                                                 t->nend, t->order, N, t->rec[0],
-                                                                 t->rec[1]);
+    if (t->nsup > 1)
+      fill_i32_k<<<grid_for((int64_t)t->nsup * kDepths, 256), 256, 0, s>>>(
+          t->cross2, (int64_t)t->nsup * kDepths, -1);
+    chunks_k<<<(unsigned)t->nch, kBuildBlock, 0, s>>>(t->depth, t->skip, basep, n, t->chunk_log,
+                                                      t->nch, t->nsup, t->chunk_x, t->chunk_off,
+                                                      t->chunk_nodes, t->cross, t->cross2,
+                                                      t->cross_kids, t->cross2_kids);
     TRY(hipGetLastError());
   }
 #undef TRY
@@ -1166,14 +1160,18 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   fill_f64_k<<<1, 64, 0, s>>>(dsigma, 1, 0.0);
   attract_bwd_k<<<grid_for(max_units_for(n, 1) * kWave, 256), 256, 0, s>>>(S.B, O);
   grad_sum_k<<<grid_for(ng, 256), 256, 0, s>>>(O.G, ng);
-  for (int k = 0; k <= kMaxDepth; ++k) {
-    const int64_t cnt = t->level_off[k + 1] - t->level_off[k];
-    if (cnt == 0) continue;
-    push_level_k<<<grid_for(cnt, 256), 256, 0, s>>>(t->level_nodes + t->level_off[k], cnt,
-                                                     t->rec[0], t->rec[1], O.G, H, N);
-  }
+  const Chunks C = chunks_of(t);
+  if (C.nsup > 1)
+    push_cross_k<<<1, kCross2Block, 0, s>>>(C.cross2, C.cross2_kids, C.nsup, t->rec[0], t->rec[1], O.G, H,
+                                      N);
+  if (C.nch > 1)
+    push_cross_k<<<(unsigned)C.nsup, kSuper, 0, s>>>(C.cross, C.cross_kids, C.nch, t->rec[0],
+                                                     t->rec[1], O.G, H, N);
+  push_chunk_k<<<(unsigned)C.nch, 512, 0, s>>>(C, t->rec[0], t->rec[1], O.G, H,
+                                                                   N);
   push_leaves_k<<<grid_for(n, 256), 256, 0, s>>>(t->leaf_of, t->nbeg, t->nend, t->order,
-                                                  t->vs[0], t->vs[1], H, N, n, O.dpos, dpos);
+                                                 t->rec[0], t->rec[1], t->vs[0], t->vs[1], H, N, n,
+                                                 O.dpos, dpos);
   MSP_HIP_TRY(hipGetLastError());
   return MSP_OK;
 }

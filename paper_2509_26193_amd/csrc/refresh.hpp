@@ -1,12 +1,12 @@
-// Vacancy refresh (Sec. III-B, "Division of work"): the leaves in one pass, then the
-// inner nodes bottom-up, one launch per depth.
-// A leaf takes its neuron's count and position; an inner node the sum of its
-// children's counts and the count-weighted mean of their centroids, accumulated in
-// float64 left to right in octant order with one rounding per operation (the
+// Vacancy refresh (Sec. III-B, "Division of work"): the leaves and the inner nodes bottom-up,
+// by chunks of the tree (see chunks_k).
+// A leaf takes its neuron's count (its position stays in its record); an inner node the
+// sum of its children's counts and the count-weighted mean of their centroids, accumulated
+// in float64 left to right in octant order with one rounding per operation (the
 // library is compiled without FP contraction, so no product is fused into a sum).
 #pragma once
 
-#include "common.hpp"
+#include "build.hpp"
 
 namespace msp {
 
@@ -38,52 +38,28 @@ struct Acc3 {
   }
 };
 
-// Leaves, one thread per neuron in sorted order (leaf indices, records and member
-// counts are read and written in order; positions and the caller's vacancy arrays
-// are gathered by id). A bucket leaf is done by its first member's thread, its
-// members in sorted order (id order within the finest cell).
-__global__ void __launch_bounds__(kRefreshBlock) refresh_leaves_k(
-    int64_t n, NodeRec* __restrict__ r0, NodeRec* __restrict__ r1,
-    const int32_t* __restrict__ leaf_at, const int32_t* __restrict__ nbeg,
-    const int32_t* __restrict__ nend, const int32_t* __restrict__ order,
-    const double* __restrict__ pos, const int32_t* __restrict__ vexc,
-    const int32_t* __restrict__ vinh, int32_t* __restrict__ vs0, int32_t* __restrict__ vs1,
-    int32_t* err) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int32_t x = leaf_at[p];
-  const uint32_t meta = r0[x].meta;
-  if (!(meta & kBucketBit)) {
-    const int32_t id = order[p];
-    const int32_t a = vexc[id], b = vinh[id];
-    if (a < 0 || b < 0) atomicOr(err, kErrNegative);
-    NodeRec e, f;
-    e.x = f.x = pos[3 * (int64_t)id];
-    e.y = f.y = pos[3 * (int64_t)id + 1];
-    e.z = f.z = pos[3 * (int64_t)id + 2];
-    e.v = a < 0 ? 0 : a;
-    f.v = b < 0 ? 0 : b;
-    e.meta = f.meta = meta;
-    r0[x] = e;
-    r1[x] = f;
-    vs0[p] = e.v;
-    vs1[p] = f.v;
-    return;
-  }
-  if (p != nbeg[x]) return;
+// The inner node x with meta word `meta` from its children (ascending, -1: none), after every
+// deeper node below it. The children's records are loaded four at a time, not one after
+// the other as their subtree ends lead from one to the next.
+__device__ __forceinline__ void refresh_node(int32_t x, uint32_t meta, const int32_t (&kids)[8],
+                                             NodeRec* r0, NodeRec* r1, int32_t* err) {
   Acc3 A, B;
-  for (int32_t q = nbeg[x]; q < nend[x]; ++q) {
-    const int32_t id = order[q];
-    int32_t a = vexc[id], b = vinh[id];
-    if (a < 0 || b < 0) atomicOr(err, kErrNegative);
-    a = a < 0 ? 0 : a;
-    b = b < 0 ? 0 : b;
-    const double px = pos[3 * (int64_t)id], py = pos[3 * (int64_t)id + 1],
-                 pz = pos[3 * (int64_t)id + 2];
-    A.add(a, px, py, pz);
-    B.add(b, px, py, pz);
-    vs0[q] = a;
-    vs1[q] = b;
+#pragma unroll
+  for (int k = 0; k < 8; k += 4) {
+    if (kids[k] < 0) break;
+    NodeRec a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t c = kids[k + q] < 0 ? kids[k] : kids[k + q];
+      a[q] = r0[c];
+      b[q] = r1[c];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (kids[k + q] < 0) break;
+      A.add(a[q].v, a[q].x, a[q].y, a[q].z);
+      B.add(b[q].v, b[q].x, b[q].y, b[q].z);
+    }
   }
   NodeRec e, f;
   e.meta = f.meta = meta;
@@ -93,31 +69,159 @@ __global__ void __launch_bounds__(kRefreshBlock) refresh_leaves_k(
   r1[x] = f;
 }
 
-// Inner nodes of one depth (after every deeper depth and the leaves).
-__global__ void __launch_bounds__(kRefreshBlock) refresh_level_k(
-    const int32_t* __restrict__ nodes, int64_t cnt, NodeRec* __restrict__ r0,
-    NodeRec* __restrict__ r1, int32_t* err) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= cnt) return;
-  const int32_t x = nodes[q];
-  const uint32_t meta = r0[x].meta;
-  // children are x+1, then each child's subtree end, up to our own end
-  const int32_t end = (int32_t)(meta & kSkipMask);
-  Acc3 A, B;
-  int32_t c = x + 1;
-  while (c < end) {
-    const NodeRec ca = r0[c];
-    const NodeRec cb = r1[c];
-    A.add(ca.v, ca.x, ca.y, ca.z);
-    B.add(cb.v, cb.x, cb.y, cb.z);
-    c = (ca.meta & kLeafBit) ? c + 1 : (int32_t)(ca.meta & kSkipMask);
+// The subtree ends of a chunk's nodes in LDS (those past kSkipRoom stay in global memory),
+// and the children of its inner nodes found through them.
+constexpr int kSkipRoom = 8192;
+
+struct ChunkSkips {
+  const int32_t* lds;
+  const int32_t* skip;
+  int32_t x0;
+  __device__ __forceinline__ int32_t operator()(int32_t x) const {
+    return x - x0 < kSkipRoom ? lds[x - x0] : skip[x];
   }
-  NodeRec e, f;
-  e.meta = f.meta = meta;
-  A.store(e, err);
-  B.store(f, err);
-  r0[x] = e;
-  r1[x] = f;
+  __device__ __forceinline__ void kids(int32_t x, int32_t end, int32_t (&k)[8]) const {
+    int32_t c = x + 1;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const bool in = c < end;
+      k[q] = in ? c : -1;
+      if (in) c = (*this)(c);
+    }
+  }
+};
+
+// The octree's chunks, as the kernels read them.
+struct Chunks {
+  int32_t log, nch, nsup;
+  const int32_t* x;
+  const int32_t* off;
+  const int32_t* nodes;
+  const int32_t* cross;
+  const int32_t* cross2;
+  const int32_t* cross_kids;
+  const int32_t* cross2_kids;
+  const int32_t* skip;
+};
+
+inline Chunks chunks_of(const msp_octree_s* t) {
+  return Chunks{t->chunk_log, t->nch, t->nsup, t->chunk_x, t->chunk_off, t->chunk_nodes,
+                t->cross, t->cross2, t->cross_kids, t->cross2_kids, t->skip};
+}
+
+// The node of depth d that crosses the end of chunk (or run) c, with its children.
+struct CrossNode {
+  int32_t x, kids[8];
+  __device__ __forceinline__ CrossNode(const int32_t* cross, const int32_t* kids_of, int count,
+                                       int c, int d) {
+    const int64_t at = (int64_t)d * count + (c < count ? c : 0);
+    x = c < count ? cross[at] : -1;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) kids[k] = kids_of[8 * at + k];
+  }
+};
+
+// Both types' counts by id side by side, for the refresh of a tree of more than kPairMin neurons:
+// its gathers by id then fetch one line per neuron instead of two (8M neurons: 0.84 ms for the
+// chunks without, 0.81 with). Smaller trees' counts stay in the L2 caches.
+constexpr int64_t kPairMin = (int64_t)1 << 18;
+
+__global__ void pair_counts_k(const int32_t* __restrict__ vexc, const int32_t* __restrict__ vinh,
+                              int64_t n, int2* __restrict__ both) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) both[i] = make_int2(vexc[i], vinh[i]);
+}
+
+// One block per chunk: its leaves (the caller's vacancy arrays are gathered by id; a bucket
+// leaf is done by its first member's thread, its members in sorted order, which is id order
+// within the finest cell), then its inner nodes by depth, deepest first. Bound by the
+// gathers (a 128-byte line for 8 bytes per neuron) and the records read and written; small
+// trees by the chain of children (8 dependent reads per depth). The whole refresh, against a
+// kernel for the leaves and one per depth: 8M neurons 0.95 ms (1.39), 2M 0.31 (0.37), 4 096
+// 50 us in one launch (41 us in nine, and 22 us for the lists of the depths).
+template <bool PAIRS>
+__global__ void __launch_bounds__(1024) refresh_chunk_k(
+    int64_t n, Chunks C, NodeRec* r0, NodeRec* r1, const int32_t* __restrict__ leaf_at,
+    const int32_t* __restrict__ order, const double* __restrict__ pos,
+    const int32_t* __restrict__ vexc, const int32_t* __restrict__ vinh,
+    const int2* __restrict__ both, int32_t* __restrict__ vs0, int32_t* __restrict__ vs1,
+    int32_t* err) {
+  __shared__ int32_t skips[kSkipRoom];
+  const int c = (int)blockIdx.x;
+  const int32_t x0 = C.x[c], x1 = C.x[c + 1];
+  for (int32_t x = x0 + (int)threadIdx.x; x < x1 && x - x0 < kSkipRoom; x += blockDim.x)
+    skips[x - x0] = C.skip[x];
+  const ChunkSkips S{skips, C.skip, x0};
+  auto counts = [&](int32_t id) -> int2 {
+    const int2 v = PAIRS ? both[id] : make_int2(vexc[id], vinh[id]);
+    if (v.x < 0 || v.y < 0) atomicOr(err, kErrNegative);
+    return make_int2(v.x < 0 ? 0 : v.x, v.y < 0 ? 0 : v.y);
+  };
+  const int64_t p0 = (int64_t)c << C.log;
+  const int64_t p1 = p0 + ((int64_t)1 << C.log) < n ? p0 + ((int64_t)1 << C.log) : n;
+  for (int64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
+    const int32_t x = leaf_at[p];
+    const bool first = p == 0 || leaf_at[p - 1] != x;
+    if (first && (p + 1 >= n || leaf_at[p + 1] != x)) {
+      const int2 v = counts(order[p]);
+      r0[x].v = v.x;
+      r1[x].v = v.y;
+    } else if (first) {
+      Acc3 A, B;
+      for (int64_t q = p; q < n && leaf_at[q] == x; ++q) {
+        const int32_t id = order[q];
+        const int2 v = counts(id);
+        const double px = pos[3 * (int64_t)id], py = pos[3 * (int64_t)id + 1],
+                     pz = pos[3 * (int64_t)id + 2];
+        A.add(v.x, px, py, pz);
+        B.add(v.y, px, py, pz);
+        vs0[q] = v.x;
+        vs1[q] = v.y;
+      }
+      NodeRec e, f;
+      e.meta = f.meta = r0[x].meta;
+      A.store(e, err);
+      B.store(f, err);
+      r0[x] = e;
+      r1[x] = f;
+    }
+  }
+  const int32_t* off = C.off + (int64_t)c * (kDepths + 1);
+  const int32_t* nodes = C.nodes + x0;
+  int32_t lo = 0;
+  for (int k = 1; k <= kDepths; ++k) {             // depth kMaxDepth + 1 - k
+    const int32_t hi = off[k];
+    if (hi == lo) continue;                        // (uniform over the block)
+    __syncthreads();
+    for (int32_t q = lo + (int)threadIdx.x; q < hi; q += blockDim.x) {
+      const int32_t x = nodes[q], end = S(x);
+      int32_t kids[8];
+      S.kids(x, end, kids);
+      refresh_node(x, (uint32_t)end | ((uint32_t)(kMaxDepth + 1 - k) << kSkipBits), kids, r0, r1,
+                   err);
+    }
+    lo = hi;
+  }
+}
+
+// One block per run of kSuper chunks, a chunk per thread: the nodes that cross chunk ends
+// inside the run, by depth; with cross2 (one block, a run per thread) those that cross the
+// ends of runs. Bound by the chain over the depths (a barrier and the children's records
+// each), so the next depth's node and children are loaded ahead of the barrier.
+constexpr int kCross2Block = 512;          // runs of a tree of kMaxNodes neurons
+
+__global__ void __launch_bounds__(kCross2Block) refresh_cross_k(
+    const int32_t* __restrict__ cross, const int32_t* __restrict__ kids_of,
+    const int32_t* __restrict__ skip, int count, NodeRec* r0, NodeRec* r1, int32_t* err) {
+  const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  CrossNode next(cross, kids_of, count, c, kMaxDepth);
+  for (int d = kMaxDepth; d >= 0; --d) {
+    const CrossNode at = next;
+    if (d > 0) next = CrossNode(cross, kids_of, count, c, d - 1);
+    if (!__syncthreads_or(at.x >= 0)) continue;
+    if (at.x < 0) continue;
+    refresh_node(at.x, (uint32_t)skip[at.x] | ((uint32_t)d << kSkipBits), at.kids, r0, r1, err);
+  }
 }
 
 }  // namespace msp
