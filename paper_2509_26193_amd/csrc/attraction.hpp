@@ -34,9 +34,8 @@ struct AttractArgs {
   double* dpos;                 // [n][3] float64 accumulator
   double* dsigma;               // scalar accumulator
   double two_over_s2;           // 2 / sigma^2
-  double two_over_s3;           // 2 / sigma^3
+  double one_over_s;            // 1 / sigma
   int64_t N;
-  const int32_t* unit_count;    // device scalar: the units (runs of parts of tiles)
 };
 
 // The die (XCC) this wave runs on: bits 3:0 of hardware register XCC_ID (20). It only
@@ -74,53 +73,63 @@ __device__ __forceinline__ double wave_sum(double v) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// v from lane (lane ^ m), through the LDS crossbar (both 32-bit halves).
-__device__ __forceinline__ double shfl_xor_f64(double v, int lane, int m) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const int addr = (lane ^ m) << 2;
-  const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)b);
-  const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)(b >> 32));
-  return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
+// The wave's contributions to nodes, summed over its lanes kSumNodes nodes at a time: every
+// lane puts the three components of its entry into LDS, and when the rows are full four lanes
+// per sum add up 16 values each and one atomic instruction sends all sums. The walk is bound by
+// vector instructions, and this takes about 9 per entry, where exchanges between the lanes
+// down to one sum per entry took 30 and waited for each other (262 144 neurons: 2.64 -> 1.88 ms).
+// The rows' stride and the lanes' share of the columns keep the reads (16 bytes a lane, 16
+// lanes at a time) on different banks.
+constexpr int kBwdBlock = 128;
+constexpr int kSumNodes = 4;
+constexpr int kSumStride = 72;
+constexpr int kSumRoom = 3 * kSumNodes * kSumStride;
 
-// The wave sums of three values at once (every lane active): the lanes split the
-// values between them as they add, so each exchange moves one or two values instead of
-// three. After the pair and quad steps lane l holds a partial sum of value
-// {0, 2, 1, 3}[l % 4] (value 3 is zero), then the four lanes of a row with that value
-// and the four rows are added. Returns lane l's full sum of that value; `comp` is set
-// to its index (3: none).
-__device__ __forceinline__ double wave_sum3(double fx, double fy, double fz, int lane, int& comp) {
-  const bool odd = lane & 1;
-  // pairs: even lanes keep (x, y) and send (z, 0); odd lanes the other way round
-  const double s0 = odd ? fx : fz, s1 = odd ? fy : 0.0;
-  const double k0 = odd ? fz : fx, k1 = odd ? 0.0 : fy;
-  const double p = k0 + dpp_f64<0xB1, 0xF>(s0);      // quad_perm [1,0,3,2]
-  const double q = k1 + dpp_f64<0xB1, 0xF>(s1);
-  // quads: lanes 0, 1 of a quad keep p (x, z), lanes 2, 3 keep q (y, 0)
-  const bool up = (lane >> 1) & 1;
-  double v = (up ? q : p) + dpp_f64<0x4E, 0xF>(up ? p : q);   // quad_perm [2,3,0,1]
-  v += dpp_f64<0x124, 0xF>(v);                       // row_ror:4
-  v += dpp_f64<0x128, 0xF>(v);                       // row_ror:8
-  v += shfl_xor_f64(v, lane, 16);
-  v += shfl_xor_f64(v, lane, 32);
-  const int r = lane & 3;
-  comp = r == 0 ? 0 : r == 1 ? 2 : r == 2 ? 1 : 3;
-  return v;
-}
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-// Add the wave's contributions (fx, fy, fz) to dst[0..2] (skipped if
-// all are zero).
-__device__ __forceinline__ void wave_add3(double fx, double fy, double fz, double* dst, int lane) {
-  if (!__any(fx != 0.0 || fy != 0.0 || fz != 0.0)) return;
-  int comp = 3;
-  const double v = wave_sum3(fx, fy, fz, lane, comp);
-  if (lane < 3) atomicAdd(dst + comp, v);
-}
+struct NodeSums {
+  double* buf;                     // [kSumNodes][3][kSumStride], the wave's own
+  double* G;                       // node gradients of the wave's die and type
+  double* dpos;
+  int lane;
+  int filled = 0;
+  int32_t to = 0;                  // the lane's sum's node, or ~(neuron of a bucket)
+
+  __device__ __forceinline__ int node() const { return (lane >> 2) / 3; }
+
+  __device__ __forceinline__ void add(double fx, double fy, double fz, int32_t dst) {
+    double* p = buf + filled * (3 * kSumStride) + lane;
+    p[0] = fx;
+    p[kSumStride] = fy;
+    p[2 * kSumStride] = fz;
+    to = node() == filled ? dst : to;
+    if (++filled == kSumNodes) flush();
+  }
+
+  __device__ __forceinline__ void flush() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int row = lane >> 2, comp = row - 3 * node();
+    if (row < 3 * filled) {
+      const f64x2* p = reinterpret_cast<const f64x2*>(buf + row * kSumStride) + (lane & 3);
+      f64x2 v = p[0];
+#pragma unroll
+      for (int k = 1; k < 8; ++k) v += p[4 * k];
+      double s = v.x + v.y;
+      s += dpp_f64<0xB1, 0xF>(s);        // quad_perm [1,0,3,2]
+      s += dpp_f64<0x4E, 0xF>(s);        // quad_perm [2,3,0,1]
+      if ((lane & 3) == 0 && s != 0.0)
+        atomicAdd((to < 0 ? dpos + 3 * (int64_t)~to : G + 3 * (int64_t)to) + comp, s);
+    }
+    filled = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+};
 
 // The parts of unit U of the tile (the search's level-0 sweep cut into parts: the lane
-// states at the unit's first node come from its ancestors).
+// states at the unit's first node come from its ancestors). OWN: as in the search's sweep.
+template <bool OWN>
 __device__ void attract_unit(const SearchArgs& A, const AttractArgs& O, int tile,
-                             const UnitParts& U, int lane) {
+                             const UnitParts& U, int lane, double* sums) {
   const int64_t slot = (int64_t)tile * kWave + lane;
   const int32_t i = A.work[slot];
   const bool valid = i >= 0;
@@ -136,25 +145,30 @@ __device__ void attract_unit(const SearchArgs& A, const AttractArgs& O, int tile
     zi = A.pos[3 * (int64_t)i + 2];
     g = (double)O.gZ[i];
   }
-  double dxi = 0.0, dyi = 0.0, dzi = 0.0, ds = 0.0;
-  double* G = O.G + ((int64_t)xcc_id() * 2 + t) * O.N * 3;
-  // one accepted entry of this lane: the gradient factor f = g * w * 2 / sigma^2
-  // applied to the offset (x_i - c)
-  auto take = [&](bool on, int32_t v, double cx, double cy, double cz, double& fx, double& fy,
-                  double& fz) {
-    fx = fy = fz = 0.0;
-    if (!on) return;
-    const double dx = xi - cx, dy = yi - cy, dz = zi - cz;
-    const double d2 = dist2(xi, yi, zi, cx, cy, cz);
-    const double w = kernel_weight(v, d2, A.k2);
-    const double f = g * w * O.two_over_s2;
-    fx = f * dx;
-    fy = f * dy;
-    fz = f * dz;
+  double dxi = 0.0, dyi = 0.0, dzi = 0.0, ds = 0.0;   // ds: the sum of f d2
+  NodeSums S{sums, O.G + ((int64_t)xcc_id() * 2 + t) * O.N * 3, O.dpos, lane};
+  // an entry that the lanes of mask m accept: the gradient factor f = g * w * 2 / sigma^2
+  // applied to the offset (x_i - c). Evaluated on every lane, with weight 0 where the lane
+  // does not take the entry; a source whose gradient is not finite gets an explicit 0.
+  const double g2 = g * O.two_over_s2;
+  const bool odd = __any(!(fabs(g2) <= DBL_MAX));
+  auto take = [&](uint64_t m, int32_t v, double cx, double cy, double cz, double d2, int32_t dst) {
+    const bool on = __builtin_amdgcn_inverse_ballot_w64(m);
+    double f = g2 * kernel_weight_if(on, v, d2, A.k2);
+    double ex = xi - cx, ey = yi - cy, ez = zi - cz, e2 = d2;
+    if (OWN || __builtin_expect(odd, 0)) {   // (outside the cube offsets may overflow)
+      f = on ? f : 0.0;
+      ex = on ? ex : 0.0;
+      ey = on ? ey : 0.0;
+      ez = on ? ez : 0.0;
+      e2 = on ? e2 : 0.0;
+    }
+    const double fx = f * ex, fy = f * ey, fz = f * ez;
     dxi -= fx;
     dyi -= fy;
     dzi -= fz;
-    ds += g * w * d2 * O.two_over_s3;
+    ds = __builtin_fma(f, e2, ds);
+    S.add(fx, fy, fz, dst);
   };
   const NodeRec root = load_rec(R, 0);
   if (!(root.meta & kLeafBit)) {
@@ -163,75 +177,109 @@ __device__ void attract_unit(const SearchArgs& A, const AttractArgs& O, int tile
     int32_t x = unit_begin(U, med);
     const int32_t end = part_end(U, U.count - 1, med, root_end);
     int32_t me = valid ? 0 : 0x7FFFFFFF;
-    if (x > 1 && x < end) me = mask_at<true>(A.L2, A.theta2, A.acc_d2, R, x, me, li, xi, yi, zi);
+    if (x > 1 && x < end) me = mask_at<OWN>(A.L2, A.theta2, A.acc_d2, R, x, me, li, xi, yi, zi);
+    NodeRec nxt = load_rec_u(R, (uint32_t)x);
     while (x < end) {
-      const NodeRec cur = load_rec(R, x);
-      const bool active = x >= me;
+      // the next record is requested as soon as the next node is known, ahead of this one's
+      // weights (position N: the record after the last)
+      const NodeRec cur = nxt;
+      const uint64_t m_act = __builtin_amdgcn_ballot_w64(x >= me);
       const uint32_t meta = cur.meta;
+      const int32_t here = x;
       if (meta & kLeafBit) {
-        if (cur.v != 0) {
-          if (!(meta & kBucketBit)) {
-            // a neuron's leaf: its gradient reaches the neuron through the push-down
-            const int32_t id = (int32_t)(meta & kIdMask);
-            double fx, fy, fz;
-            take(active && id != i, cur.v, cur.x, cur.y, cur.z, fx, fy, fz);
-            wave_add3(fx, fy, fz, G + 3 * (int64_t)x, lane);
-          } else {
-            // members of a bucket are entries at their own positions
-            const cptr<int32_t> vs = as_const(A.vs[t]);
-            const cptr<int32_t> order = as_const(A.order);
-            const cptr<double> pos = as_const(A.pos);
-            const int32_t pe = as_const(A.nend)[x];
-            for (int32_t p = as_const(A.nbeg)[x]; p < pe; ++p) {
-              const int32_t id = order[p];
-              const int32_t v = vs[p];
-              double fx, fy, fz;
-              take(active && id != i && v != 0, v, pos[3 * (int64_t)id], pos[3 * (int64_t)id + 1],
-                   pos[3 * (int64_t)id + 2], fx, fy, fz);
-              wave_add3(fx, fy, fz, O.dpos + 3 * (int64_t)id, lane);
-            }
+        x = x + 1;
+        nxt = load_rec_u(R, (uint32_t)x);
+        if (cur.v == 0) continue;
+        if (!(meta & kBucketBit)) {
+          // a neuron's leaf: its gradient reaches the neuron through the push-down
+          const int32_t id = (int32_t)(meta & kIdMask);
+          const uint64_t m = m_act & __builtin_amdgcn_ballot_w64(id != i);
+          if (m)
+            take(m, cur.v, cur.x, cur.y, cur.z, dist2(xi, yi, zi, cur.x, cur.y, cur.z), here);
+        } else {
+          // members of a bucket are entries at their own positions
+          const cptr<int32_t> vs = as_const(A.vs[t]);
+          const cptr<int32_t> order = as_const(A.order);
+          const cptr<double> pos = as_const(A.pos);
+          const int32_t pe = as_const(A.nend)[here];
+          for (int32_t p = as_const(A.nbeg)[here]; p < pe; ++p) {
+            const int32_t id = order[p];
+            const int32_t v = vs[p];
+            const uint64_t m = m_act & __builtin_amdgcn_ballot_w64(id != i);
+            if (v == 0 || !m) continue;
+            const double cx = pos[3 * (int64_t)id], cy = pos[3 * (int64_t)id + 1],
+                         cz = pos[3 * (int64_t)id + 2];
+            take(m, v, cx, cy, cz, dist2(xi, yi, zi, cx, cy, cz), ~id);
           }
         }
-        x = x + 1;
         continue;
       }
       int32_t sk = (int32_t)(meta & kSkipMask);
       sk = sk > x ? sk : x + 1;
       if (cur.v == 0) {
         x = sk;
+        nxt = load_rec_u(R, (uint32_t)x);
         continue;
       }
-      const bool contains = A.own && li >= x && li < sk;
       const double d2 = dist2(xi, yi, zi, cur.x, cur.y, cur.z);
-      const bool acc_ok = bh_accept_u(A.L2, A.theta2, d2, meta);
-      const bool open = active && (contains || !acc_ok);
-      const bool accept = active && !contains && acc_ok;
-      double fx, fy, fz;
-      take(accept, cur.v, cur.x, cur.y, cur.z, fx, fy, fz);
-      wave_add3(fx, fy, fz, G + 3 * (int64_t)x, lane);
-      if (accept) me = sk;
-      x = __any(open) ? x + 1 : sk;
+      uint64_t m_far = __builtin_amdgcn_ballot_w64(
+          OWN ? bh_accept_u(A.L2, A.theta2, d2, meta) : bh_accept_d(A.acc_d2, d2, meta));
+      if (OWN) m_far &= ~__builtin_amdgcn_ballot_w64(li >= x && li < sk);
+      const uint64_t m = m_act & m_far;
+      x = m_act & ~m_far ? x + 1 : sk;
+      nxt = load_rec_u(R, (uint32_t)x);
+      if (m) {
+        __builtin_amdgcn_sched_barrier(0);
+        take(m, cur.v, cur.x, cur.y, cur.z, d2, here);
+        if (__builtin_amdgcn_inverse_ballot_w64(m)) me = sk;
+      }
     }
   }
+  S.flush();
   if (valid) {
     atomicAdd(O.dpos + 3 * (int64_t)i + 0, dxi);
     atomicAdd(O.dpos + 3 * (int64_t)i + 1, dyi);
     atomicAdd(O.dpos + 3 * (int64_t)i + 2, dzi);
   }
   ds = wave_sum(ds);
-  if (lane == 0 && ds != 0.0) atomicAdd(O.dsigma, ds);
+  if (lane == 0 && ds != 0.0) atomicAdd(O.dsigma, ds * O.one_over_s);
 }
 
-// One wave per unit, a part of a tile of the batch path's worklist of sources with
-// a_i > 0 (one simulation).
-__global__ void __launch_bounds__(256) attract_bwd_k(BatchDev B, AttractArgs O) {
+// Persistent waves take the units as the search's sweep does (see search_sweep_k): each die has
+// a range of neighbouring units, so that the nodes near them, whose gradients make up
+// most of the additions, are read by one die (262 144 neurons: 1.88 -> 1.81 ms; 17 M steps of
+// about 37 vector instructions, the vector units busy three quarters of the time).
+template <bool OWN>
+__global__ void __launch_bounds__(kBwdBlock) attract_bwd_k(BatchDev B, SweepOut W, AttractArgs O) {
+  __shared__ __attribute__((aligned(16))) double sums[kBwdBlock / kWave][kSumRoom];
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t unit = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (unit >= *O.unit_count) return;
+  const int nunits = *as_const(W.unit_count);
   const SearchArgs A = args_of(B.sims, 0, B.work);
-  int sim, tile;
-  const UnitParts U = unit_parts(B, __builtin_amdgcn_readfirstlane((int)unit), sim, tile);
-  attract_unit(A, O, tile, U, lane);
+  int got = (int)(blockIdx.x / kXcd * (kBwdBlock / kWave) + threadIdx.x / kWave);
+  for (int q = 0; q < kXcd;) {
+    const int qq = (int)((blockIdx.x + q) % kXcd);
+    const int lo = (int)((int64_t)nunits * qq / kXcd);
+    const int count = (int)((int64_t)nunits * (qq + 1) / kXcd) - lo;
+    const int fixed = ((int)gridDim.x - qq + kXcd - 1) / kXcd * (kBwdBlock / kWave);
+    if (got < 0) {
+      int at = 0;
+      if (lane == 0 && count > fixed) {
+        int32_t* next = &W.queue[qq * kQueueStride];
+        at = __hip_atomic_load(next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (at + fixed < count) at = atomicAdd(next, 1);
+      }
+      got = __builtin_amdgcn_readfirstlane(at) + fixed;
+    }
+    got = __builtin_amdgcn_readfirstlane(got);
+    if (got < count) {
+      int sim, tile;
+      const UnitParts U = unit_parts(B, lo + got, sim, tile);
+      attract_unit<OWN>(A, O, tile, U, lane, sums[threadIdx.x / kWave]);
+    } else {
+      ++q;
+    }
+    got = -1;
+  }
 }
 
 // Z of every source from the sweep's part sums (added in part order, then rounded to

@@ -141,24 +141,28 @@ constexpr int kDefaultBranchLevel = kNoDefer;
 
 // Persistent sweep blocks: occupancy x CUs (times `frac` in [0, 1]), at most one
 // wave per unit (a tile's part).
-hipError_t sweep_blocks_for(int device, bool diag, int64_t max_units, double frac,
-                            unsigned* blocks_out) {
+hipError_t resident_blocks(int device, const void* kernel, int block, int64_t max_units,
+                           double frac, unsigned* blocks_out) {
   int ncu = 0, per_cu = 0;
   hipError_t e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu,
-      diag ? (const void*)search_sweep_k<true, true, true>
-           : (const void*)search_sweep_k<false, true, true>,
-      kWaveBlock, 0);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, 0);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
   int64_t blocks = (int64_t)((double)ncu * per_cu * frac);
-  const int64_t need = (max_units + (kWaveBlock / kWave) - 1) / (kWaveBlock / kWave);
+  const int64_t need = (max_units + (block / kWave) - 1) / (block / kWave);
   if (blocks > need) blocks = need;
   if (blocks < 1) blocks = 1;
   *blocks_out = (unsigned)blocks;
   return hipSuccess;
+}
+
+hipError_t sweep_blocks_for(int device, bool diag, int64_t max_units, double frac,
+                            unsigned* blocks_out) {
+  return resident_blocks(device,
+                         diag ? (const void*)search_sweep_k<true, true, true>
+                              : (const void*)search_sweep_k<false, true, true>,
+                         kWaveBlock, max_units, frac, blocks_out);
 }
 
 // The checkpoints of a search: kCkptMax aimed at per tile if that many slots per tile fit
@@ -1146,9 +1150,8 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   AttractArgs O{};
   O.gZ = gZ;
   O.two_over_s2 = 2.0 / (sigma_um * sigma_um);
-  O.two_over_s3 = 2.0 / (sigma_um * sigma_um * sigma_um);
+  O.one_over_s = 1.0 / sigma_um;
   O.N = N;
-  O.unit_count = S.W.unit_count;
   const int64_t ng = 2 * N * 3, nh = 2 * N * 3, np = 3 * n;
   MSP_HIP_TRY(grads.alloc(sizeof(double) * (size_t)(kGradCopies * ng + nh + np)));
   O.G = grads.as<double>();
@@ -1158,17 +1161,20 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   fill_f64_k<<<grid_for(kGradCopies * ng + nh + np, 256), 256, 0, s>>>(
       O.G, kGradCopies * ng + nh + np, 0.0);
   fill_f64_k<<<1, 64, 0, s>>>(dsigma, 1, 0.0);
-  attract_bwd_k<<<grid_for(max_units_for(n, 1) * kWave, 256), 256, 0, s>>>(S.B, O);
+  const auto walk = own_cell_needed(t, theta) ? attract_bwd_k<true> : attract_bwd_k<false>;
+  unsigned blocks = 0;
+  MSP_HIP_TRY(resident_blocks(t->device, (const void*)walk, kBwdBlock, max_units_for(n, 1), 1.0,
+                              &blocks));
+  walk<<<blocks, kBwdBlock, 0, s>>>(S.B, S.W, O);
   grad_sum_k<<<grid_for(ng, 256), 256, 0, s>>>(O.G, ng);
   const Chunks C = chunks_of(t);
   if (C.nsup > 1)
-    push_cross_k<<<1, kCross2Block, 0, s>>>(C.cross2, C.cross2_kids, C.nsup, t->rec[0], t->rec[1], O.G, H,
-                                      N);
+    push_cross_k<<<1, kCross2Block, 0, s>>>(C.cross2, C.cross2_kids, C.nsup, t->rec[0], t->rec[1],
+                                            O.G, H, N);
   if (C.nch > 1)
     push_cross_k<<<(unsigned)C.nsup, kSuper, 0, s>>>(C.cross, C.cross_kids, C.nch, t->rec[0],
                                                      t->rec[1], O.G, H, N);
-  push_chunk_k<<<(unsigned)C.nch, 512, 0, s>>>(C, t->rec[0], t->rec[1], O.G, H,
-                                                                   N);
+  push_chunk_k<<<(unsigned)C.nch, 512, 0, s>>>(C, t->rec[0], t->rec[1], O.G, H, N);
   push_leaves_k<<<grid_for(n, 256), 256, 0, s>>>(t->leaf_of, t->nbeg, t->nend, t->order,
                                                  t->rec[0], t->rec[1], t->vs[0], t->vs[1], H, N, n,
                                                  O.dpos, dpos);
