@@ -113,6 +113,8 @@ __device__ __forceinline__ void act_send(int32_t q, int32_t q1, const uint32_t* 
     uint32_t to[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) to[k] = out[q + k < q1 ? q + k : q];
+    // (all four before the first is used: the compiler would wait for each in turn)
+    asm volatile("" : "+v"(to[0]), "+v"(to[1]), "+v"(to[2]), "+v"(to[3]));
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (q + k < q1) A.add((int32_t)(to[k] & 0x7FFFFFFFu), to[k] >> 31);
@@ -159,10 +161,10 @@ struct Approximated {
 __device__ __forceinline__ void act_approx(int64_t q, int64_t n, const Approximated& S,
                                            uint64_t seed, uint64_t t,
                                            const double* __restrict__ freq, const Arrivals& A) {
-  const int32_t i = S.src[q], g = S.tgt[q];
-  const uint8_t ty = S.type[q];
+  int32_t i = S.src[q], g = S.tgt[q], ty = S.type[q], x = S.idx ? S.idx[q] : 0;
+  asm volatile("" : "+v"(i), "+v"(g), "+v"(ty), "+v"(x));       // (loaded together)
   if (i < 0 || i >= n || g < 0 || g >= n || ty > 1) return;     // reported at setup
-  const uint64_t s = S.idx ? (uint64_t)S.idx[q] : (uint64_t)q;
+  const uint64_t s = S.idx ? (uint64_t)x : (uint64_t)q;
   const double u = (double)(philox_word0(seed, 5, s, t, 0, 0) >> 11) * 0x1p-53;
   if (u < freq[i]) A.add(g, ty);
 }
@@ -183,16 +185,16 @@ __global__ void __launch_bounds__(kActBlock) act_approx_k(int64_t n, Approximate
 // less per step.
 // Bound by memory in large networks: per neuron 8 bytes read and written for each of v, u
 // and calcium, 4 for each arrival count, 1 + 1 for its type and spike; the epoch's count only
-// where it changes (8M neurons at 15 Hz: 151 -> 130 us, 0.5 GB; marks of neurons with
+// where it changes (8M neurons at 15 Hz: 151 -> 125 us, 0.5 GB; marks of neurons with
 // arrivals, to skip the others' counts, and two or four neurons per thread gain nothing). In
 // small ones by the chain of loads behind a spike (131 101 neurons, 2 synapses each: 8.7 +
-// 3.0 us in two launches -> 7.2 us in one).
+// 3.0 us in two launches -> 6.6 us in one).
 __global__ void __launch_bounds__(kActBlock) act_neuron_k(
     int64_t n, unsigned neurons, const uint8_t* __restrict__ ntype, ActParams P, uint64_t seed,
-    uint64_t t, double* __restrict__ v, double* __restrict__ u, double* __restrict__ ca,
-    uint8_t* __restrict__ spk, int32_t* __restrict__ count, double* __restrict__ freq,
-    Arrivals A, int32_t* __restrict__ last_input, unsigned long long* part,
-    Exact X, Arrivals B, Approximated S) {
+    uint64_t t, bool closes, double* __restrict__ v, double* __restrict__ u,
+    double* __restrict__ ca, uint8_t* __restrict__ spk, int32_t* __restrict__ count,
+    double* __restrict__ freq, Arrivals A, int32_t* __restrict__ last_input,
+    unsigned long long* part, Exact X, Arrivals B, Approximated S) {
   if (blockIdx.x >= neurons) {
     const int64_t total = S.idx ? (int64_t)*S.count : S.m;
     for (int64_t q = (int64_t)(blockIdx.x - neurons) * kActBlock + threadIdx.x; q < total;
@@ -229,7 +231,6 @@ __global__ void __launch_bounds__(kActBlock) act_neuron_k(
     if (f) c = c + P.beta;
     ca[g] = c;
     spk[g] = f ? 1 : 0;
-    const bool closes = (t + 1) % (uint64_t)P.delta == 0;
     if (f || closes) {
       const int32_t cnt = count[g] + (f ? 1 : 0);
       if (closes) freq[g] = (double)cnt * P.inv_delta;

@@ -1652,10 +1652,11 @@ msp_status msp_activity_run(int64_t n, const uint8_t* neuron_type, const int32_t
     const uint64_t t = t0 + (uint64_t)k;
     if (some && !ahead)
       act_approx_k<<<ablocks, kActBlock, 0, s>>>(n, S, seed, t, freq, arrivals(k));
-    ahead = some && k + 1 < steps && (t + 1) % (uint64_t)P.delta != 0;
+    const bool closes = (t + 1) % (uint64_t)P.delta == 0;         // an epoch
+    ahead = some && k + 1 < steps && !closes;
     act_neuron_k<<<(unsigned)nblocks + (ahead ? ablocks : 0), kActBlock, 0, s>>>(
-        n, (unsigned)nblocks, neuron_type, P, seed, t, v, u, calcium, spiked, epoch_count, freq,
-        arrivals(k), k == steps - 1 ? last_input : nullptr,
+        n, (unsigned)nblocks, neuron_type, P, seed, t, closes, v, u, calcium, spiked, epoch_count,
+        freq, arrivals(k), k == steps - 1 ? last_input : nullptr,
         spikes ? part.as<unsigned long long>() : nullptr, X, arrivals(k + 1), S);
     MSP_HIP_TRY(hipGetLastError());
   }
