@@ -75,13 +75,34 @@ search_sweep_k(BatchDev, SweepOut) {
   }
 }
 
-// One thread per worklist slot (source): its elements' draws and restarts. The 64
-// slots of a wavefront form one tile, so the simulation is uniform across the wave.
+// One thread per worklist slot (source) and share of its elements: their draws and
+// restarts. The 64 slots of a wavefront form one tile, so the simulation is uniform across
+// the wave. In launches of up to kDrawSplitTiles tiles a source's elements go to kDrawSplit
+// threads (element j to share j % kDrawSplit, one share's blocks after the other's): such a
+// launch takes as long as its longest chains of record loads (4 096 neurons with up to 2
+// elements: 88 -> 49 us, 60 001: 144 -> 86, 1 M clustered with up to 4: 1.11 -> 1.02 ms). Larger
+// ones are bound by the records that miss the L2 (8M neurons: 185 M lines of 128 bytes, 6.6
+// TB/s), and the tile's data would be read twice (3.55 -> 3.93 ms, 64 simulations 1.52 -> 1.65).
+// In both, groups of kDrawGroup neighbouring blocks share a die's L2 (8M neurons: 3.55 -> 3.49
+// ms, 64 simulations 1.52 -> 1.44; 128 blocks: the same, but 1 M clustered neurons 1.09 -> 1.21).
+constexpr int kDrawSplit = 2;
+constexpr int kDrawSplitTiles = 16384;
+constexpr int kDrawGroup = 32;
+
 template <bool DIAG, bool DEFER>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) search_draw_k(BatchDev B, SweepOut W) {
-  const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int tiles = *as_const(W.tile_count);
+  if (tiles <= 0) return;
+  const int split = tiles <= kDrawSplitTiles ? kDrawSplit : 1;
+  const int per = (int)blockDim.x / kWave, blocks = (tiles + per - 1) / per;
+  const int group = blocks < kXcd * kDrawGroup ? 1 : kDrawGroup;
+  const int padded = (blocks + kXcd * group - 1) / (kXcd * group) * (kXcd * group);
+  const int share = (int)blockIdx.x / padded, c = (int)blockIdx.x % padded, b = c / kXcd;
+  if (share >= split) return;
+  const int64_t at = (int64_t)(b / group * kXcd + c % kXcd) * group + b % group;
+  const int64_t slot = at * blockDim.x + threadIdx.x;
   const int64_t tile = slot / kWave;
-  if (tile >= *W.tile_count) return;
+  if (tile >= tiles) return;
   const int sim = __builtin_amdgcn_readfirstlane(find_sim(as_const(B.tile_base), B.nsims, tile));
   const SearchArgs A = args_of(B.sims, sim, B.work);
   const int plog = __builtin_amdgcn_readfirstlane((int)as_const(B.plog)[sim]);
@@ -107,7 +128,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) s
                          reinterpret_cast<uint32_t*>(keep_lds + kRestartKeep * blockDim.x) +
                              threadIdx.x,
                          (int)blockDim.x};
-  draw_slot<DIAG, DEFER>(A, D, W, slot, u0, plog, s0, nslog, &keep);
+  draw_slot<DIAG, DEFER>(A, D, W, slot, share, split, u0, plog, s0, nslog, &keep);
 }
 
 // Second phase of a two-phase search (one simulation): one thread per request in
@@ -885,7 +906,11 @@ inline void launch_draw(const SearchScratch& S, unsigned grid, int block, hipStr
 
 inline hipError_t enqueue_search(SearchScratch& S, bool diag, unsigned sweep_blocks,
                                  int draw_block, hipStream_t s, hipEvent_t mid = nullptr) {
-  const unsigned draw_grid = grid_for(S.B.max_slots, draw_block);
+  // (whole groups of blocks on every die, once for each share of the elements)
+  const unsigned turn =
+      S.B.max_slots < (int64_t)kXcd * kDrawGroup * draw_block ? kXcd : kXcd * kDrawGroup;
+  const unsigned draw_grid =
+      (grid_for(S.B.max_slots, draw_block) + turn - 1) / turn * turn * kDrawSplit;
   if (diag)
     launch_sweep<true, true>(S, sweep_blocks, s);
   else

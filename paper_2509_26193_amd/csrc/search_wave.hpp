@@ -620,14 +620,14 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
   }
 }
 
-// The draws and restarts of the source in worklist slot `slot` (DEFER: restarts from
-// cells at depth >= W.defer.depth become second-phase requests). The slot's tile has
-// 2^plog parts, the launch's parts u0, u0 + 1, ... with checkpoint slots from s0 on, 2^nslog
-// each. keep: the thread's memory for a restart level's entries (see restart_search).
+// The draws and restarts of elements first, first + split, ... of the source in worklist
+// slot `slot` (DEFER: restarts from cells at depth >= W.defer.depth become second-phase
+// requests). The slot's tile has 2^plog parts, the launch's parts u0, u0 + 1, ... with
+// checkpoint slots from s0 on, 2^nslog each. keep: the thread's memory for a restart level's entries (see restart_search).
 template <bool DIAG, bool DEFER>
 __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D, const SweepOut& W,
-                                          int64_t slot, int64_t u0, int plog, int64_t s0,
-                                          int nslog, const KeptEntries* keep) {
+                                          int64_t slot, int first, int split, int64_t u0, int plog,
+                                          int64_t s0, int nslog, const KeptEntries* keep) {
   const int32_t i = A.work[slot];
   if (i < 0) return;
   const int lane = (int)(slot % kWave);
@@ -669,7 +669,7 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
       c0.entries += W.e0[(u0 + q) * kWave + lane];
     }
   }
-  for (int32_t j = 0; j < a; ++j) {
+  for (int32_t j = first; j < a; j += split) {
     int lev = 1;
     Count c = c0;
     int32_t tgt = -1;
