@@ -374,7 +374,8 @@ def commit_synapses(target: torch.Tensor, elem_offset: torch.Tensor, neuron_type
     src = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
     tgt = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
     sty = torch.empty(max(cap, 1), dtype=torch.uint8, device=dev)
-    nf = torch.zeros(1, dtype=torch.int64, device=dev)
+    # (the call writes it from the device and waits: read without a copy)
+    nf = torch.zeros(1, dtype=torch.int64, pin_memory=True)
     Sx = target.numel()
     acc = torch.empty(max(Sx, 1), dtype=torch.uint8, device=dev) if return_accepted else None
     tp = _dev(target, torch.int32, "target") if target.numel() > 0 else None

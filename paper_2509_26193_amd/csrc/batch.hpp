@@ -186,7 +186,15 @@ __global__ void phase2_count_k(SweepOut W, int64_t nreq, int64_t* out) {
   *out = lo;
 }
 
-// Validity of vac_axon and types; per-simulation status starts at 0 (fill before).
+// Statuses and counters at 0, the worklist empty (-1).
+__global__ void b_clear_k(BatchDev B, int32_t* counters) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < B.max_slots) B.work[q] = -1;
+  if (q < B.nsims) B.status[q] = 0;
+  if (q < kCounters) counters[q] = 0;
+}
+
+// Validity of vac_axon and types; per-simulation status starts at 0 (b_clear_k).
 __global__ void b_check_k(BatchDev B, int64_t total) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= total) return;
@@ -254,11 +262,19 @@ __global__ void b_src_type_k(BatchDev B, int64_t total) {
   B.src_type[g] = st;
 }
 
-struct FlatSource {             // flat Morton position g is a type-`want` source
+struct FlatSource {             // flat Morton position g: a source of type 0 (low word) or 1
   const uint8_t* src_type;
-  uint8_t want;
-  __device__ int32_t operator()(int32_t, int64_t g) const { return src_type[g] == want ? 1 : 0; }
+  __device__ int64_t operator()(int32_t, int64_t g) const {
+    const uint8_t t = src_type[g];
+    return t == 0 ? 1 : t == 1 ? 1ll << 32 : 0;
+  }
 };
+
+__device__ __forceinline__ int32_t sources0(int64_t p) { return (int32_t)(uint32_t)p; }
+__device__ __forceinline__ int32_t sources1(int64_t p) { return (int32_t)(p >> 32); }
+__device__ __forceinline__ int64_t sources(int64_t p) {
+  return (int64_t)sources0(p) + sources1(p);
+}
 
 // log2 of the parts of each of a simulation's `ts` tiles (force >= 0: that). A launch with
 // few tiles takes as long as the longest chain of dependent record loads in it: the more
@@ -291,7 +307,7 @@ __host__ __device__ inline int parts_log(int64_t ts, int force) {
 constexpr int kTilesBlock = kScanBlock;
 
 __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* tile_count,
-                                                        int32_t* unit_count, int32_t* sources,
+                                                        int32_t* unit_count, int32_t* nsources,
                                                         int64_t total, int force, int ck_slots,
                                                         int64_t ck_cap) {
   __shared__ int64_t lds[kTilesBlock / kWave];
@@ -299,7 +315,8 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
   auto tiles = [&](int s) -> int64_t {
     if (s >= B.nsims) return 0;
     const int64_t b = B.nbase[s], e = B.nbase[s + 1];
-    const int32_t c0 = B.p0[e] - B.p0[b], c1 = B.p1[e] - B.p1[b];
+    const int64_t c = B.sources[e] - B.sources[b];
+    const int32_t c0 = sources0(c), c1 = sources1(c);
     return (c0 + kWave - 1) / kWave + (c1 + kWave - 1) / kWave;
   };
   // the launch's parts, and its slots at ever fewer per part
@@ -365,7 +382,7 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
     B.slot_base[B.nsims] = at_s;
     *tile_count = (int32_t)at_t;
     *unit_count = (int32_t)at_u;
-    *sources = B.p0[total] + B.p1[total];
+    *nsources = (int32_t)sources(B.sources[total]);
   }
 }
 
@@ -671,7 +688,7 @@ __global__ void b_hkeys_k(BatchDev B, int64_t total, int gb, int kb, uint64_t* k
   morton_decode(d.keys[g - B.nbase[s]], x, y, z);
   const int hb = kb - gb;
   const uint64_t h = hilbert3(x, y, z) >> (63 - hb);
-  const int64_t idx = (int64_t)B.p0[g] + B.p1[g];
+  const int64_t idx = sources(B.sources[g]);
   key[idx] = ((uint64_t)(2 * s + t) << hb) | h;
   val[idx] = (int32_t)g;
 }
@@ -680,15 +697,15 @@ __global__ void b_hkeys_k(BatchDev B, int64_t total, int gb, int kb, uint64_t* k
 // sorted position minus the group's start.
 __global__ void b_work_sorted_k(BatchDev B, int64_t total, const int32_t* __restrict__ val) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= (int64_t)B.p0[total] + B.p1[total]) return;
+  if (p >= sources(B.sources[total])) return;
   const int64_t g = val[p];
   const int s = find_sim(B.nbase, B.nsims, g);
   const int64_t b = B.nbase[s], e = B.nbase[s + 1];
   const SimDesc& d = B.sims[s];
   const int32_t id = d.order[g - b];
   const int t = B.src_type[g];
-  const int32_t c0 = B.p0[e] - B.p0[b];
-  const int64_t start = (int64_t)B.p0[b] + B.p1[b] + (t ? c0 : 0);
+  const int32_t c0 = sources0(B.sources[e] - B.sources[b]);
+  const int64_t start = sources(B.sources[b]) + (t ? c0 : 0);
   const int64_t base = (int64_t)B.tile_base[s] * kWave +
                        (t ? (int64_t)((c0 + kWave - 1) / kWave) * kWave : 0);
   B.work[base + (p - start)] = id;
@@ -761,7 +778,7 @@ inline ScratchSizes scratch_sizes(const SearchSize& q) {
   const int64_t mp = max_parts_for(q.total_n, q.nsims, q.force);
   const bool ck = q.slots > 0;
   z.ea = align_up(sizeof(int64_t) * (q.total_n + 1));
-  z.p = align_up(sizeof(int32_t) * (q.total_n + 1));
+  z.p = align_up(sizeof(int64_t) * (q.total_n + 1));
   z.base = align_up(sizeof(int32_t) * (q.nsims + 1));
   z.slot_base = align_up(sizeof(int64_t) * (q.nsims + 1));
   z.log = align_up(sizeof(uint8_t) * q.nsims);
@@ -781,7 +798,7 @@ inline ScratchSizes scratch_sizes(const SearchSize& q) {
   z.hkey = align_up(sizeof(uint64_t) * q.total_n);
   z.hval = align_up(sizeof(int32_t) * q.total_n);
   z.hsort = align_up(radix_sort_ws_bytes(q.total_n));
-  z.total = z.ea + 2 * z.p + 3 * z.base + z.slot_base + 3 * z.log + z.status + z.work + z.Z +
+  z.total = z.ea + z.p + 3 * z.base + z.slot_base + 3 * z.log + z.status + z.work + z.Z +
             3 * z.v + z.nck + z.cuts + z.ckx + z.ckP + z.ckme + z.counters + z.scan + z.srct +
             2 * z.hkey + 2 * z.hval + z.hsort;
   return z;
@@ -802,8 +819,7 @@ inline SearchScratch carve(void* base, const SearchSize& q, const SimDesc* d_sim
   S.B.nsims = q.nsims;
   S.B.nbase = d_nbase;
   S.B.ea = reinterpret_cast<int64_t*>(take(z.ea));
-  S.B.p0 = reinterpret_cast<int32_t*>(take(z.p));
-  S.B.p1 = reinterpret_cast<int32_t*>(take(z.p));
+  S.B.sources = reinterpret_cast<int64_t*>(take(z.p));
   S.B.tile_base = reinterpret_cast<int32_t*>(take(z.base));
   S.B.part_base = reinterpret_cast<int32_t*>(take(z.base));
   S.B.unit_base = reinterpret_cast<int32_t*>(take(z.base));
@@ -847,20 +863,16 @@ inline hipError_t enqueue_prep(SearchScratch& S, hipStream_t s) {
   BatchDev& B = S.B;
   const int64_t total_n = S.q.total_n;
   const unsigned g = grid_for(total_n, 256);
-  fill_i32_k<<<grid_for(B.nsims, 256), 256, 0, s>>>(B.status, B.nsims, 0);
-  fill_i32_k<<<grid_for(B.max_slots, 256), 256, 0, s>>>(B.work, B.max_slots, -1);
-  fill_i32_k<<<grid_for(kCounters, 256), 256, 0, s>>>(S.counters, kCounters, 0);
+  b_clear_k<<<grid_for(std::max<int64_t>(B.max_slots, std::max<int64_t>(B.nsims, kCounters)), 256),
+              256, 0, s>>>(B, S.counters);
   b_check_k<<<g, 256, 0, s>>>(B, total_n);
   hipError_t e = exclusive_scan<int64_t, int32_t, FlatAxon>(nullptr, B.ea, total_n, FlatAxon{B},
                                                              true, s, S.scan_tmp);
   if (e != hipSuccess) return e;
   b_offsets_k<<<g, 256, 0, s>>>(B, total_n);
   b_src_type_k<<<g, 256, 0, s>>>(B, total_n);
-  e = exclusive_scan<int32_t, int32_t, FlatSource>(nullptr, B.p0, total_n,
-                                                   FlatSource{B.src_type, 0}, true, s, S.scan_tmp);
-  if (e != hipSuccess) return e;
-  e = exclusive_scan<int32_t, int32_t, FlatSource>(nullptr, B.p1, total_n,
-                                                   FlatSource{B.src_type, 1}, true, s, S.scan_tmp);
+  e = exclusive_scan<int64_t, int32_t, FlatSource>(nullptr, B.sources, total_n,
+                                                   FlatSource{B.src_type}, true, s, S.scan_tmp);
   if (e != hipSuccess) return e;
   b_tiles_k<<<1, kTilesBlock, 0, s>>>(B, S.counters, S.counters + 2, S.counters + 1, total_n,
                                       S.q.force, S.W.ck_slots, S.W.ck_cap);

@@ -23,11 +23,17 @@ struct GroupThr {
   int32_t mode;
 };
 
-// Source of every request slot below S.
-__global__ void __launch_bounds__(kCommitBlock) src_of_k(const int64_t* __restrict__ off, int64_t n,
-                                                        DevCount S, int32_t* __restrict__ src_of) {
+// Start of a commit: the source of every request slot below S, the groups' counts and (after
+// them, cnt[2n]) the flags cleared.
+__global__ void __launch_bounds__(kCommitBlock) commit_start_k(const int64_t* __restrict__ off,
+                                                              int64_t n, DevCount S,
+                                                              int32_t* __restrict__ src_of,
+                                                              int32_t* __restrict__ cnt) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i > n) return;
+  cnt[2 * i] = 0;
+  if (i == n) return;
+  cnt[2 * i + 1] = 0;
   const int64_t S_ = S.get();
   const int64_t e = off[i + 1] < S_ ? off[i + 1] : S_;
   for (int64_t s = off[i]; s < e; ++s) src_of[s] = (int32_t)i;
@@ -167,26 +173,28 @@ __global__ void __launch_bounds__(kCommitBlock) req_decide_k(
   }
 }
 
-// Writes the accepted requests' synapses at their places in the output list, unless
-// the list (capacity `cap`) cannot hold them all or a target was out of range
-// (kErrArgs in *flags): then it writes nothing (and sets kCommitCapacity for the
-// former). The vacancies are taken by dec_groups_k and dec_sources_k under the same
-// condition.
-__device__ __forceinline__ bool commit_ok(const int64_t* __restrict__ dst, int64_t S_, int64_t cap,
-                                          const int32_t* flags) {
-  return S_ > 0 && !(*flags & kErrArgs) && dst[S_] <= cap;
-}
-
-__global__ void __launch_bounds__(kCommitBlock) commit_write_k(
+// End of a commit: the accepted requests' synapses at their places in the output list, each
+// group's accepted count off its target's vacancies of that type (the two types of a target
+// are different arrays, so no two threads write one count), each source's accepted requests
+// off its vacant axonal elements, and the number of synapses formed. If the list (capacity
+// `cap`) cannot hold them all, or a target was out of range (kErrArgs in *flags), nothing is
+// written and none are formed (kCommitCapacity is set for the former). One launch for the
+// four: they are independent of each other.
+__global__ void __launch_bounds__(kCommitBlock) commit_end_k(
     const uint8_t* __restrict__ acc, const int64_t* __restrict__ dst, const int64_t* __restrict__ key,
-    const int32_t* __restrict__ src_of, DevCount S, int64_t cap, int32_t* syn_src, int32_t* syn_tgt,
-    uint8_t* syn_type, uint8_t* acc_out, int32_t* flags) {
+    const int32_t* __restrict__ src_of, const int32_t* __restrict__ acc_cnt,
+    const int64_t* __restrict__ off, int64_t n, DevCount S, int64_t cap, int32_t* syn_src,
+    int32_t* syn_tgt, uint8_t* syn_type, uint8_t* acc_out, int32_t* __restrict__ vexc,
+    int32_t* __restrict__ vinh, int32_t* __restrict__ vac_axon, int64_t* __restrict__ n_formed,
+    int32_t* flags) {
   const int64_t S_ = S.get();
-  if (S_ == 0 || (*flags & kErrArgs)) return;
-  if (dst[S_] > cap) {
-    if (gtid() == 0) atomicOr(flags, kCommitCapacity);
-    return;
+  const int64_t formed = S_ == 0 ? 0 : dst[S_];
+  const bool bad = (*flags & kErrArgs) != 0, over = formed > cap;
+  if (gtid() == 0) {
+    *n_formed = bad || over ? 0 : formed;
+    if (S_ != 0 && !bad && over) atomicOr(flags, kCommitCapacity);
   }
+  if (S_ <= 0 || bad || over) return;
   for (int64_t s = gtid(); s < S_; s += gstride()) {
     const uint8_t a = acc[s];
     if (acc_out) acc_out[s] = a;
@@ -199,27 +207,10 @@ __global__ void __launch_bounds__(kCommitBlock) commit_write_k(
     syn_tgt[p] = g;
     syn_type[p] = (uint8_t)ty;
   }
-}
-
-// Each group's accepted count off its target's vacancies of that type (the two types
-// of a target are different arrays, so no two threads write one count).
-__global__ void __launch_bounds__(kCommitBlock) dec_groups_k(
-    const int32_t* __restrict__ acc_cnt, int64_t n2, const int64_t* __restrict__ dst, DevCount S,
-    int64_t cap, const int32_t* flags, int32_t* __restrict__ vexc, int32_t* __restrict__ vinh) {
-  if (!commit_ok(dst, S.get(), cap, flags)) return;
-  for (int64_t k = gtid(); k < n2; k += gstride()) {
+  for (int64_t k = gtid(); k < 2 * n; k += gstride()) {
     const int32_t a = acc_cnt[k];
     if (a) ((k & 1) ? vinh : vexc)[k >> 1] -= a;
   }
-}
-
-// Each source's accepted requests off its vacant axonal elements.
-__global__ void __launch_bounds__(kCommitBlock) dec_sources_k(
-    const int64_t* __restrict__ off, int64_t n, const uint8_t* __restrict__ acc,
-    const int64_t* __restrict__ dst, DevCount S, int64_t cap, const int32_t* flags,
-    int32_t* __restrict__ vac_axon) {
-  const int64_t S_ = S.get();
-  if (!commit_ok(dst, S_, cap, flags)) return;
   for (int64_t i = gtid(); i < n; i += gstride()) {
     const int64_t e = off[i + 1] < S_ ? off[i + 1] : S_;
     int32_t a = 0;
@@ -231,14 +222,5 @@ __global__ void __launch_bounds__(kCommitBlock) dec_sources_k(
 struct AccFlag {
   __device__ int64_t operator()(uint8_t a, int64_t) const { return (int64_t)a; }
 };
-
-// Synapses formed: the accepted requests, or 0 where commit_write_k wrote nothing.
-__global__ void formed_k(const int64_t* __restrict__ dst, DevCount S, int64_t cap,
-                         const int32_t* __restrict__ flags, int64_t* __restrict__ n_formed) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int64_t S_ = S.get();
-  const int64_t f = S_ == 0 ? 0 : dst[S_];
-  *n_formed = ((*flags & kErrArgs) || f > cap) ? 0 : f;
-}
 
 }  // namespace msp

@@ -37,7 +37,7 @@ void carve_neurons(msp_octree_s* t, char* base, size_t* bytes) {
   const int log = run_log(n);
   t->box[0] = c.take<float>(6 * runs_of(n, log));
   t->box[1] = c.take<float>(6 * runs_of(n, log + 6));
-  t->err = c.take<int32_t>(1);
+  t->err = c.take<int32_t>(3);
   *bytes = c.off;
 }
 
@@ -387,24 +387,23 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
   carve_neurons(t, nullptr, &bytes);
   TRY(pool_alloc(&t->slab_n, bytes, s));
   carve_neurons(t, static_cast<char*>(t->slab_n), &bytes);
-  TRY(hipMemsetAsync(t->err, 0, sizeof(int32_t), s));
+  TRY(hipMemsetAsync(t->err, 0, 3 * sizeof(int32_t), s));
   {
     // every temporary of the build in one pool block (one allocation, one free)
     const size_t b_k1 = align_up(sizeof(uint64_t) * n), b_v1 = align_up(sizeof(int32_t) * n),
                  b_ws = align_up(radix_sort_ws_bytes(n)), b_cnt = align_up(sizeof(int32_t) * n),
                  b_base = align_up(sizeof(int32_t) * (n + 1)),
-                 b_out = align_up(2 * sizeof(int32_t)), b_scan = align_up(scan_tmp_bytes<int32_t>(n));
+                 b_scan = align_up(scan_tmp_bytes<int32_t>(n));
     Temp tmp(s);
-    TRY(tmp.alloc(b_k1 + b_v1 + b_ws + b_cnt + b_base + b_out + b_scan));
+    TRY(tmp.alloc(b_k1 + b_v1 + b_ws + b_cnt + b_base + b_scan));
     char* tp = tmp.as<char>();
     uint64_t* k1 = reinterpret_cast<uint64_t*>(tp);
     int32_t* v1 = reinterpret_cast<int32_t*>(tp + b_k1);
     void* sort_ws = tp + b_k1 + b_v1;
     int32_t* cntp = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws);
     int32_t* basep = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt);
-    int32_t* outside = reinterpret_cast<int32_t*>(tp + b_k1 + b_v1 + b_ws + b_cnt + b_base);
-    void* scan_ws = tp + b_k1 + b_v1 + b_ws + b_cnt + b_base + b_out;
-    TRY(hipMemsetAsync(outside, 0, 2 * sizeof(int32_t), s));
+    int32_t* outside = t->err + 1;               // a position outside, keys out of order
+    void* scan_ws = tp + b_k1 + b_v1 + b_ws + b_cnt + b_base;
     keys_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(pos, n, box_min[0], box_min[1],
                                                             box_min[2], box_edge, t->pos, t->keys,
                                                             t->order, t->err, outside);
@@ -425,9 +424,15 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
       TRY(hipGetLastError());
       TRY((exclusive_scan<int32_t, int32_t, Ident<int32_t>>(cntp, basep, n, Ident<int32_t>(), true,
                                                             s, scan_ws)));
-      TRY(hipMemcpyAsync(&N32, basep + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      TRY(hipMemcpyAsync(found, outside, sizeof(found), hipMemcpyDeviceToHost, s));
-      TRY(hipStreamSynchronize(s));
+      ReadBack R;
+      R.add(basep + n);
+      R.add(outside);
+      R.add(outside + 1);
+      int64_t got[3];
+      TRY(read_back(R, got, s));
+      N32 = (int32_t)got[0];
+      found[0] = (int32_t)got[1];
+      found[1] = (int32_t)got[2];
       if (!found[1] || whole) break;
     }
     double far = 0.0;
@@ -531,7 +536,6 @@ msp_status msp_find_targets_diag(msp_octree t, const uint8_t* neuron_type,
     any = h.diag.z0 || h.diag.levels || h.diag.visits || h.diag.opens || h.diag.visits0 ||
           h.diag.opens0 || h.diag.entries0;
   }
-  const int64_t hbase[2] = {0, n};
   int force = -1;                       // parts per tile: automatic
   if (diag && diag->parts_per_tile != 0) {
     const int pp = diag->parts_per_tile;
@@ -544,25 +548,26 @@ msp_status msp_find_targets_diag(msp_octree t, const uint8_t* neuron_type,
   void* scratch = nullptr;
   // the workspace also holds the simulation descriptor and the neuron bases
   const size_t body = scratch_sizes(size).total;
-  MSP_HIP_TRY(ws.acquire(body + align_up(sizeof(SimDesc)) + align_up(sizeof(hbase)), s,
+  MSP_HIP_TRY(ws.acquire(body + align_up(sizeof(SimDesc)) + align_up(2 * sizeof(int64_t)), s,
                          &scratch));
   SimDesc* dsim = reinterpret_cast<SimDesc*>(static_cast<char*>(scratch) + body);
   int64_t* dbase = reinterpret_cast<int64_t*>(static_cast<char*>(scratch) + body +
                                               align_up(sizeof(SimDesc)));
-  MSP_HIP_TRY(hipMemcpyAsync(dsim, &h, sizeof(SimDesc), hipMemcpyHostToDevice, s));
-  MSP_HIP_TRY(hipMemcpyAsync(dbase, hbase, sizeof(hbase), hipMemcpyHostToDevice, s));
+  put_desc_k<<<1, 64, 0, s>>>(h, dsim, dbase, n);
+  MSP_HIP_TRY(hipGetLastError());
   SearchScratch S = carve(scratch, size, dsim, dbase);
   S.own_cell = own_cell_needed(t, theta);
   if (any) S.W.wave_steps = reinterpret_cast<unsigned long long*>(diag->wave_steps);
   MSP_HIP_TRY(enqueue_prep(S, s));
-  int32_t status = 0, ntiles = 0, nunits = 0;
-  int64_t total_S = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&status, S.B.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipMemcpyAsync(&ntiles, S.counters, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipMemcpyAsync(&nunits, S.W.unit_count, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipMemcpyAsync(&total_S, elem_offset_out + n, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack R;
+  R.add(S.B.status);
+  R.add(S.counters);
+  R.add(S.W.unit_count);
+  R.add(elem_offset_out + n);
+  int64_t got[4];
+  MSP_HIP_TRY(read_back(R, got, s));
+  const int32_t status = (int32_t)got[0], ntiles = (int32_t)got[1], nunits = (int32_t)got[2];
+  const int64_t total_S = got[3];
   if (status & kSimInvalid) return MSP_ERR_INVALID;
   if (status & kSimCapacity) return MSP_ERR_CAPACITY;
   if (diag && diag->phase2_requests)
@@ -655,13 +660,13 @@ msp_status msp_search_offsets(const int32_t* vac_axon, int64_t n, int64_t* elem_
   MSP_HIP_TRY(hipGetLastError());
   MSP_HIP_TRY((exclusive_scan<int64_t, int32_t, NonNeg>(vac_axon, elem_offset_out, n, NonNeg(),
                                                        true, s)));
-  int64_t S = 0;
-  int32_t bad = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&S, elem_offset_out + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipMemcpyAsync(&bad, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
-  if (bad) return MSP_ERR_INVALID;
-  *S_out = S;
+  ReadBack R;
+  R.add(elem_offset_out + n);
+  R.add(err.as<int32_t>());
+  int64_t got[2];
+  MSP_HIP_TRY(read_back(R, got, s));
+  if (got[1]) return MSP_ERR_INVALID;
+  *S_out = got[0];
   return MSP_OK;
 }
 
@@ -733,14 +738,16 @@ msp_status msp_commit_synapses_ex(const int32_t* target, const int64_t* elem_off
   if (!elem_offset || !neuron_type || !vac_axon || !vac_exc || !vac_inh || !n_formed)
     return MSP_ERR_INVALID;
   if (n < 1 || n > MSP_MAX_NEURONS || syn_capacity < 0) return MSP_ERR_INVALID;
+  ReadBack R;
+  R.add(elem_offset + n);
   int64_t S = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&S, elem_offset + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  MSP_HIP_TRY(read_back(R, &S, s));
   // group offsets, cursors and request indices are int32
   if (S < 0 || S >= (int64_t)INT32_MAX) return MSP_ERR_INVALID;
   if (S == 0) {
     fill_i64_k<<<1, 64, 0, s>>>(n_formed, 1, 0);
     MSP_HIP_TRY(hipGetLastError());
+    MSP_HIP_TRY(hipStreamSynchronize(s));       // (n_formed may be the host's memory)
     return MSP_OK;
   }
   if (!target) return MSP_ERR_INVALID;
@@ -757,9 +764,10 @@ msp_status msp_commit_synapses_ex(const int32_t* target, const int64_t* elem_off
   MSP_HIP_TRY(enqueue_commit(w, target, elem_offset, neuron_type, n, host_count(S), vac_axon,
                              vac_exc, vac_inh, seed, host_step(step), syn_src, syn_tgt, syn_type,
                              syn_capacity, n_formed, accepted_out, s));
-  int32_t flags = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&flags, w.flags, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack F;
+  F.add(w.flags);
+  int64_t flags = 0;
+  MSP_HIP_TRY(read_back(F, &flags, s));
   if (flags & kErrArgs) return MSP_ERR_INVALID;
   if (flags & kCommitCapacity) return MSP_ERR_CAPACITY;
   return MSP_OK;
@@ -1121,19 +1129,19 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   // the search's preparation gives the worklist; targets are not written here
   SimDesc h = make_desc(t, neuron_type, vac_axon, sigma_um, theta, 0, 0,
                         reinterpret_cast<int32_t*>(off.p), off.as<int64_t>(), INT64_MAX);
-  const int64_t hbase[2] = {0, n};
   MSP_HIP_TRY(dsim.alloc(sizeof(SimDesc)));
-  MSP_HIP_TRY(dbase.alloc(sizeof(hbase)));
+  MSP_HIP_TRY(dbase.alloc(2 * sizeof(int64_t)));
   // the worklist only: no draws, so no checkpoints
   const SearchSize size{n, 1, 0, 0, -1, false};
   MSP_HIP_TRY(scratch.alloc(scratch_sizes(size).total));
-  MSP_HIP_TRY(hipMemcpyAsync(dsim.p, &h, sizeof(SimDesc), hipMemcpyHostToDevice, s));
-  MSP_HIP_TRY(hipMemcpyAsync(dbase.p, hbase, sizeof(hbase), hipMemcpyHostToDevice, s));
+  put_desc_k<<<1, 64, 0, s>>>(h, dsim.as<SimDesc>(), dbase.as<int64_t>(), n);
+  MSP_HIP_TRY(hipGetLastError());
   SearchScratch S = carve(scratch.p, size, dsim.as<SimDesc>(), dbase.as<int64_t>());
   MSP_HIP_TRY(enqueue_prep(S, s));
-  int32_t status = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&status, S.B.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack R;
+  R.add(S.B.status);
+  int64_t status = 0;
+  MSP_HIP_TRY(read_back(R, &status, s));
   if (status & kSimInvalid) return MSP_ERR_INVALID;
 
   if (!bwd) {
@@ -1255,22 +1263,17 @@ msp_status msp_plasticity_record(int64_t n, const int32_t* new_src, const int32_
   if (!new_src || !new_tgt || !new_type || !syn_src || !syn_tgt || !syn_type)
     return MSP_ERR_INVALID;
   if (m + m_new > capacity) return MSP_ERR_CAPACITY;
-  MSP_HIP_TRY(hipMemcpyAsync(syn_src + m, new_src, sizeof(int32_t) * m_new,
-                             hipMemcpyDeviceToDevice, s));
-  MSP_HIP_TRY(hipMemcpyAsync(syn_tgt + m, new_tgt, sizeof(int32_t) * m_new,
-                             hipMemcpyDeviceToDevice, s));
-  MSP_HIP_TRY(hipMemcpyAsync(syn_type + m, new_type, sizeof(uint8_t) * m_new,
-                             hipMemcpyDeviceToDevice, s));
   Temp err(s);
   MSP_HIP_TRY(err.alloc(sizeof(int32_t)));
   fill_i32_k<<<1, 64, 0, s>>>(err.as<int32_t>(), 1, 0);
-  bind_k<<<grid_cap(m_new, kPlastBlock), kPlastBlock, 0, s>>>(new_src, new_tgt, new_type,
-                                                            host_count(m_new), n, bound,
-                                                            err.as<int32_t>());
+  bind_k<<<grid_cap(m_new, kPlastBlock), kPlastBlock, 0, s>>>(
+      new_src, new_tgt, new_type, m_new, SynList{syn_src + m, syn_tgt + m, syn_type + m}, n, bound,
+      err.as<int32_t>());
   MSP_HIP_TRY(hipGetLastError());
-  int32_t bad = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&bad, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack R;
+  R.add(err.as<int32_t>());
+  int64_t bad = 0;
+  MSP_HIP_TRY(read_back(R, &bad, s));
   return bad ? MSP_ERR_INVALID : MSP_OK;
 }
 
@@ -1299,9 +1302,10 @@ msp_status msp_plasticity_step(int64_t n, const msp_plasticity_params* params, u
   MSP_HIP_TRY(enqueue_plasticity(w, n, c, seed, host_step(step), z, bound,
                                  SynList{syn_src, syn_tgt, syn_type}, host_count(m), m_dev,
                                  vac_axon, vac_exc, vac_inh, s));
+  ReadBack R;
+  R.add(m_dev);
   int64_t M = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&M, m_dev, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  MSP_HIP_TRY(read_back(R, &M, s));
   *m_out = M;
   return MSP_OK;
 }
@@ -1553,9 +1557,10 @@ msp_status msp_activity_init(int64_t n, const uint8_t* neuron_type,
                                                           u, calcium, spiked, epoch_count, freq,
                                                           err.as<int32_t>());
   MSP_HIP_TRY(hipGetLastError());
-  int32_t bad = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&bad, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack R;
+  R.add(err.as<int32_t>());
+  int64_t bad = 0;
+  MSP_HIP_TRY(read_back(R, &bad, s));
   return bad ? MSP_ERR_INVALID : MSP_OK;
 }
 
@@ -1664,9 +1669,10 @@ msp_status msp_activity_run(int64_t n, const uint8_t* neuron_type, const int32_t
     act_spikes_k<<<1, kActBlock, 0, s>>>(part.as<int64_t>(), slots, spikes);
     MSP_HIP_TRY(hipGetLastError());
   }
-  int32_t bad = 0;
-  MSP_HIP_TRY(hipMemcpyAsync(&bad, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  MSP_HIP_TRY(hipStreamSynchronize(s));
+  ReadBack R;
+  R.add(err.as<int32_t>());
+  int64_t bad = 0;
+  MSP_HIP_TRY(read_back(R, &bad, s));
   return bad ? MSP_ERR_INVALID : MSP_OK;
 }
 

@@ -510,16 +510,16 @@ __global__ void __launch_bounds__(kPlastBlock) vacancy_k(const double* __restric
   out[j] = (int32_t)floor(z[g]) - bound[g];
 }
 
-// New synapses (appended by the caller) bind their elements.
-__global__ void __launch_bounds__(kPlastBlock) bind_k(const int32_t* __restrict__ src,
-                                                     const int32_t* __restrict__ tgt,
-                                                     const uint8_t* __restrict__ type,
-                                                     DevCount cnt, int64_t n, int32_t* bound,
-                                                     int32_t* err) {
-  const int64_t c = cnt.get();
+// New synapses appended at `to`; they bind their elements.
+__global__ void __launch_bounds__(kPlastBlock) bind_k(const int32_t* src, const int32_t* tgt,
+                                                     const uint8_t* type, int64_t c, SynList to,
+                                                     int64_t n, int32_t* bound, int32_t* err) {
   for (int64_t q = gtid(); q < c; q += gstride()) {
     const int32_t i = src[q], g = tgt[q];
     const uint8_t ty = type[q];
+    to.src[q] = i;
+    to.tgt[q] = g;
+    to.type[q] = ty;
     if (i < 0 || i >= n || g < 0 || g >= n || ty > 1) {
       atomicOr(err, 1);
       continue;

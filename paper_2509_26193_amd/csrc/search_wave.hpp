@@ -173,8 +173,8 @@ struct BatchDev {
   int32_t nsims;
   const int64_t* nbase;         // [nsims + 1] flat neuron offsets
   int64_t* ea;                  // [total + 1] flat exclusive scan of vac_axon
-  int32_t* p0;                  // [total + 1] flat scan: excitatory sources, Morton order
-  int32_t* p1;                  // [total + 1] flat scan: inhibitory sources, Morton order
+  int64_t* sources;             // [total + 1] flat scan, Morton order: excitatory sources in
+                                // the low word, inhibitory ones in the high word
   uint8_t* src_type;            // [total] type of the source at flat position g, 2: none
   int32_t* tile_base;           // [nsims + 1]
   int32_t* part_base;           // [nsims + 1] parts of tiles before each

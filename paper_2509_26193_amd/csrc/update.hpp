@@ -20,7 +20,7 @@ struct CommitWs {
   int32_t* src_of;
   int64_t* key;
   uint64_t* prio;
-  int32_t* cnt;                 // [2n] requests per group, then the accepted ones
+  int32_t* cnt;                 // [2n] requests per group, then the accepted ones; the flags
   int32_t* within;              // [cap_S] each request's place in its group
   GroupThr* thr;                // [2n] each group's decision
   int32_t* seg_off;             // [2n + 1]
@@ -37,14 +37,14 @@ inline CommitWs commit_ws(void* base, int64_t n, int64_t cap_S, size_t* bytes) {
   w.src_of = c.take<int32_t>(cap_S);
   w.key = c.take<int64_t>(cap_S);
   w.prio = c.take<uint64_t>(cap_S);
-  w.cnt = c.take<int32_t>(2 * n);
+  w.cnt = c.take<int32_t>(2 * n + 1);
+  w.flags = w.cnt ? w.cnt + 2 * n : nullptr;
   w.within = c.take<int32_t>(cap_S);
   w.thr = c.take<GroupThr>(2 * n);
   w.seg_off = c.take<int32_t>(2 * n + 1);
   w.seg = c.take<int32_t>(cap_S);
   w.acc = c.take<uint8_t>(cap_S);
   w.dst = c.take<int64_t>(cap_S + 1);
-  w.flags = c.take<int32_t>(1);
   w.scan_ws = c.take_bytes(std::max(scan_tmp_bytes<int32_t>(2 * n),
                                     scan_tmp_bytes<int64_t>(cap_S + 1)));
   *bytes = c.off;
@@ -63,9 +63,8 @@ inline hipError_t enqueue_commit(const CommitWs& w, const int32_t* target,
                                  int32_t* syn_tgt, uint8_t* syn_type, int64_t syn_capacity,
                                  int64_t* n_formed, uint8_t* accepted_out, hipStream_t s) {
   const unsigned gs = grid_cap(S.v, kCommitBlock);
-  fill_i32_k<<<grid_for(2 * n, 256), 256, 0, s>>>(w.cnt, 2 * n, 0);
-  fill_i32_k<<<1, 64, 0, s>>>(w.flags, 1, 0);
-  src_of_k<<<grid_for(n, kCommitBlock), kCommitBlock, 0, s>>>(elem_offset, n, S, w.src_of);
+  commit_start_k<<<grid_for(n + 1, kCommitBlock), kCommitBlock, 0, s>>>(elem_offset, n, S,
+                                                                       w.src_of, w.cnt);
   req_key_k<<<gs, kCommitBlock, 0, s>>>(target, elem_offset, w.src_of, neuron_type, S, n, seed,
                                         step, w.key, w.prio, w.cnt, w.within, w.flags);
   hipError_t e = hipGetLastError();
@@ -84,13 +83,9 @@ inline hipError_t enqueue_commit(const CommitWs& w, const int32_t* target,
   e = exclusive_scan<int64_t, uint8_t, AccFlag>(w.acc, w.dst, S.v, AccFlag(), true, s, w.scan_ws,
                                                 S.p);
   if (e != hipSuccess) return e;
-  commit_write_k<<<gs, kCommitBlock, 0, s>>>(w.acc, w.dst, w.key, w.src_of, S, syn_capacity,
-                                             syn_src, syn_tgt, syn_type, accepted_out, w.flags);
-  dec_groups_k<<<gg, kCommitBlock, 0, s>>>(w.cnt, 2 * n, w.dst, S, syn_capacity, w.flags,
-                                           vac_exc, vac_inh);
-  dec_sources_k<<<grid_cap(n, kCommitBlock), kCommitBlock, 0, s>>>(
-      elem_offset, n, w.acc, w.dst, S, syn_capacity, w.flags, vac_axon);
-  formed_k<<<1, 64, 0, s>>>(w.dst, S, syn_capacity, w.flags, n_formed);
+  commit_end_k<<<std::max(gs, gg), kCommitBlock, 0, s>>>(
+      w.acc, w.dst, w.key, w.src_of, w.cnt, elem_offset, n, S, syn_capacity, syn_src, syn_tgt,
+      syn_type, accepted_out, vac_exc, vac_inh, vac_axon, n_formed, w.flags);
   return hipGetLastError();
 }
 
