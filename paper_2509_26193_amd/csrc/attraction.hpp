@@ -358,26 +358,32 @@ __global__ void __launch_bounds__(kCross2Block) push_cross_k(
     const int32_t* __restrict__ cross, const int32_t* __restrict__ kids_of, int count,
     const NodeRec* __restrict__ r0, const NodeRec* __restrict__ r1, const double* __restrict__ G,
     double* H, int64_t N) {
+  __shared__ uint32_t depths;
   const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  CrossNode next(cross, kids_of, count, c, 0);
-  for (int d = 0; d <= kMaxDepth; ++d) {
+  uint32_t left = cross_depths(cross, count, c, &depths);
+  if (left == 0) return;
+  CrossNode next(cross, kids_of, count, c, __ffs((int)left) - 1);
+  while (left) {
     const CrossNode at = next;
-    if (d < kMaxDepth) next = CrossNode(cross, kids_of, count, c, d + 1);
-    if (!__syncthreads_or(at.x >= 0)) continue;
+    left &= left - 1;
+    if (left) next = CrossNode(cross, kids_of, count, c, __ffs((int)left) - 1);
     if (at.x >= 0) push_node(at.x, at.kids, r0, r1, G, H, N);
+    __syncthreads();
   }
 }
 
+template <bool ONE>
 __global__ void __launch_bounds__(512) push_chunk_k(Chunks C, const NodeRec* __restrict__ r0,
                                                    const NodeRec* __restrict__ r1,
                                                    const double* __restrict__ G, double* H,
                                                    int64_t N) {
-  __shared__ int32_t skips[kSkipRoom];
+  constexpr int kRoom = ONE ? kSkipRoomOne : kSkipRoom;
+  __shared__ int32_t skips[kRoom];
   const int32_t x0 = C.x[blockIdx.x], x1 = C.x[blockIdx.x + 1];
-  for (int32_t x = x0 + (int)threadIdx.x; x < x1 && x - x0 < kSkipRoom; x += blockDim.x)
+  for (int32_t x = x0 + (int)threadIdx.x; x < x1 && x - x0 < kRoom; x += blockDim.x)
     skips[x - x0] = C.skip[x];
   __syncthreads();
-  const ChunkSkips S{skips, C.skip, x0};
+  const ChunkSkips S{skips, C.skip, x0, kRoom};
   const int32_t* off = C.off + (int64_t)blockIdx.x * (kDepths + 1);
   const int32_t* nodes = C.nodes + x0;
   for (int k = kDepths; k >= 1; --k) {

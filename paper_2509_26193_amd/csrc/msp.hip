@@ -284,8 +284,9 @@ hipError_t enqueue_refresh(msp_octree_s* t, const int32_t* vac_exc, const int32_
   if (t->both)
     pair_counts_k<<<grid_for(t->n, kRefreshBlock), kRefreshBlock, 0, s>>>(vac_exc, vac_inh, t->n,
                                                                           t->both);
-  (t->both ? refresh_chunk_k<true> : refresh_chunk_k<false>)
-      <<<(unsigned)C.nch, C.nch == 1 ? 1024 : 512, 0, s>>>(
+  (t->both       ? refresh_chunk_k<true, false>
+   : C.nch == 1 ? refresh_chunk_k<false, true>
+                : refresh_chunk_k<false, false>)<<<(unsigned)C.nch, C.nch == 1 ? 1024 : 512, 0, s>>>(
           t->n, C, t->rec[0], t->rec[1], t->leaf_at, t->order, t->pos, vac_exc, vac_inh, t->both,
           t->vs[0], t->vs[1], t->err);
   if (C.nch > 1)
@@ -460,7 +461,7 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
     if (t->nsup > 1)
       fill_i32_k<<<grid_for((int64_t)t->nsup * kDepths, 256), 256, 0, s>>>(
           t->cross2, (int64_t)t->nsup * kDepths, -1);
-    chunks_k<<<(unsigned)t->nch, kBuildBlock, 0, s>>>(t->depth, t->skip, basep, n, t->chunk_log,
+    chunks_k<<<(unsigned)t->nch, t->nch == 1 ? kChunksOne : kBuildBlock, 0, s>>>(t->depth, t->skip, basep, n, t->chunk_log,
                                                       t->nch, t->nsup, t->chunk_x, t->chunk_off,
                                                       t->chunk_nodes, t->cross, t->cross2,
                                                       t->cross_kids, t->cross2_kids);
@@ -1182,7 +1183,8 @@ msp_status attraction(msp_octree t, const uint8_t* neuron_type, const int32_t* v
   if (C.nch > 1)
     push_cross_k<<<(unsigned)C.nsup, kSuper, 0, s>>>(C.cross, C.cross_kids, C.nch, t->rec[0],
                                                      t->rec[1], O.G, H, N);
-  push_chunk_k<<<(unsigned)C.nch, 512, 0, s>>>(C, t->rec[0], t->rec[1], O.G, H, N);
+  (C.nch == 1 ? push_chunk_k<true> : push_chunk_k<false>)<<<(unsigned)C.nch, 512, 0, s>>>(
+      C, t->rec[0], t->rec[1], O.G, H, N);
   push_leaves_k<<<grid_for(n, 256), 256, 0, s>>>(t->leaf_of, t->nbeg, t->nend, t->order,
                                                  t->rec[0], t->rec[1], t->vs[0], t->vs[1], H, N, n,
                                                  O.dpos, dpos);

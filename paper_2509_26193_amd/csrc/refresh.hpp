@@ -69,16 +69,18 @@ __device__ __forceinline__ void refresh_node(int32_t x, uint32_t meta, const int
   r1[x] = f;
 }
 
-// The subtree ends of a chunk's nodes in LDS (those past kSkipRoom stay in global memory),
-// and the children of its inner nodes found through them.
-constexpr int kSkipRoom = 8192;
+// The subtree ends of a chunk's nodes in LDS (those past `room` stay in global memory), and the
+// children of its inner nodes found through them.
+constexpr int kSkipRoomOne = 8192;         // trees of one chunk (see kChunkLogOne)
+constexpr int kSkipRoom = 2048;            // (with 32 KB of LDS a block of 512 threads leaves
+                                           // a CU's wavefronts short)
 
 struct ChunkSkips {
   const int32_t* lds;
   const int32_t* skip;
-  int32_t x0;
+  int32_t x0, room;
   __device__ __forceinline__ int32_t operator()(int32_t x) const {
-    return x - x0 < kSkipRoom ? lds[x - x0] : skip[x];
+    return x - x0 < room ? lds[x - x0] : skip[x];
   }
   __device__ __forceinline__ void kids(int32_t x, int32_t end, int32_t (&k)[8]) const {
     int32_t c = x + 1;
@@ -136,47 +138,71 @@ __global__ void pair_counts_k(const int32_t* __restrict__ vexc, const int32_t* _
 // leaf is done by its first member's thread, its members in sorted order, which is id order
 // within the finest cell), then its inner nodes by depth, deepest first. Bound by the
 // gathers (a 128-byte line for 8 bytes per neuron) and the records read and written; small
-// trees by the chain of children (8 dependent reads per depth). The whole refresh, against a
-// kernel for the leaves and one per depth: 8M neurons 0.95 ms (1.39), 2M 0.31 (0.37), 4 096
-// 50 us in one launch (41 us in nine, and 22 us for the lists of the depths).
-template <bool PAIRS>
-__global__ void __launch_bounds__(1024) refresh_chunk_k(
+// trees by the chain over the depths. The whole refresh, against a kernel for the leaves and
+// one per depth: 8M neurons 0.88 ms (1.39), 2M 0.30 (0.37), 4 096 47 us in one launch (41 us
+// in nine, and 22 us for the lists of the depths). A thread's neurons, and its first node of
+// the next depth, are loaded together and ahead: 8M 0.81 -> 0.75 ms for the chunks.
+template <bool PAIRS, bool ONE>
+__global__ void __launch_bounds__(ONE ? 1024 : 512) refresh_chunk_k(
     int64_t n, Chunks C, NodeRec* r0, NodeRec* r1, const int32_t* __restrict__ leaf_at,
     const int32_t* __restrict__ order, const double* __restrict__ pos,
     const int32_t* __restrict__ vexc, const int32_t* __restrict__ vinh,
     const int2* __restrict__ both, int32_t* __restrict__ vs0, int32_t* __restrict__ vs1,
     int32_t* err) {
-  __shared__ int32_t skips[kSkipRoom];
-  const int c = (int)blockIdx.x;
+  constexpr int kRoom = ONE ? kSkipRoomOne : kSkipRoom;
+  constexpr int kAtOnce = ONE ? 4 : 2;             // a thread's neurons, loaded together
+  __shared__ int32_t skips[kRoom];
+  __shared__ int32_t off[kDepths + 1];
+  const int c = (int)blockIdx.x, t = (int)threadIdx.x, threads = (int)blockDim.x;
   const int32_t x0 = C.x[c], x1 = C.x[c + 1];
-  for (int32_t x = x0 + (int)threadIdx.x; x < x1 && x - x0 < kSkipRoom; x += blockDim.x)
-    skips[x - x0] = C.skip[x];
-  const ChunkSkips S{skips, C.skip, x0};
-  auto counts = [&](int32_t id) -> int2 {
-    const int2 v = PAIRS ? both[id] : make_int2(vexc[id], vinh[id]);
+  if (t <= kDepths) off[t] = C.off[(int64_t)c * (kDepths + 1) + t];
+  for (int32_t x = x0 + t; x < x1 && x - x0 < kRoom; x += threads) skips[x - x0] = C.skip[x];
+  const ChunkSkips S{skips, C.skip, x0, kRoom};
+  auto load = [&](int32_t id) -> int2 {
+    return PAIRS ? both[id] : make_int2(vexc[id], vinh[id]);
+  };
+  auto checked = [&](int2 v) -> int2 {
     if (v.x < 0 || v.y < 0) atomicOr(err, kErrNegative);
     return make_int2(v.x < 0 ? 0 : v.x, v.y < 0 ? 0 : v.y);
   };
   const int64_t p0 = (int64_t)c << C.log;
   const int64_t p1 = p0 + ((int64_t)1 << C.log) < n ? p0 + ((int64_t)1 << C.log) : n;
-  for (int64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const int32_t x = leaf_at[p];
-    const bool first = p == 0 || leaf_at[p - 1] != x;
-    if (first && (p + 1 >= n || leaf_at[p + 1] != x)) {
-      const int2 v = counts(order[p]);
-      r0[x].v = v.x;
-      r1[x].v = v.y;
-    } else if (first) {
+  for (int64_t b = p0 + t; b < p1; b += kAtOnce * threads) {
+    int32_t at[kAtOnce], before[kAtOnce], after[kAtOnce], id[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int64_t p = b + u * threads < p1 ? b + u * threads : b;
+      at[u] = leaf_at[p];
+      before[u] = p > 0 ? leaf_at[p - 1] : -1;
+      after[u] = p + 1 < n ? leaf_at[p + 1] : -1;
+      id[u] = order[p];
+    }
+    int2 v[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) v[u] = load(id[u]);
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) asm volatile("" : "+v"(v[u].x), "+v"(v[u].y));
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int64_t p = b + u * threads;
+      const int32_t x = at[u];
+      if (p >= p1 || before[u] == x) continue;
+      if (after[u] != x) {
+        const int2 w = checked(v[u]);
+        r0[x].v = w.x;
+        r1[x].v = w.y;
+        continue;
+      }
       Acc3 A, B;
       for (int64_t q = p; q < n && leaf_at[q] == x; ++q) {
-        const int32_t id = order[q];
-        const int2 v = counts(id);
-        const double px = pos[3 * (int64_t)id], py = pos[3 * (int64_t)id + 1],
-                     pz = pos[3 * (int64_t)id + 2];
-        A.add(v.x, px, py, pz);
-        B.add(v.y, px, py, pz);
-        vs0[q] = v.x;
-        vs1[q] = v.y;
+        const int32_t i = order[q];
+        const int2 w = checked(load(i));
+        const double px = pos[3 * (int64_t)i], py = pos[3 * (int64_t)i + 1],
+                     pz = pos[3 * (int64_t)i + 2];
+        A.add(w.x, px, py, pz);
+        B.add(w.y, px, py, pz);
+        vs0[q] = w.x;
+        vs1[q] = w.y;
       }
       NodeRec e, f;
       e.meta = f.meta = r0[x].meta;
@@ -186,41 +212,72 @@ __global__ void __launch_bounds__(1024) refresh_chunk_k(
       r1[x] = f;
     }
   }
-  const int32_t* off = C.off + (int64_t)c * (kDepths + 1);
+  // the lists of the depths follow one another: a thread's first node of the next depth is
+  // loaded ahead of the barrier
   const int32_t* nodes = C.nodes + x0;
-  int32_t lo = 0;
+  __syncthreads();
+  const int32_t all = off[kDepths];
+  int32_t lo = 0, next = t < all ? nodes[t] : 0;
   for (int k = 1; k <= kDepths; ++k) {             // depth kMaxDepth + 1 - k
     const int32_t hi = off[k];
     if (hi == lo) continue;                        // (uniform over the block)
-    __syncthreads();
-    for (int32_t q = lo + (int)threadIdx.x; q < hi; q += blockDim.x) {
-      const int32_t x = nodes[q], end = S(x);
+    int32_t x = next;
+    next = hi + t < all ? nodes[hi + t] : 0;
+    for (int32_t q = lo + t; q < hi; q += threads) {
+      if (q != lo + t) x = nodes[q];
+      const int32_t end = S(x);
       int32_t kids[8];
       S.kids(x, end, kids);
       refresh_node(x, (uint32_t)end | ((uint32_t)(kMaxDepth + 1 - k) << kSkipBits), kids, r0, r1,
                    err);
     }
     lo = hi;
+    __syncthreads();
   }
+}
+
+// The depths (bit d: depth d) at which a thread of the block has a crossing node.
+__device__ __forceinline__ uint32_t cross_depths(const int32_t* cross, int count, int c,
+                                                 uint32_t* lds) {
+  if (threadIdx.x == 0) *lds = 0;
+  uint32_t mine = 0;
+#pragma unroll
+  for (int d = 0; d < kDepths; ++d)
+    if (c < count && cross[(int64_t)d * count + c] >= 0) mine |= 1u << d;
+  __syncthreads();
+  if (mine) atomicOr(lds, mine);
+  __syncthreads();
+  return *lds;
 }
 
 // One block per run of kSuper chunks, a chunk per thread: the nodes that cross chunk ends
 // inside the run, by depth; with cross2 (one block, a run per thread) those that cross the
 // ends of runs. Bound by the chain over the depths (a barrier and the children's records
-// each), so the next depth's node and children are loaded ahead of the barrier.
+// each), so only depths with such nodes are visited, and the next one's nodes and children
+// are loaded ahead of the barrier (20 011 neurons: 28 -> 25 us).
 constexpr int kCross2Block = 512;          // runs of a tree of kMaxNodes neurons
 
 __global__ void __launch_bounds__(kCross2Block) refresh_cross_k(
     const int32_t* __restrict__ cross, const int32_t* __restrict__ kids_of,
     const int32_t* __restrict__ skip, int count, NodeRec* r0, NodeRec* r1, int32_t* err) {
+  __shared__ uint32_t depths;
   const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  CrossNode next(cross, kids_of, count, c, kMaxDepth);
-  for (int d = kMaxDepth; d >= 0; --d) {
+  uint32_t left = cross_depths(cross, count, c, &depths);
+  if (left == 0) return;
+  int d = 31 - __clz(left);
+  CrossNode next(cross, kids_of, count, c, d);
+  while (left) {
     const CrossNode at = next;
-    if (d > 0) next = CrossNode(cross, kids_of, count, c, d - 1);
-    if (!__syncthreads_or(at.x >= 0)) continue;
-    if (at.x < 0) continue;
-    refresh_node(at.x, (uint32_t)skip[at.x] | ((uint32_t)d << kSkipBits), at.kids, r0, r1, err);
+    const int here = d;
+    left &= ~(1u << d);
+    if (left) {
+      d = 31 - __clz(left);
+      next = CrossNode(cross, kids_of, count, c, d);
+    }
+    if (at.x >= 0)
+      refresh_node(at.x, (uint32_t)skip[at.x] | ((uint32_t)here << kSkipBits), at.kids, r0, r1,
+                   err);
+    __syncthreads();
   }
 }
 
