@@ -76,8 +76,9 @@ typedef struct msp_octree_s* msp_octree;
  *   out       (host) receives the handle. The library owns every node array.
  * Errors: MSP_ERR_INVALID for n < 1 or n > MSP_MAX_NEURONS, a non-finite box corner, an
  * edge outside that range, leaf_size != 1, null pointers; MSP_ERR_OOM. A non-finite
- * position sets the device error flag. The build waits on `s` twice (to size the node
- * arrays and the per-depth lists); its last kernels may still run when it returns.
+ * position sets the device error flag. The build waits on `s` once, to size the node
+ * arrays (twice where more than 24 neurons share the leading bits of their cells and are
+ * out of order in the rest); its last kernels may still run when it returns.
  */
 msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3],
                             double box_edge, int32_t leaf_size, hipStream_t s,
@@ -113,7 +114,8 @@ msp_status msp_update_vacant_counts(msp_octree t, const int32_t* vac_dend_exc,
  * float64 in the walk's depth-first order; a call with fewer than about 2^23 sources cuts
  * the walk into up to 64 consecutive pre-order ranges, searched in parallel, whose sums
  * are then added in order, so Z's last bits depend on the cuts (the draw follows the
- * same sums; the cuts follow from the octree and the sources alone). Errors: MSP_ERR_CAPACITY if S = sum(vac_axon) > capacity_S:
+ * same sums; the cuts follow from the octree and the sources alone). Errors:
+ * MSP_ERR_CAPACITY if S = sum(vac_axon) > capacity_S:
  * then only elem_offset_out is written (elem_offset_out[n] = S sizes the buffer);
  * MSP_ERR_INVALID for sigma <= 0, theta < 0, a negative vac_axon or a type > 1
  * (the last two found on the device before the search: target_out is not written).
@@ -302,7 +304,8 @@ msp_status msp_attraction_bwd(msp_octree t, const uint8_t* neuron_type, const in
  *   ties broken by (i, j); the rest are declined.
  *   vac_axon, vac_exc, vac_inh [n] int32, in/out: decremented by the synapses formed.
  *   syn_src, syn_tgt [syn_capacity] int32, syn_type [syn_capacity] uint8: the formed
- *   synapses, ordered by (source, element). n_formed: device int64 scalar.
+ *   synapses, ordered by (source, element). n_formed: device int64 scalar (or page-locked
+ *   host memory that the device reaches).
  *   accepted_out [S] uint8 (nullable in msp_commit_synapses_ex): 1 if the request in
  *   that slot was accepted.
  * Errors: MSP_ERR_CAPACITY if more than syn_capacity synapses would form, and
