@@ -81,8 +81,8 @@ search_sweep_k(BatchDev, SweepOut) {
 // threads (element j to share j % kDrawSplit, one share's blocks after the other's): such a
 // launch takes as long as its longest chains of record loads (4 096 neurons with up to 2
 // elements: 88 -> 49 us, 60 001: 144 -> 86, 1 M clustered with up to 4: 1.11 -> 1.02 ms). Larger
-// ones are bound by the records that miss the L2 (8M neurons: 185 M lines of 128 bytes, 6.6
-// TB/s), and the tile's data would be read twice (3.55 -> 3.93 ms, 64 simulations 1.52 -> 1.65).
+// ones are bound by the lines that miss the L2 (8M neurons: 20 GB fetched, 5.8 TB/s), and the
+// tile's data would be read twice (3.55 -> 3.93 ms, 64 simulations 1.52 -> 1.65).
 // In both, groups of kDrawGroup neighbouring blocks share a die's L2 (8M neurons: 3.55 -> 3.49
 // ms, 64 simulations 1.52 -> 1.44; 128 blocks: the same, but 1 M clustered neurons 1.09 -> 1.21).
 constexpr int kDrawSplit = 2;
