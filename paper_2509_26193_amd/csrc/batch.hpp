@@ -297,13 +297,24 @@ __host__ __device__ inline int parts_log(int64_t ts, int force) {
   return p;
 }
 
+// log2 of the checkpoint slots of each part of a tile with 2^p parts, after `cut` halvings:
+// twice a part's share of the tile's `ck_slots`, at least kMinSlots of them, never under two.
+__host__ __device__ inline int slots_log(int p, int ck_slots, int cut) {
+  if (ck_slots == 0) return 0;
+  int want = (2 * ck_slots) >> p;
+  want = want > ck_slots ? ck_slots : want < kMinSlots ? kMinSlots : want;
+  int l = 0;
+  while (want >> (l + 1)) ++l;
+  return l - cut < 1 ? 1 : l - cut;
+}
+
 // Tiles per simulation: excitatory sources padded to a multiple of 64, then
 // inhibitory ones, so no tile mixes simulations or types; their parts, the parts' units
 // (a launch with more than kUnitsMax parts groups 2^g consecutive parts of a tile into a
-// unit, or as many as its tile has) and the parts' checkpoint slots: twice a tile's share of
-// `ck_slots`, at least kMinSlots, halved until all fit into `ck_cap` slots (at least two
-// each). One block; a thread takes every kTilesBlock-th simulation. Also writes the tile
-// and unit counts and the number of sources (the length of the Hilbert sort).
+// unit, or as many as its tile has) and the parts' checkpoint slots (slots_log), halved until
+// all fit into `ck_cap` slots; two for every part always do (see search_size_in). One block; a
+// thread takes every kTilesBlock-th simulation. Also writes the tile and unit counts and the
+// number of sources (the length of the Hilbert sort).
 constexpr int kTilesBlock = kScanBlock;
 
 __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* tile_count,
@@ -330,13 +341,6 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
   int g = 0;
   while (g < kPartLogMax && (parts >> g) > kUnitsMax) ++g;
   if (force >= 0 || B.nsims == 1) g = 0;
-  auto slots = [&](int p, int cut) -> int {       // log2 of the slots per part
-    if (ck_slots == 0) return 0;
-    int want = (2 * ck_slots) >> p;
-    want = want > ck_slots ? ck_slots : want < kMinSlots ? kMinSlots : want;
-    const int l = 31 - __clz(want) - cut;
-    return l < 1 ? 1 : l;
-  };
   int cut = 0;
   for (; cut < 8; ++cut) {
     int64_t sum = 0;
@@ -344,7 +348,7 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
       const int64_t ts = tiles(s0 + t);
       const int p = parts_log(ts, force);
       int64_t tot;
-      (void)block_exclusive_scan<int64_t>((ts << p) << slots(p, cut), lds, &tot);
+      (void)block_exclusive_scan<int64_t>((ts << p) << slots_log(p, ck_slots, cut), lds, &tot);
       sum += tot;
     }
     if (sum <= ck_cap) break;
@@ -355,7 +359,7 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
     const int64_t ts = tiles(s);
     const int p = parts_log(ts, force);
     const int u = p > g ? p - g : 0;
-    const int l = slots(p, cut);
+    const int l = slots_log(p, ck_slots, cut);
     int64_t tt, tp, tu, tl;
     const int64_t et = block_exclusive_scan<int64_t>(ts, lds, &tt);
     const int64_t ep = block_exclusive_scan<int64_t>(ts << p, lds, &tp);
@@ -726,6 +730,10 @@ struct SearchSize {
   bool counts;
 };
 
+// Checkpoint bytes per slot: the wave position and, per lane, the running sum and the
+// mask end.
+constexpr size_t kCkptSlotBytes = sizeof(int32_t) + kWave * (sizeof(double) + sizeof(int32_t));
+
 struct SearchScratch {
   SearchSize q;
   BatchDev B;
@@ -755,6 +763,24 @@ inline int64_t max_parts_for(int64_t total_n, int nsims, int force = -1) {
                     : std::min(mt << kPartLogMax, two + eight + fine);
 }
 
+// The checkpoints of a search on a device of `mem` bytes: kCkptMax aimed at per tile if that
+// many slots per tile fit in an eighth of it, else kCkptMin. More slots mean shorter re-walks
+// in the draw kernel; the targets do not depend on the choice. Slots in all: as many per tile,
+// and as many more as that eighth holds up to twice that (the forced parts' share, where
+// parts are forced) or kMinSlots for each part of a launch with few tiles; and in any case
+// two for every part there can be, which b_tiles_k counts on. (An ensemble of 9 000
+// simulations of 4 096 neurons needs more for that than the eighth of 288 GB holds.)
+inline SearchSize search_size_in(size_t mem, int64_t total_n, int nsims, int force, bool counts) {
+  const int64_t mt = max_tiles_for(total_n, nsims);
+  const double budget = (double)(mem / 8);
+  const int slots = (double)mt * kCkptMax * (double)kCkptSlotBytes <= budget ? kCkptMax : kCkptMin;
+  const int64_t fine = std::min(mt << kPartLogMax, (int64_t)nsims * kPartsFine) * kMinSlots;
+  const int64_t want = force >= 0 ? (mt << force) * slots : std::max(2 * mt * slots, fine);
+  const int64_t fit = (int64_t)(budget / (double)kCkptSlotBytes);
+  const int64_t least = std::max(mt * slots, 2 * max_parts_for(total_n, nsims, force));
+  return SearchSize{total_n, nsims, slots, std::max(least, std::min(want, fit)), force, counts};
+}
+
 // Sweep units of all tiles: the parts, in a batch grouped to about kUnitsMax.
 inline int64_t max_units_for(int64_t total_n, int nsims, int force = -1) {
   const int64_t mp = max_parts_for(total_n, nsims, force);
@@ -766,10 +792,6 @@ struct ScratchSizes {
   size_t ea, p, base, slot_base, log, status, work, Z, v, nck, cuts, ckx, ckP, ckme, counters,
       scan, srct, hkey, hval, hsort, total;
 };
-
-// Checkpoint bytes per slot: the wave position and, per lane, the running sum and the
-// mask end.
-constexpr size_t kCkptSlotBytes = sizeof(int32_t) + kWave * (sizeof(double) + sizeof(int32_t));
 
 inline ScratchSizes scratch_sizes(const SearchSize& q) {
   ScratchSizes z;

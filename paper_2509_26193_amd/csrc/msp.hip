@@ -165,11 +165,7 @@ hipError_t sweep_blocks_for(int device, bool diag, int64_t max_units, double fra
                          kWaveBlock, max_units, frac, blocks_out);
 }
 
-// The checkpoints of a search: kCkptMax aimed at per tile if that many slots per tile fit
-// in an eighth of the device's memory, else kCkptMin. More slots mean shorter re-walks in
-// the draw kernel; the targets do not depend on the choice. Slots in all: as many per
-// tile, and as many more as that eighth holds up to twice that (the forced parts' share,
-// where parts are forced) or kMinSlots for each part of a launch with few tiles.
+// The checkpoints of a search on `device` (see search_size_in).
 hipError_t search_size(int device, int64_t total_n, int nsims, int force, bool counts,
                        SearchSize* out) {
   static size_t mem[64] = {};
@@ -180,14 +176,7 @@ hipError_t search_size(int device, int64_t total_n, int nsims, int force, bool c
     if (e != hipSuccess) return e;
     mem[device] = p.totalGlobalMem;
   }
-  const int64_t mt = max_tiles_for(total_n, nsims);
-  const double budget = (double)(mem[device] / 8);
-  const int slots = (double)mt * kCkptMax * (double)kCkptSlotBytes <= budget ? kCkptMax : kCkptMin;
-  const int64_t fine = std::min(mt << kPartLogMax, (int64_t)nsims * kPartsFine) * kMinSlots;
-  const int64_t want = force >= 0 ? (mt << force) * slots : std::max(2 * mt * slots, fine);
-  const int64_t fit = (int64_t)(budget / (double)kCkptSlotBytes);
-  *out = SearchSize{total_n, nsims, slots, std::max(mt * slots, std::min(want, fit)), force,
-                    counts};
+  *out = search_size_in(mem[device], total_n, nsims, force, counts);
   return hipSuccess;
 }
 
