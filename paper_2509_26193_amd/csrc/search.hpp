@@ -29,6 +29,7 @@ struct SearchArgs {
   const int32_t* vs[2];          // per-type counts in sorted order (bucket members)
   const double* pos;
   const int32_t* order;
+  const uint64_t* keys;          // sorted Morton keys
   const int32_t* nbeg;
   const int32_t* nend;
   const int32_t* leaf_of;
@@ -138,8 +139,9 @@ __device__ __forceinline__ double kernel_weight_vd(bool keep, double vd, double 
 // product of a fused multiply-add (one vector instruction fewer per entry; the sweep at 8M
 // neurons: 33.2 -> 32.5 ms). 2^-y is exact where it is a normal double, so the sum is at
 // least as near to the exact one as with the product rounded first; below 2^-1022 it is
-// rounded to a multiple of 2^-1074, which matters only to sums below kTinyZ: those are
-// added up from the products (see draw_slot). The walk's step needs no test of y here: kMaxY
+// rounded to a multiple of 2^-1074 (to 0 where y is within 2^-25 below 1075 and the float32
+// mantissa is 1/2), which matters only to sums below kTinyZ, 0 included: those are
+// added up from the products (see tiny_sum). The walk's step needs no test of y here: kMaxY
 // is the last double below 1075, and from there on the mantissa is at most 1 and the exponent
 // at most -1075, which rounds to 0 (a tie, to even) by itself (the sweep at 8M
 // neurons 32.6 -> 31.7 ms, 64 simulations 9.48 -> 9.21).
@@ -313,6 +315,34 @@ struct KeptEntries {
   int stride;
 };
 
+// SelectPass over the n kept entries.
+__device__ __forceinline__ void choose_kept(const KeptEntries& K, int n, double T, int32_t& id,
+                                            bool& neuron) {
+  double P = 0.0;
+  int32_t chosen = -1, last = -1;
+  bool chosen_neuron = false, last_neuron = false;
+  for (int e = 0; e < n; ++e) {
+    const double w = K.w[e * K.stride];
+    const uint32_t r = K.id[e * K.stride];
+    const int32_t eid = (int32_t)(r & ~kKeptNeuron);
+    const bool en = (r & kKeptNeuron) != 0;
+    if (w > 0.0) {
+      last = eid;
+      last_neuron = en;
+    }
+    P = P + w;
+    if (P > T) {
+      chosen = eid;
+      chosen_neuron = en;
+      break;
+    }
+  }
+  id = chosen >= 0 ? chosen : last;
+  neuron = chosen >= 0 ? chosen_neuron : last_neuron;
+}
+
+// POSITIVE: entries of weight 0 are not kept (they change no sum and are never chosen).
+template <bool POSITIVE>
 struct SumKeepPass {
   double k2;
   KeptEntries K;
@@ -321,6 +351,7 @@ struct SumKeepPass {
   __device__ __forceinline__ bool operator()(int32_t id, bool neuron, int32_t v, double d2) {
     const double w = kernel_weight(v, d2, k2);
     Z = Z + w;
+    if (POSITIVE && !(w > 0.0)) return false;
     if (n < kRestartKeep) {
       K.w[n * K.stride] = w;
       K.id[n * K.stride] = (uint32_t)id | (neuron ? kKeptNeuron : 0u);
@@ -349,34 +380,13 @@ __device__ int32_t restart_search(const SearchArgs& A, const NodeRec* R, const i
     int32_t id;
     bool neuron;
     if (keep) {
-      SumKeepPass s{A.k2, *keep};
+      SumKeepPass<false> s{A.k2, *keep};
       expand<COUNT>(A, R, vs, S, i, li, xi, yi, zi, s, cnt);
       *levels_out = level + 1;
       if (!(s.Z > 0.0)) return -1;
       const double T = draw_u(A.seed, i, j, A.step, level) * s.Z;
       if (s.n <= kRestartKeep) {
-        // SelectPass over the kept entries
-        double P = 0.0;
-        int32_t chosen = -1, last = -1;
-        bool chosen_neuron = false, last_neuron = false;
-        for (int e = 0; e < s.n; ++e) {
-          const double w = keep->w[e * keep->stride];
-          const uint32_t r = keep->id[e * keep->stride];
-          const int32_t eid = (int32_t)(r & ~kKeptNeuron);
-          const bool en = (r & kKeptNeuron) != 0;
-          if (w > 0.0) {
-            last = eid;
-            last_neuron = en;
-          }
-          P = P + w;
-          if (P > T) {
-            chosen = eid;
-            chosen_neuron = en;
-            break;
-          }
-        }
-        id = chosen >= 0 ? chosen : last;
-        neuron = chosen >= 0 ? chosen_neuron : last_neuron;
+        choose_kept(*keep, s.n, T, id, neuron);
       } else {
         SelectPass<false> p{A.k2, T};
         expand<false>(A, R, vs, S, i, li, xi, yi, zi, p, none);

@@ -25,6 +25,7 @@
 // (not from the root), then restart levels (a drawn cell) run per thread.
 #pragma once
 
+#include "build.hpp"
 #include "search.hpp"
 
 namespace msp {
@@ -209,6 +210,7 @@ __device__ __forceinline__ SearchArgs args_of(const SimDesc* sims, int s, const 
   A.vs[1] = d->vs[1];
   A.pos = d->pos;
   A.order = d->order;
+  A.keys = d->keys;
   A.nbeg = d->nbeg;
   A.nend = d->nend;
   A.leaf_of = d->leaf_of;
@@ -626,6 +628,75 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
   }
 }
 
+// The source's walk over its level-0 list [1, end) for a sum so small that its entries lie
+// close to where the weights end (kMaxY) or beyond. Where the tree's cells bound the positions
+// and centroids in them (no own-cell test, see own_cell_needed), a cell that would be opened
+// is passed over if all of it lies beyond that distance: its entries weigh exactly 0. The
+// distance is that of the grid cells between the source's and the cell's, so no rounding of
+// the positions matters (the factor covers that of the centroids and products).
+template <class F>
+__device__ void expand_near(const SearchArgs& A, const NodeRec* __restrict__ R, const int32_t* vs,
+                            int32_t end, int32_t i, int32_t li, double xi, double yi, double zi,
+                            F& f) {
+  const double reach2 =
+      kMaxY / A.k2 / edge2_at(A.L2, (uint32_t)kMaxDepth << kSkipBits) * (1.0 + 0x1p-9);
+  const uint64_t mine = A.keys[A.nbeg[li]];
+  const int32_t q[3] = {(int32_t)gather3(mine >> 2), (int32_t)gather3(mine >> 1),
+                        (int32_t)gather3(mine)};
+  int32_t x = 1;
+  while (x < end) {
+    const NodeRec r = R[x];
+    if (r.meta & kLeafBit) {
+      if (r.v != 0 && leaf_entries(A, vs, x, r, i, xi, yi, zi, f)) return;
+      ++x;
+      continue;
+    }
+    int32_t sk = (int32_t)(r.meta & kSkipMask);
+    sk = sk > x ? sk : x + 1;
+    if (r.v == 0) {
+      x = sk;
+      continue;
+    }
+    if (A.own) {
+      if (li >= x && li < sk) {
+        ++x;
+        continue;
+      }
+    }
+    const double d2 = dist2(xi, yi, zi, r.x, r.y, r.z);
+    if (bh_accept(A.L2, A.theta2, d2, r.meta)) {
+      if (f(x, false, r.v, d2)) return;
+      x = sk;
+      continue;
+    }
+    ++x;
+    if (A.own) continue;
+    const uint64_t key = A.keys[A.nbeg[x - 1]];
+    const int up = kMaxDepth - cell_depth(r.meta);
+    double gap2 = 0.0;                        // squared, in grid cells
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int32_t lo = (int32_t)(gather3(key >> (2 - a)) >> up << up), hi = lo + (1 << up);
+      const int32_t g = lo > q[a] ? lo - q[a] - 1 : q[a] - hi;       // (hi: the first after)
+      const double gd = (double)(g > 0 ? g : 0);
+      gap2 += gd * gd;
+    }
+    if (gap2 > reach2) x = sk;
+  }
+}
+
+// A level-0 sum below kTinyZ once more, from the rounded products (see kernel_add), with the
+// entries of weight above 0 kept where there is room.
+__device__ __forceinline__ double tiny_sum(const SearchArgs& A, const NodeRec* __restrict__ R,
+                                           const int32_t* vs, int32_t end, int32_t i, int32_t li,
+                                           double xi, double yi, double zi,
+                                           const KeptEntries& keep, int& n) {
+  SumKeepPass<true> s{A.k2, keep};
+  expand_near(A, R, vs, end, i, li, xi, yi, zi, s);
+  n = s.n;
+  return s.Z;
+}
+
 // The draws and restarts of elements first, first + split, ... of the source in worklist
 // slot `slot` (DEFER: restarts from cells at depth >= W.defer.depth become second-phase
 // requests). The slot's tile has 2^plog parts, the launch's parts u0, u0 + 1, ... with
@@ -657,14 +728,7 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
   for (; q0 < np; ++q0) Z = Z + Zp[q0 * kWave];
   const NodeRec root = R[0];             // Z > 0 implies an inner root
   const int32_t end = (int32_t)(root.meta & kSkipMask);
-  // a sum that small once more, from the rounded products (see kernel_add)
-  const bool tiny = Z > 0.0 && Z < kTinyZ;
-  if (__builtin_expect(tiny, 0)) {
-    SumPass s{A.k2};
-    Count none;
-    expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, s, none);
-    Z = s.Z;
-  }
+  const bool tiny = Z < kTinyZ && root.v > 0 && !(root.meta & kLeafBit);
   const int32_t a = A.vac_axon[i];
   const int64_t off = A.elem_off[i];
   Count c0;
@@ -680,7 +744,23 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
     Count c = c0;
     int32_t tgt = -1;
     int32_t deferred = -1;
-    if (Z > 0.0) {
+    int32_t id = -1;
+    bool neuron = false;
+    if (__builtin_expect(tiny, 0)) {
+      int n = 0;
+      Z = tiny_sum(A, R, vs, end, i, li, xi, yi, zi, *keep, n);
+      if (Z > 0.0) {
+        const double T = draw_u(A.seed, i, j, A.step, 0) * Z;
+        if (n <= kRestartKeep) {
+          choose_kept(*keep, n, T, id, neuron);
+        } else {
+          SelectPass<false> s{A.k2, T};
+          expand_near(A, R, vs, end, i, li, xi, yi, zi, s);
+          id = s.chosen >= 0 ? s.chosen : s.last;
+          neuron = s.chosen >= 0 ? s.chosen_neuron : s.last_neuron;
+        }
+      }
+    } else if (Z > 0.0) {
       const double T = draw_u(A.seed, i, j, A.step, 0) * Z;
       SelectPass<true> p{A.k2, T};
       Count none;
@@ -721,19 +801,13 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
         p = SelectPass<true>{A.k2, T};
         expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, p, none);
       }
-      int32_t id = p.chosen >= 0 ? p.chosen : p.last;
-      bool neuron = p.chosen >= 0 ? p.chosen_neuron : p.last_neuron;
-      if (__builtin_expect(tiny, 0)) {          // (see kernel_add)
-        SelectPass<false> s{A.k2, T};
-        expand_range<false>(A, R, vs, 1, end, i, li, xi, yi, zi, s, none);
-        id = s.chosen >= 0 ? s.chosen : s.last;
-        neuron = s.chosen >= 0 ? s.chosen_neuron : s.last_neuron;
-      }
-      if (id >= 0)
-        tgt = neuron ? id
-                     : restart_search<DIAG, DEFER>(A, R, vs, id, 1, W.defer.depth, i, j, li,
-                                                   xi, yi, zi, &lev, c, &deferred, keep);
+      id = p.chosen >= 0 ? p.chosen : p.last;
+      neuron = p.chosen >= 0 ? p.chosen_neuron : p.last_neuron;
     }
+    if (id >= 0)
+      tgt = neuron ? id
+                   : restart_search<DIAG, DEFER>(A, R, vs, id, 1, W.defer.depth, i, j, li, xi,
+                                                 yi, zi, &lev, c, &deferred, keep);
     if (DEFER) {
       const int64_t e = off + j;
       if (tgt == kDeferred) {
