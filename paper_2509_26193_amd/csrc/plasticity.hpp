@@ -52,8 +52,16 @@ __device__ __forceinline__ void grow(double* __restrict__ z, int64_t g, int64_t 
   z[g] = zz > 0.0 ? zz : 0.0;
 }
 
+// Whether synapse s binds elements: one recorded with an endpoint outside [0, n) or a type
+// above 1 does not (see bind_k).
+__device__ __forceinline__ bool binds(const SynList& L, int64_t s, int64_t n) {
+  const int32_t i = L.src[s], g = L.tgt[s];
+  return i >= 0 && i < n && g >= 0 && g < n && L.type[s] <= 1;
+}
+
 // Frees the two elements a synapse binds.
 __device__ __forceinline__ void unbind(const SynList& L, int64_t s, int64_t n, int32_t* bound) {
+  if (!binds(L, s, n)) return;
   atomicSub(&bound[L.src[s]], 1);
   atomicSub(&bound[(1 + (int64_t)L.type[s]) * n + L.tgt[s]], 1);
 }
@@ -356,11 +364,11 @@ struct RetractWs {
 constexpr int kSegSmall = 64;   // candidates of an owner ranked by one thread each
 
 // Owner of synapse s: kind 0: its source; kinds 1 and 2 (k = 1): its target in its type's
-// array (-1: a type that binds no element).
+// array (-1: no such neuron or array).
 __device__ __forceinline__ int64_t owner_of(const SynList& L, int64_t s, int64_t n, int k) {
-  if (k == 0) return L.src[s];
-  const int t = (int)L.type[s];
-  return t > 1 ? -1 : t * n + L.tgt[s];
+  const int32_t j = k == 0 ? L.src[s] : L.tgt[s];
+  const int t = k == 0 ? 0 : (int)L.type[s];
+  return j < 0 || j >= n || t > 1 ? -1 : t * n + j;
 }
 
 __global__ void __launch_bounds__(kPlastBlock) excess_k(const int32_t* __restrict__ bound_k,
@@ -381,7 +389,7 @@ __global__ void __launch_bounds__(kPlastBlock) retract_count_k(SynList L, int64_
     bool f = false;
     if (!dead[s]) {
       const int64_t o = owner_of(L, s, n, k);
-      f = o >= 0 && R.exc[o] > 0;
+      f = o >= 0 && R.exc[o] > 0 && binds(L, s, n);
       if (f) R.within[s] = atomicAdd(&R.cnt[o], 1);
     }
     R.flag[s] = f ? 1 : 0;
