@@ -677,11 +677,23 @@ __device__ __forceinline__ void morton_decode(uint64_t k, uint32_t& x, uint32_t&
   }
 }
 
-// Sort keys of the sources: (simulation, type) group in the top `gb` of `kb` bits, then
-// the leading kb - gb bits of the Hilbert index; value = flat Morton position. Sources
-// are packed in Morton order (position p0 + p1), so only that prefix is sorted.
-__global__ void b_hkeys_k(BatchDev B, int64_t total, int gb, int kb, uint64_t* key,
-                          int32_t* val) {
+// Leading bits of the Hilbert index that order the sources of a simulation of n neurons: by
+// n alone, so that its tiles, the cuts of their walks and the last bits of its sums are
+// the same in every batch. 23 bits make 32 cells or more per neuron, cells of 1/200 of the
+// box edge, and three passes of the sort for one simulation.
+constexpr int64_t kFewNeurons = (int64_t)1 << 18;
+
+__host__ __device__ inline int hilbert_bits(int64_t n) { return n <= kFewNeurons ? 23 : 31; }
+
+// Sort key of a source: its (simulation, type) group, then its simulation's `own` bits of
+// the Hilbert index in a field of `bits`, those of the launch's largest simulation.
+__host__ __device__ inline uint64_t source_key(uint64_t group, uint64_t h, int own, int bits) {
+  return (group << bits) | ((h >> (63 - own)) << (bits - own));
+}
+
+// Sort keys of the sources; value = flat Morton position. Sources are packed in Morton order
+// (position p0 + p1), so only that prefix is sorted.
+__global__ void b_hkeys_k(BatchDev B, int64_t total, int bits, uint64_t* key, int32_t* val) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= total) return;
   const int t = B.src_type[g];
@@ -690,10 +702,9 @@ __global__ void b_hkeys_k(BatchDev B, int64_t total, int gb, int kb, uint64_t* k
   const SimDesc& d = B.sims[s];
   uint32_t x, y, z;
   morton_decode(d.keys[g - B.nbase[s]], x, y, z);
-  const int hb = kb - gb;
-  const uint64_t h = hilbert3(x, y, z) >> (63 - hb);
   const int64_t idx = sources(B.sources[g]);
-  key[idx] = ((uint64_t)(2 * s + t) << hb) | h;
+  key[idx] = source_key((uint64_t)(2 * s + t), hilbert3(x, y, z),
+                        hilbert_bits(B.nbase[s + 1] - B.nbase[s]), bits);
   val[idx] = (int32_t)g;
 }
 
@@ -736,6 +747,7 @@ constexpr size_t kCkptSlotBytes = sizeof(int32_t) + kWave * (sizeof(double) + si
 
 struct SearchScratch {
   SearchSize q;
+  int64_t max_n;                // neurons of the largest simulation
   BatchDev B;
   SweepOut W;
   int32_t* counters;            // [0] tile count, [1] sources, [2] units, then the dies'
@@ -837,6 +849,7 @@ inline SearchScratch carve(void* base, const SearchSize& q, const SimDesc* d_sim
   };
   SearchScratch S{};
   S.q = q;
+  S.max_n = q.total_n;
   S.B.sims = d_sims;
   S.B.nsims = q.nsims;
   S.B.nbase = d_nbase;
@@ -899,14 +912,11 @@ inline hipError_t enqueue_prep(SearchScratch& S, hipStream_t s) {
   b_tiles_k<<<1, kTilesBlock, 0, s>>>(B, S.counters, S.counters + 2, S.counters + 1, total_n,
                                       S.q.force, S.W.ck_slots, S.W.ck_cap);
   // 64-source tiles in Hilbert order within each (simulation, type) group
-  // (the keys keep 6 Hilbert bits more than it takes to number the neurons, which leaves
-  // about a neuron per cell where they lie 64 times denser than on average, up to 20 bits or
-  // more: cells of about a hundredth of the box edge or finer, for up to 2048 simulations)
-  int gb = 1, nb = 1;
+  // (24 bits for one simulation of few neurons, 32 for up to 256 of them or one large one)
+  int gb = 1;
   while ((1ll << gb) < 2ll * B.nsims) ++gb;
-  while ((1ll << nb) < total_n) ++nb;
-  const int kb = gb > 12 ? 48 : gb + nb + 6 <= 24 ? 24 : 32;
-  b_hkeys_k<<<g, 256, 0, s>>>(B, total_n, gb, kb, S.hkey[0], S.hval[0]);
+  const int bits = hilbert_bits(S.max_n), kb = (gb + bits + 7) / 8 * 8;
+  b_hkeys_k<<<g, 256, 0, s>>>(B, total_n, bits, S.hkey[0], S.hval[0]);
   int at = 0;
   e = radix_sort_pairs_ws(S.hkey[0], S.hval[0], S.hkey[1], S.hval[1], total_n, 0, kb, s, S.hsort,
                           S.counters + 1, &at);

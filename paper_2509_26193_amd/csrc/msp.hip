@@ -1009,6 +1009,8 @@ msp_status msp_batch_create(const msp_sim* sims, int32_t n_sims, int32_t flags, 
     return e == hipErrorOutOfMemory ? MSP_ERR_OOM : MSP_ERR_HIP;
   }
   b->S = carve(b->scratch, size, b->d_sims, b->d_nbase);
+  b->S.max_n = 0;
+  for (int k = 0; k < n_sims; ++k) b->S.max_n = std::max(b->S.max_n, sims[k].tree->n);
   handle_register(b, HandleKind::kBatch);
   *out = b;
   return MSP_OK;
