@@ -151,59 +151,174 @@ __global__ void __launch_bounds__(kPlastBlock) grow_draw_k(double* __restrict__ 
   }
 }
 
+// Selection of the r-th smallest of many 64-bit keys by one block: a histogram of twelve bits,
+// most significant first, then of the next twelve among the keys in the bin that holds it,
+// until few enough are left to be ranked. LDS of a block of THREADS threads:
 constexpr int kPickBlock = 1024;
-constexpr int kPickBins = 4096;
+constexpr int kPickBits = 12;
+constexpr int kPickBins = 1 << kPickBits;
+constexpr int kPickList = 256;             // keys that are ranked
+
+template <int THREADS>
+struct PickRoom {
+  union {
+    uint32_t hist[kPickBins];
+    struct {
+      uint64_t lk[kPickList];
+      int32_t li[kPickList];
+    };
+  };
+  int64_t lds[THREADS / kWave];
+  int64_t before;
+  DelSelect found;
+  int32_t bin, nlist;
+};
 
 // The value of each thread summed over the block; synchronises.
+template <int THREADS>
 __device__ __forceinline__ int64_t pick_sum(int64_t v, int64_t* lds) {
   for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = v;
   __syncthreads();
   int64_t s = 0;
-  for (int w = 0; w < kPickBlock / kWave; ++w) s += lds[w];
+  for (int w = 0; w < THREADS / kWave; ++w) s += lds[w];
   return s;
 }
 
-// The bin that holds the r-th item (r from 1) of a histogram, and the items before it.
-__device__ __forceinline__ void pick_bin(const uint32_t* hist, int64_t r, int64_t* lds, int* bin,
-                                         int64_t* before) {
-  constexpr int kPer = kPickBins / kPickBlock;
+// The bin that holds the r-th item (r from 1) of the room's histogram, the items before it
+// and those in it; synchronises at the end.
+template <int THREADS>
+__device__ __forceinline__ void pick_bin(PickRoom<THREADS>& L, int64_t r, int& bin, int64_t& before,
+                                         int64_t& count) {
+  constexpr int kPer = kPickBins / THREADS;
   const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   int64_t s = 0;
-  for (int q = 0; q < kPer; ++q) s += hist[t * kPer + q];
+  for (int q = 0; q < kPer; ++q) s += L.hist[t * kPer + q];
   int64_t x = s;
   for (int o = 1; o < kWave; o <<= 1) {
     const int64_t y = __shfl_up(x, o, kWave);
     if (lane >= o) x += y;
   }
   __syncthreads();
-  if (lane == kWave - 1) lds[w] = x;
+  if (lane == kWave - 1) L.lds[w] = x;
   __syncthreads();
   int64_t at = x - s;
-  for (int k = 0; k < w; ++k) at += lds[k];
+  for (int k = 0; k < w; ++k) at += L.lds[k];
   for (int q = 0; q < kPer; ++q) {
-    const int64_t h = hist[t * kPer + q];
+    const int64_t h = L.hist[t * kPer + q];
     if (at < r && r <= at + h) {
-      *bin = t * kPer + q;
-      *before = at;
+      L.bin = t * kPer + q;
+      L.before = at;
     }
     at += h;
   }
   __syncthreads();
+  bin = L.bin;
+  before = L.before;
+  count = L.hist[bin];
+  __syncthreads();
+}
+
+// The r-th of the room's list (nlist keys), by (key, index); synchronises.
+template <int THREADS>
+__device__ __forceinline__ DelSelect pick_listed(PickRoom<THREADS>& L, int64_t r) {
+  const int nlist = L.nlist;
+  for (int l = (int)threadIdx.x; l < nlist; l += THREADS) {
+    const uint64_t k = L.lk[l];
+    const int32_t i = L.li[l];
+    int64_t rank = 0;
+    for (int q = 0; q < nlist; ++q)
+      rank += (L.lk[q] < k || (L.lk[q] == k && L.li[q] < i)) ? 1 : 0;
+    if (rank == r - 1) L.found = DelSelect{k, i};
+  }
+  __syncthreads();
+  return L.found;
+}
+
+// f(key, index) for each of c keys, a thread's next four loaded together: a block alone is
+// bound by the latency of its loads.
+template <int THREADS, class F>
+__device__ __forceinline__ void pick_scan(const uint64_t* __restrict__ key, int64_t c, F f) {
+  constexpr int kAtOnce = 4;
+  for (int64_t b = (int64_t)threadIdx.x; b < c; b += kAtOnce * THREADS) {
+    uint64_t k[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int64_t i = b + u * THREADS;
+      k[u] = key[i < c ? i : b];
+    }
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u)
+      if (b + u * THREADS < c) f(k[u], b + u * THREADS);
+  }
+}
+
+// The r-th smallest (r from 1 to c) of c keys and its index, equal keys in the order of their
+// indices. Every thread of the block gets it.
+template <int THREADS>
+__device__ DelSelect kth_key(const uint64_t* __restrict__ key, int64_t c, int64_t r,
+                             PickRoom<THREADS>& L) {
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  uint64_t prefix = 0, mask = 0;
+  int64_t count = c;
+  for (int shift = 64 - kPickBits; shift > -kPickBits && count > kPickList; shift -= kPickBits) {
+    const int s0 = shift < 0 ? 0 : shift;
+    const uint64_t digit = shift < 0 ? (1u << (kPickBits + shift)) - 1 : kPickBins - 1;
+    __syncthreads();
+    for (int q = t; q < kPickBins; q += THREADS) L.hist[q] = 0;
+    __syncthreads();
+    pick_scan<THREADS>(key, c, [&](uint64_t k, int64_t) {
+      if ((k & mask) == prefix) atomicAdd(&L.hist[(k >> s0) & digit], 1u);
+    });
+    __syncthreads();
+    int bin;
+    int64_t before;
+    pick_bin(L, r, bin, before, count);
+    prefix |= (uint64_t)bin << s0;
+    mask |= digit << s0;
+    r -= before;
+  }
+  __syncthreads();
+  if (count <= kPickList) {
+    if (t == 0) L.nlist = 0;
+    __syncthreads();
+    pick_scan<THREADS>(key, c, [&](uint64_t k, int64_t i) {
+      if ((k & mask) != prefix) return;
+      const int l = atomicAdd(&L.nlist, 1);
+      L.lk[l] = k;
+      L.li[l] = (int32_t)i;
+    });
+    __syncthreads();
+    return pick_listed(L, r);
+  }
+  // all the bits are spent: the r-th of the equal keys
+  for (int64_t s0 = 0; s0 < c; s0 += THREADS) {
+    const int64_t s = s0 + t;
+    const bool eq = s < c && key[s] == prefix;
+    const int64_t n = pick_sum<THREADS>(eq ? 1 : 0, L.lds);
+    if (n < r) {
+      r -= n;
+      continue;
+    }
+    const uint64_t b = __ballot(eq);
+    __syncthreads();
+    if (lane == 0) L.lds[w] = __popcll(b);
+    __syncthreads();
+    int64_t rank = __popcll(b & ((1ull << lane) - 1ull));
+    for (int k = 0; k < w; ++k) rank += L.lds[k];
+    if (eq && rank == r - 1) L.found = DelSelect{prefix, s};
+    break;
+  }
+  __syncthreads();
+  return L.found;
 }
 
 // One block: the want-th smallest (priority, index).
 __global__ void __launch_bounds__(kPickBlock) del_pick_k(double frac, DevCount mc, int blocks,
                                                         const uint64_t* __restrict__ key,
                                                         DelWs W) {
-  __shared__ uint32_t hist[kPickBins];
-  __shared__ int64_t lds[kPickBlock / kWave];
-  __shared__ uint64_t lk[kPickBlock];
-  __shared__ int32_t li[kPickBlock];
-  __shared__ int bin;
-  __shared__ int64_t before;
-  __shared__ int32_t nlist;
+  __shared__ PickRoom<kPickBlock> L;
   __shared__ int32_t first[kStrideGrid + 1];     // kept priorities of the blocks before
   const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   const int64_t m = mc.get();
@@ -230,18 +345,18 @@ __global__ void __launch_bounds__(kPickBlock) del_pick_k(double frac, DevCount m
     const int64_t y = __shfl_up(x, o, kWave);
     if (lane >= o) x += y;
   }
-  if (lane == kWave - 1) lds[w] = x;
+  if (lane == kWave - 1) L.lds[w] = x;
   __syncthreads();
   int64_t at = x - nk;
-  for (int k = 0; k < w; ++k) at += lds[k];
+  for (int k = 0; k < w; ++k) at += L.lds[k];
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     first[t * kPer + q] = (int32_t)at;
     at += kept[q];
   }
   if (t == kPickBlock - 1) first[kStrideGrid] = (int32_t)at;
-  nb = pick_sum(nb, lds);
-  over = pick_sum(over, lds);
+  nb = pick_sum<kPickBlock>(nb, L.lds);
+  over = pick_sum<kPickBlock>(over, L.lds);
   nk = first[kStrideGrid];
   const int64_t r = want - nb;
   // the i-th kept priority of all: its place in the blocks' rooms
@@ -258,71 +373,33 @@ __global__ void __launch_bounds__(kPickBlock) del_pick_k(double frac, DevCount m
     const uint64_t width = hi - lo;
     int sh = 0;
     while ((width >> sh) >= kPickBins) ++sh;
-    for (int q = t; q < kPickBins; q += kPickBlock) hist[q] = 0;
-    if (t == 0) nlist = 0;
+    for (int q = t; q < kPickBins; q += kPickBlock) L.hist[q] = 0;
     __syncthreads();
     for (int i = t; i < (int)nk; i += kPickBlock)
-      atomicAdd(&hist[(W.ckey[place(i)] - lo) >> sh], 1u);
+      atomicAdd(&L.hist[(W.ckey[place(i)] - lo) >> sh], 1u);
     __syncthreads();
-    pick_bin(hist, r, lds, &bin, &before);
-    for (int i = t; i < (int)nk; i += kPickBlock) {
-      const int64_t p = place(i);
-      const uint64_t k = W.ckey[p];
-      if ((int)((k - lo) >> sh) != bin) continue;
-      const int l = atomicAdd(&nlist, 1);
-      if (l < kPickBlock) {
-        lk[l] = k;
-        li[l] = W.cidx[p];
+    int bin;
+    int64_t before, count;
+    pick_bin(L, r, bin, before, count);
+    if (count <= kPickList) {
+      if (t == 0) L.nlist = 0;
+      __syncthreads();
+      for (int i = t; i < (int)nk; i += kPickBlock) {
+        const int64_t p = place(i);
+        const uint64_t k = W.ckey[p];
+        if ((int)((k - lo) >> sh) != bin) continue;
+        const int l = atomicAdd(&L.nlist, 1);
+        L.lk[l] = k;
+        L.li[l] = W.cidx[p];
       }
-    }
-    __syncthreads();
-    if (nlist <= kPickBlock) {
-      if (t < nlist) {
-        int64_t rank = 0;
-        for (int q = 0; q < nlist; ++q)
-          rank += (lk[q] < lk[t] || (lk[q] == lk[t] && li[q] < li[t])) ? 1 : 0;
-        if (before + rank == r - 1) *W.st = DelSelect{lk[t], li[t]};
-      }
+      __syncthreads();
+      const DelSelect d = pick_listed(L, r - before);
+      if (t == 0) *W.st = d;
       return;
     }
   }
-  // all priorities, most significant digits first, then the index among equal ones
-  uint64_t prefix = 0, mask = 0;
-  int64_t left = want;
-  for (int shift = 52; shift > -12; shift -= 12) {
-    const int s0 = shift < 0 ? 0 : shift;
-    const uint64_t digit = shift < 0 ? (1u << (12 + shift)) - 1 : kPickBins - 1;
-    for (int q = t; q < kPickBins; q += kPickBlock) hist[q] = 0;
-    __syncthreads();
-    for (int64_t s = t; s < m; s += kPickBlock) {
-      const uint64_t k = key[s];
-      if ((k & mask) == prefix) atomicAdd(&hist[(k >> s0) & digit], 1u);
-    }
-    __syncthreads();
-    pick_bin(hist, left, lds, &bin, &before);
-    prefix |= (uint64_t)bin << s0;
-    mask |= digit << s0;
-    left -= before;
-    __syncthreads();
-  }
-  for (int64_t s0 = 0; s0 < m && left > 0; s0 += kPickBlock) {
-    const int64_t s = s0 + t;
-    const bool eq = s < m && key[s] == prefix;
-    const int64_t c = pick_sum(eq ? 1 : 0, lds);
-    if (c < left) {
-      left -= c;
-      continue;
-    }
-    // the left-th of this chunk
-    const uint64_t b = __ballot(eq);
-    __syncthreads();
-    if (lane == 0) lds[w] = __popcll(b);
-    __syncthreads();
-    int64_t rank = __popcll(b & ((1ull << lane) - 1ull));
-    for (int k = 0; k < w; ++k) rank += lds[k];
-    if (eq && rank == left - 1) *W.st = DelSelect{prefix, s};
-    break;
-  }
+  const DelSelect d = kth_key(key, m, want, L);
+  if (t == 0) *W.st = d;
 }
 
 // Marks the deleted synapses (st null: none, all marks cleared) and frees their elements.
@@ -352,16 +429,21 @@ __global__ void __launch_bounds__(kPlastBlock) del_mark_k(const uint64_t* __rest
 // place of a sort of them all by (owner, priority) for each kind: 6 launches twice instead
 // of 18 to 45 three times.
 struct RetractWs {
-  int32_t* exc;                 // [owners] elements to retract
+  uint32_t* exc;                // [owners] elements to retract, times two, plus one where the
+                                // owner has more than kSegLarge elements; 0: none
   int32_t* cnt;                 // [owners] candidates
   int32_t* off;                 // [owners] candidates of the owners before
   uint8_t* flag;                // [m] candidate
   int32_t* within;              // [m] place among the owner's candidates
   uint64_t* seg;                // [candidates] (priority << 32 | synapse), by owner
-  int32_t* nlarge;              // [1] owners with more than kSegSmall candidates,
+  int32_t* nlarge;              // [2] owners with more than kSegSmall candidates, with more
+                                // than kSegLarge,
   int32_t* large;               // [m / kSegSmall + 1] and which
+  int32_t* huge;                // [m / kSegLarge + 1]
 };
 constexpr int kSegSmall = 64;   // candidates of an owner ranked by one thread each
+constexpr int kSegLarge = 16384;           // candidates of an owner that one block takes
+constexpr int kSegBlocks = 32;  // blocks of an owner with more: each selects, and marks its share
 
 // Owner of synapse s: kind 0: its source; kinds 1 and 2 (k = 1): its target in its type's
 // array (-1: no such neuron or array).
@@ -375,22 +457,40 @@ __global__ void __launch_bounds__(kPlastBlock) excess_k(const int32_t* __restric
                                                        const double* __restrict__ z_k,
                                                        int64_t owners, RetractWs R) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j == 0) *R.nlarge = 0;
+  if (j < 2) R.nlarge[j] = 0;
   if (j >= owners) return;
-  R.exc[j] = bound_k[j] - (int32_t)floor(z_k[j]);
+  const int32_t b = bound_k[j], e = b - (int32_t)floor(z_k[j]);
+  R.exc[j] = e > 0 ? (uint32_t)e << 1 | (b > kSegLarge ? 1u : 0u) : 0u;
   R.cnt[j] = 0;
 }
 
+// Owners with many elements take one atomic per wave and owner: additions to one address
+// follow one another. (A step over 2 M synapses, a third of them one neuron's, takes 1.3 ms with
+// this and the blocks of kSegBlocks, 19 ms without, 0.3 ms over the same list without that
+// neuron.)
 __global__ void __launch_bounds__(kPlastBlock) retract_count_k(SynList L, int64_t n, int k,
                                                               const uint8_t* __restrict__ dead,
                                                               DevCount mc, RetractWs R) {
   const int64_t m = mc.get();
+  const int lane = (int)(threadIdx.x & (kWave - 1));
   for (int64_t s = gtid(); s < m; s += gstride()) {
-    bool f = false;
+    bool f = false, many = false;
+    int64_t o = -1;
     if (!dead[s]) {
-      const int64_t o = owner_of(L, s, n, k);
-      f = o >= 0 && R.exc[o] > 0 && binds(L, s, n);
-      if (f) R.within[s] = atomicAdd(&R.cnt[o], 1);
+      o = owner_of(L, s, n, k);
+      const uint32_t e = o >= 0 ? R.exc[o] : 0u;
+      f = e > 0 && binds(L, s, n);
+      many = f && (e & 1u);
+    }
+    if (f && !many) R.within[s] = atomicAdd(&R.cnt[o], 1);
+    for (uint64_t left = __ballot(many); left;) {            // (uniform over the wave)
+      const int first = __ffsll((unsigned long long)left) - 1;
+      const uint64_t same = __ballot(many && o == __shfl(o, first, kWave));
+      int32_t at = 0;
+      if (lane == first) at = atomicAdd(&R.cnt[o], __popcll(same));
+      at = __shfl(at, first, kWave);
+      if (same >> lane & 1) R.within[s] = at + __popcll(same & ((1ull << lane) - 1ull));
+      left &= ~same;
     }
     R.flag[s] = f ? 1 : 0;
   }
@@ -408,30 +508,26 @@ __global__ void __launch_bounds__(kPlastBlock) retract_lay_k(SynList L, int64_t 
     const uint64_t q = philox_word0(seed, 4, (uint64_t)s, st, kind, 0) >> 32;
     const int32_t at = R.within[s];
     R.seg[(int64_t)R.off[o] + at] = (q << 32) | (uint64_t)s;
-    if (at == 0 && R.cnt[o] > kSegSmall) R.large[atomicAdd(R.nlarge, 1)] = (int32_t)o;
+    if (at == 0) {
+      const int32_t c = R.cnt[o];
+      if (c > kSegLarge) R.huge[atomicAdd(&R.nlarge[1], 1)] = (int32_t)o;
+      else if (c > kSegSmall) R.large[atomicAdd(&R.nlarge[0], 1)] = (int32_t)o;
+    }
   }
 }
 
-__device__ __forceinline__ void retract_one(const SynList& L, int64_t s, int64_t n,
-                                            uint8_t* dead, int32_t* bound) {
-  dead[s] = 1;
-  unbind(L, s, n, bound);
-}
-
-// Each candidate's rank among its owner's, one thread each; the owners with many
-// candidates a block each (the excess-th smallest by digits of 8 bits, most significant
-// first).
-__global__ void __launch_bounds__(kPlastBlock) retract_k(SynList L, int64_t n, int k, DevCount mc,
-                                                        uint8_t* __restrict__ dead, int32_t* bound,
-                                                        RetractWs R) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint64_t prefix;
-  __shared__ int32_t left;
+// Each candidate's rank among its owner's, one thread each; the owners with many candidates a
+// block each, those with very many kSegBlocks blocks that mark a share each (every one of them
+// selects the excess-th smallest by itself: no launch or wait between).
+__global__ void __launch_bounds__(kPlastBlock) __attribute__((amdgpu_waves_per_eu(8))) retract_k(
+    SynList L, int64_t n, int k, DevCount mc, uint8_t* __restrict__ dead, int32_t* bound,
+    RetractWs R) {
+  __shared__ PickRoom<kPlastBlock> room;
   const int64_t m = mc.get();
   for (int64_t s = gtid(); s < m; s += gstride()) {
     if (!R.flag[s]) continue;
     const int64_t o = owner_of(L, s, n, k);
-    const int32_t c = R.cnt[o], e = R.exc[o];
+    const int32_t c = R.cnt[o], e = (int32_t)(R.exc[o] >> 1);
     if (c > kSegSmall) continue;
     const uint64_t* seg = R.seg + R.off[o];
     int32_t rank = 0;
@@ -439,39 +535,29 @@ __global__ void __launch_bounds__(kPlastBlock) retract_k(SynList L, int64_t n, i
       const uint64_t me = seg[R.within[s]];
       for (int32_t q = 0; q < c; ++q) rank += seg[q] < me ? 1 : 0;
     }
-    if (rank < e) retract_one(L, s, n, dead, bound);
+    if (rank < e) {
+      dead[s] = 1;
+      unbind(L, s, n, bound);
+    }
   }
-  const int32_t nlarge = *R.nlarge;
+  const int64_t huge = (int64_t)R.nlarge[1] * kSegBlocks, all = huge + R.nlarge[0];
   const int t = (int)threadIdx.x;
-  for (int32_t q = blockIdx.x; q < nlarge; q += gridDim.x) {    // uniform over the block
-    const int64_t o = R.large[q];
-    const int32_t c = R.cnt[o], e = R.exc[o];
+  for (int64_t q = blockIdx.x; q < all; q += gridDim.x) {       // uniform over the block
+    const int64_t o = q < huge ? R.huge[q / kSegBlocks] : R.large[q - huge];
+    const int64_t c = R.cnt[o], e = R.exc[o] >> 1;
+    const int share = q < huge ? (int)(q % kSegBlocks) : 0, shares = q < huge ? kSegBlocks : 1;
     const uint64_t* seg = R.seg + R.off[o];
-    uint64_t mask = 0;
-    if (t == 0) {
-      prefix = 0;
-      left = e;
+    const uint64_t last = e < c ? kth_key(seg, c, e, room).key : ~0ull;
+    int32_t gone = 0;
+    for (int64_t i = c * share / shares + t; i < c * (share + 1) / shares; i += kPlastBlock) {
+      if (seg[i] > last) continue;
+      const int64_t s = (int64_t)(uint32_t)seg[i];
+      dead[s] = 1;
+      ++gone;
+      atomicSub(&bound[k == 0 ? (1 + (int64_t)L.type[s]) * n + L.tgt[s] : L.src[s]], 1);
     }
-    for (int shift = 56; shift >= 0 && e < c; shift -= 8) {
-      hist[t] = 0;
-      __syncthreads();
-      const uint64_t pre = prefix;
-      for (int32_t i = t; i < c; i += kPlastBlock)
-        if ((seg[i] & mask) == pre) atomicAdd(&hist[(seg[i] >> shift) & 255u], 1u);
-      __syncthreads();
-      if (t == 0) {
-        int32_t l = left;
-        int d = 0;
-        while (d < 255 && (int32_t)hist[d] < l) l -= (int32_t)hist[d++];
-        left = l;
-        prefix = pre | ((uint64_t)d << shift);
-      }
-      mask |= (uint64_t)255 << shift;
-      __syncthreads();
-    }
-    const uint64_t last = e < c ? prefix : ~0ull;
-    for (int32_t i = t; i < c; i += kPlastBlock)
-      if (seg[i] <= last) retract_one(L, (int64_t)(uint32_t)seg[i], n, dead, bound);
+    for (int w = 1; w < kWave; w <<= 1) gone += __shfl_xor(gone, w, kWave);
+    if ((t & (kWave - 1)) == 0 && gone) atomicSub(&bound[k * n + o], gone);     // the owner's
     __syncthreads();
   }
 }

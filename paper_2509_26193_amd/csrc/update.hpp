@@ -119,14 +119,15 @@ inline PlastWs plast_ws(void* base, int64_t n, int64_t cap_m, size_t* bytes) {
   w.del.kept = c.take<int32_t>(blocks);
   w.del.ckey = c.take<uint64_t>(blocks * kDelRoom);
   w.del.cidx = c.take<int32_t>(blocks * kDelRoom);
-  w.ret.exc = c.take<int32_t>(2 * n);
+  w.ret.exc = c.take<uint32_t>(2 * n);
   w.ret.cnt = c.take<int32_t>(2 * n);
   w.ret.off = c.take<int32_t>(2 * n);
   w.ret.flag = c.take<uint8_t>(cap_m);
   w.ret.within = w.pos;
   w.ret.seg = w.key;
-  w.ret.nlarge = c.take<int32_t>(1);
+  w.ret.nlarge = c.take<int32_t>(2);
   w.ret.large = c.take<int32_t>(cap_m / kSegSmall + 1);
+  w.ret.huge = c.take<int32_t>(cap_m / kSegLarge + 1);
   w.scan_ws = c.take_bytes(std::max(scan_tmp_bytes<int32_t>(cap_m + 1),
                                     scan_tmp_bytes<int32_t>(2 * n)));
   w.O.src = c.take<int32_t>(cap_m);
