@@ -77,8 +77,8 @@ typedef struct msp_octree_s* msp_octree;
  * Errors: MSP_ERR_INVALID for n < 1 or n > MSP_MAX_NEURONS, a non-finite box corner, an
  * edge outside that range, leaf_size != 1, null pointers; MSP_ERR_OOM. A non-finite
  * position sets the device error flag. The build waits on `s` once, to size the node
- * arrays (twice where more than 24 neurons share the leading bits of their cells and are
- * out of order in the rest); its last kernels may still run when it returns.
+ * arrays (twice where more than 128 neurons share the leading bits of their cells and
+ * are out of order in the rest); its last kernels may still run when it returns.
  */
 msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3],
                             double box_edge, int32_t leaf_size, hipStream_t s,

@@ -399,12 +399,14 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
                                                             t->order, t->err, outside);
     TRY(hipGetLastError());
     // the leading bits and their short runs first; if that leaves keys out of order (long
-    // runs), the whole keys (from that order, in which equal keys are in id order)
+    // runs), all the bits below those that the first and the last key share, from that order,
+    // in which equal keys are in id order
     int32_t N32 = 0, found[2] = {0, 0};          // a position outside, keys out of order
-    for (int whole = 0;; ++whole) {
-      if (whole) {
+    int bits = 0;                                // of the second sort
+    for (;;) {
+      if (bits) {
         TRY(hipMemsetAsync(outside + 1, 0, sizeof(int32_t), s));
-        TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, 0, 64, s, sort_ws));
+        TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, 0, (bits + 7) / 8 * 8, s, sort_ws));
       } else {
         TRY(radix_sort_pairs_ws(t->keys, t->order, k1, v1, n, kLeadShift, kLeadBits, s, sort_ws));
         order_runs_k<<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(t->keys, t->order, n);
@@ -418,12 +420,16 @@ msp_status msp_build_octree(const double* pos, int64_t n, const double box_min[3
       R.add(basep + n);
       R.add(outside);
       R.add(outside + 1);
-      int64_t got[3];
+      R.add(reinterpret_cast<const int64_t*>(t->keys));
+      R.add(reinterpret_cast<const int64_t*>(t->keys + n - 1));
+      int64_t got[5];
       TRY(read_back(R, got, s));
       N32 = (int32_t)got[0];
       found[0] = (int32_t)got[1];
       found[1] = (int32_t)got[2];
-      if (!found[1] || whole) break;
+      if (!found[1] || bits) break;
+      bits = kLeadShift;                         // (the leading bits are in order)
+      while ((got[3] ^ got[4]) >> bits) ++bits;
     }
     double far = 0.0;
     for (int a = 0; a < 3; ++a)
