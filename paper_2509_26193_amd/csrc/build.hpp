@@ -272,13 +272,20 @@ __global__ void __launch_bounds__(kBuildBlock) nodes_k(
 // (cross2). A pass over the tree is thus one launch for up to 4 096 neurons, two up to
 // 131 072 and three beyond, instead of one per depth; small trees are bound by that.
 constexpr int kChunkLog = 10;
-constexpr int kChunkLogOne = 12;           // trees of up to 2^12 neurons are one chunk
+constexpr int kChunkLogOne = 12;           // trees of up to 2^12 neurons are one chunk, if they
+                                           // have up to kNodesOne nodes
 constexpr int kSuper = 128;
 constexpr int kDepths = kMaxDepth + 1;
 constexpr int kChunksOne = 1024;           // threads of chunks_k for a tree of one chunk (4 096
                                            // neurons: 19 us with 256, 8.5 with these)
 
-inline int chunk_log(int64_t n) { return n <= ((int64_t)1 << kChunkLogOne) ? kChunkLogOne : kChunkLog; }
+// Trees of few neurons and nodes are one chunk (4 000 neurons in 2 000 cells at the finest depth,
+// 36 000 nodes: the refresh takes 115 us by four chunks, 203 by one).
+constexpr int64_t kNodesOne = 8192;
+
+inline int chunk_log(int64_t n, int64_t N) {
+  return n <= ((int64_t)1 << kChunkLogOne) && N <= kNodesOne ? kChunkLogOne : kChunkLog;
+}
 
 __global__ void __launch_bounds__(kChunksOne) chunks_k(
     const uint8_t* __restrict__ depth, const int32_t* __restrict__ skip,

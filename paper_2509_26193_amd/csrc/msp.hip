@@ -51,7 +51,7 @@ void carve_nodes(msp_octree_s* t, char* base, size_t* bytes) {
   t->skip = c.take<int32_t>(N);
   t->nbeg = c.take<int32_t>(N);
   t->nend = c.take<int32_t>(N);
-  t->chunk_log = chunk_log(t->n);
+  t->chunk_log = chunk_log(t->n, N);
   t->nch = (int32_t)runs_of(t->n, t->chunk_log);
   t->nsup = (t->nch + kSuper - 1) / kSuper;
   t->chunk_x = c.take<int32_t>(t->nch + 1);

@@ -71,7 +71,7 @@ __device__ __forceinline__ void refresh_node(int32_t x, uint32_t meta, const int
 
 // The subtree ends of a chunk's nodes in LDS (those past `room` stay in global memory), and the
 // children of its inner nodes found through them.
-constexpr int kSkipRoomOne = 8192;         // trees of one chunk (see kChunkLogOne)
+constexpr int kSkipRoomOne = kNodesOne;    // trees of one chunk
 constexpr int kSkipRoom = 2048;            // (with 32 KB of LDS a block of 512 threads leaves
                                            // a CU's wavefronts short)
 
@@ -142,8 +142,45 @@ __global__ void pair_counts_k(const int32_t* __restrict__ vexc, const int32_t* _
 // one per depth: 8M neurons 0.88 ms (1.39), 2M 0.30 (0.37), 4 096 47 us in one launch (41 us
 // in nine, and 22 us for the lists of the depths). A thread's neurons, and its first node of
 // the next depth, are loaded together and ahead: 8M 0.81 -> 0.75 ms for the chunks.
+// A bucket's members are consecutive: every lane forms its neuron's terms, and the wave that has
+// the first member adds them up in order, from lane to lane (8M neurons in cells of 64: 2.90 ->
+// 0.86 ms, where one thread loaded one member after the other; in cells of 2: 5.88
+// -> 5.71).
+__device__ __forceinline__ void bucket_terms(int2 w, const double* __restrict__ pos, int32_t i,
+                                             double (&d)[6]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double c = pos[3 * (int64_t)i + a];
+    d[a] = w.x > 0 ? (double)w.x * c : -0.0;       // (-0.0 leaves any sum as it is)
+    d[3 + a] = w.y > 0 ? (double)w.y * c : -0.0;
+  }
+}
+
+// Lane k's value, in every lane.
+__device__ __forceinline__ double lane_f64(double v, int k) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), k);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ void bucket_add(Acc3& A, Acc3& B, int2 w, const double (&d)[6], int from,
+                                           int to) {
+  for (int k = from; k < to; ++k) {
+    A.v += __builtin_amdgcn_readlane(w.x, k);
+    B.v += __builtin_amdgcn_readlane(w.y, k);
+    A.x = A.x + lane_f64(d[0], k);
+    A.y = A.y + lane_f64(d[1], k);
+    A.z = A.z + lane_f64(d[2], k);
+    B.x = B.x + lane_f64(d[3], k);
+    B.y = B.y + lane_f64(d[4], k);
+    B.z = B.z + lane_f64(d[5], k);
+  }
+}
+
 template <bool PAIRS, bool ONE>
-__global__ void __launch_bounds__(ONE ? 1024 : 512) refresh_chunk_k(
+__global__ void __launch_bounds__(ONE ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : 6)))
+refresh_chunk_k(
     int64_t n, Chunks C, NodeRec* r0, NodeRec* r1, const int32_t* __restrict__ leaf_at,
     const int32_t* __restrict__ order, const double* __restrict__ pos,
     const int32_t* __restrict__ vexc, const int32_t* __restrict__ vinh,
@@ -165,13 +202,15 @@ __global__ void __launch_bounds__(ONE ? 1024 : 512) refresh_chunk_k(
     if (v.x < 0 || v.y < 0) atomicOr(err, kErrNegative);
     return make_int2(v.x < 0 ? 0 : v.x, v.y < 0 ? 0 : v.y);
   };
+  const int lane = t & (kWave - 1);
   const int64_t p0 = (int64_t)c << C.log;
   const int64_t p1 = p0 + ((int64_t)1 << C.log) < n ? p0 + ((int64_t)1 << C.log) : n;
-  for (int64_t b = p0 + t; b < p1; b += kAtOnce * threads) {
+  // (every wave takes its whole turns: its lanes add up buckets together)
+  for (int64_t b = p0 + t; b - lane < p1; b += kAtOnce * threads) {
     int32_t at[kAtOnce], before[kAtOnce], after[kAtOnce], id[kAtOnce];
 #pragma unroll
     for (int u = 0; u < kAtOnce; ++u) {
-      const int64_t p = b + u * threads < p1 ? b + u * threads : b;
+      const int64_t p = b + u * threads < p1 ? b + u * threads : p1 - 1;
       at[u] = leaf_at[p];
       before[u] = p > 0 ? leaf_at[p - 1] : -1;
       after[u] = p + 1 < n ? leaf_at[p + 1] : -1;
@@ -186,30 +225,76 @@ __global__ void __launch_bounds__(ONE ? 1024 : 512) refresh_chunk_k(
     for (int u = 0; u < kAtOnce; ++u) {
       const int64_t p = b + u * threads;
       const int32_t x = at[u];
-      if (p >= p1 || before[u] == x) continue;
-      if (after[u] != x) {
+      const bool mine = p < p1;
+      const bool member = mine && (before[u] == x || after[u] == x);       // of a bucket
+      if (mine && !member) {
         const int2 w = checked(v[u]);
         r0[x].v = w.x;
         r1[x].v = w.y;
-        continue;
       }
-      Acc3 A, B;
-      for (int64_t q = p; q < n && leaf_at[q] == x; ++q) {
-        const int32_t i = order[q];
-        const int2 w = checked(load(i));
-        const double px = pos[3 * (int64_t)i], py = pos[3 * (int64_t)i + 1],
-                     pz = pos[3 * (int64_t)i + 2];
-        A.add(w.x, px, py, pz);
-        B.add(w.y, px, py, pz);
-        vs0[q] = w.x;
-        vs1[q] = w.y;
+      if (!__any(member)) continue;
+      int2 w = make_int2(0, 0);
+      double d[6];
+      if (member) {
+        w = checked(v[u]);
+        vs0[p] = w.x;
+        vs1[p] = w.y;
+        bucket_terms(w, pos, id[u], d);
       }
-      NodeRec e, f;
-      e.meta = f.meta = r0[x].meta;
-      A.store(e, err);
-      B.store(f, err);
-      r0[x] = e;
-      r1[x] = f;
+      const bool head = member && before[u] != x;
+      const int last = __popcll(__ballot(mine)) - 1;
+      int64_t sum0 = 0, sum1 = 0;                  // a head's counts (its sums: in d)
+      for (uint64_t left = __ballot(head); left; left &= left - 1) {       // (uniform)
+        const int from = __ffsll((unsigned long long)left) - 1;
+        const int32_t xb = __builtin_amdgcn_readlane(x, from);
+        Acc3 A, B;
+        int to = from + __popcll(__ballot(mine && x == xb));
+        bucket_add(A, B, w, d, from, to);
+        // those past the wave's neurons
+        for (int64_t q0 = p - lane + last + 1; to == last + 1 || to == kWave; q0 += kWave) {
+          const int64_t q = q0 + lane;
+          const bool more = q < n && leaf_at[q < n ? q : p0] == xb;
+          int2 w2 = make_int2(0, 0);
+          double d2[6];
+          if (more) {
+            const int32_t i = order[q];
+            w2 = load(i);
+            w2 = make_int2(w2.x < 0 ? 0 : w2.x, w2.y < 0 ? 0 : w2.y);
+            bucket_terms(w2, pos, i, d2);
+          }
+          to = __popcll(__ballot(more));
+          if (to == 0) break;
+          bucket_add(A, B, w2, d2, 0, to);
+          if (to < kWave) break;
+        }
+        if (lane == from) {
+          sum0 = A.v;
+          sum1 = B.v;
+          d[0] = A.x;
+          d[1] = A.y;
+          d[2] = A.z;
+          d[3] = B.x;
+          d[4] = B.y;
+          d[5] = B.z;
+        }
+      }
+      if (head) {
+        Acc3 A, B;
+        A.v = sum0;
+        A.x = d[0];
+        A.y = d[1];
+        A.z = d[2];
+        B.v = sum1;
+        B.x = d[3];
+        B.y = d[4];
+        B.z = d[5];
+        NodeRec e, f;
+        e.meta = f.meta = kLeafBit | kBucketBit | (uint32_t)x;
+        A.store(e, err);
+        B.store(f, err);
+        r0[x] = e;
+        r1[x] = f;
+      }
     }
   }
   // the lists of the depths follow one another: a thread's first node of the next depth is
