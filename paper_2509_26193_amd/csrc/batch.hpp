@@ -308,6 +308,14 @@ __host__ __device__ inline int slots_log(int p, int ck_slots, int cut) {
   return l - cut < 1 ? 1 : l - cut;
 }
 
+// Halvings after which every part has its two slots: 0 without checkpoints, where nothing has
+// to fit (eight rounds of block scans took 6 us of each of a gradient's two preparations).
+__host__ __device__ inline int slot_cuts(int ck_slots) {
+  int cut = 0;
+  while (slots_log(0, ck_slots, cut) > 1) ++cut;
+  return cut;
+}
+
 // Tiles per simulation: excitatory sources padded to a multiple of 64, then
 // inhibitory ones, so no tile mixes simulations or types; their parts, the parts' units
 // (a launch with more than kUnitsMax parts groups 2^g consecutive parts of a tile into a
@@ -342,7 +350,7 @@ __global__ void __launch_bounds__(kTilesBlock) b_tiles_k(BatchDev B, int32_t* ti
   while (g < kPartLogMax && (parts >> g) > kUnitsMax) ++g;
   if (force >= 0 || B.nsims == 1) g = 0;
   int cut = 0;
-  for (; cut < 8; ++cut) {
+  for (const int cuts = slot_cuts(ck_slots); cut < cuts; ++cut) {
     int64_t sum = 0;
     for (int s0 = 0; s0 < B.nsims; s0 += kTilesBlock) {
       const int64_t ts = tiles(s0 + t);

@@ -19,6 +19,11 @@ HARNESS = r"""
 #include <vector>
 %s
 int main() {
+  // no round of fitting without checkpoints, and after the last one two slots for each part
+  if (slot_cuts(0) != 0) return printf("rounds without checkpoints\n"), 1;
+  for (int ck : {kCkptMin, kCkptMax})
+    for (int p = 0; p <= kPartLogMax; ++p)
+      if (slots_log(p, ck, slot_cuts(ck)) != 1) return printf("slots at the end\n"), 1;
   const double shares[] = {0.02, 0.3, 0.7, 1.0};
   const int64_t sizes[] = {1, 64, 1000, 2500, 4000, 4096, 5000, 8192, 20000, 65536, 262144,
                            1 << 20, 1 << 23, 1 << 25};
@@ -48,7 +53,7 @@ int main() {
               if (parts > max_parts_for(total, ns, force)) return printf("parts\n"), 1;
               for (int ck : {q.slots, kCkptMin}) {  // (a tuned plan may aim at fewer)
                 int64_t sum = 0;
-                for (int cut = 0; cut < 8; ++cut) {
+                for (int cut = 0; cut <= slot_cuts(ck); ++cut) {
                   sum = 0;
                   for (int k = 0; k < ns; ++k) {
                     const int p = parts_log(ts[k], force);
@@ -86,7 +91,7 @@ def test_every_part_has_its_slots(tmp_path):
         code += _text(wave, r"^constexpr int %s = \d+;" % c) + "\n"
     code += _text(batch, r"^constexpr size_t kCkptSlotBytes =.*?;") + "\n"
     code += _text(batch, r"^struct SearchSize \{.*?^\};") + "\n"
-    for f in ("int parts_log", "int slots_log", "int64_t max_tiles_for", "int64_t max_parts_for",
+    for f in ("int parts_log", "int slots_log", "int slot_cuts", "int64_t max_tiles_for", "int64_t max_parts_for",
               "SearchSize search_size_in"):
         one = _text(batch, r"^(?:__host__ __device__ )?inline %s\([^{]*\{(?:[^\n]*\}$|.*?^\})" % f)
         code += one.replace("__host__ __device__ ", "") + "\n"
