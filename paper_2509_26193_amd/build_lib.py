@@ -33,15 +33,19 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = True) -> str:
-    src = os.path.join(CSRC, "msp.hip")
-    tmp = LIB + ".tmp"
+def compile_hip(src: str, out: str, verbose: bool = True) -> str:
+    """A shared library from one HIP source, with the library's flags and include paths."""
+    tmp = out + ".tmp"
     cmd = [HIPCC, *FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, src, "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, out)
+    return out
+
+
+def build(verbose: bool = True) -> str:
+    return compile_hip(os.path.join(CSRC, "msp.hip"), LIB, verbose)
 
 
 if __name__ == "__main__":

@@ -257,7 +257,7 @@ __device__ __forceinline__ void pick_scan(const uint64_t* __restrict__ key, int6
 // The r-th smallest (r from 1 to c) of c keys and its index, equal keys in the order of their
 // indices. Every thread of the block gets it.
 template <int THREADS>
-__device__ DelSelect kth_key(const uint64_t* __restrict__ key, int64_t c, int64_t r,
+__device__ __forceinline__ DelSelect kth_key(const uint64_t* __restrict__ key, int64_t c, int64_t r,
                              PickRoom<THREADS>& L) {
   const int t = (int)threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   uint64_t prefix = 0, mask = 0;
