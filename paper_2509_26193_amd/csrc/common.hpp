@@ -243,11 +243,6 @@ __global__ void fill_i64_k(int64_t* p, int64_t n, int64_t v) {
   if (k < n) p[k] = v;
 }
 
-__global__ void copy_i32_k(const int32_t* __restrict__ from, int32_t* __restrict__ to, int64_t n) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) to[k] = from[k];
-}
-
 // An item count known on the host (p null: v) or only on the device (*p, clamped to
 // [0, v]: the launch is sized for the bound v and threads past the count return).
 // Device counts let a sequence of launches run without reading anything back, so that
@@ -331,9 +326,16 @@ constexpr int kReadSlots = 64;
 struct ReadBack {
   const void* from[kReadMost];
   int wide[kReadMost];                   // 1: int64
-  int count = 0;
-  void add(const int32_t* p) { from[count] = p; wide[count++] = 0; }
-  void add(const int64_t* p) { from[count] = p; wide[count++] = 1; }
+  int count = 0;                         // (more than kReadMost: read_back refuses)
+  void add(const int32_t* p) { put(p, 0); }
+  void add(const int64_t* p) { put(p, 1); }
+  void put(const void* p, int w) {
+    if (count < kReadMost) {
+      from[count] = p;
+      wide[count] = w;
+    }
+    ++count;
+  }
 };
 
 __global__ void read_back_k(ReadBack R, int64_t* out) {
@@ -387,6 +389,7 @@ class ReadLease {
 
 // The values of R, once everything before on `s` has run.
 inline hipError_t read_back(const ReadBack& R, int64_t* out, hipStream_t s) {
+  if (R.count > kReadMost) return hipErrorInvalidValue;
   ReadLease lease;
   hipError_t e = hipSuccess;
   if (int64_t* slot = lease.get()) {
