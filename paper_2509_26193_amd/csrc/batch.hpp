@@ -89,8 +89,11 @@ constexpr int kDrawSplit = 2;
 constexpr int kDrawSplitTiles = 16384;
 constexpr int kDrawGroup = 32;
 
+// Six waves per SIMD, the most that the LDS of the restart levels leaves; counting launches
+// keep five, whose registers hold the counts without spilling most of them.
 template <bool DIAG, bool DEFER>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) search_draw_k(BatchDev B, SweepOut W) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DIAG ? 5 : 6)))
+search_draw_k(BatchDev B, SweepOut W) {
   const int tiles = *as_const(W.tile_count);
   if (tiles <= 0) return;
   const int split = tiles <= kDrawSplitTiles ? kDrawSplit : 1;

@@ -739,14 +739,46 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
       c0.entries += W.e0[(u0 + q) * kWave + lane];
     }
   }
-  for (int32_t j = first; j < a; j += split) {
+  // element j with its level-0 choice: restarts and outputs
+  auto finish = [&](int32_t j, int32_t id, bool neuron) {
     int lev = 1;
     Count c = c0;
     int32_t tgt = -1;
     int32_t deferred = -1;
-    int32_t id = -1;
-    bool neuron = false;
-    if (__builtin_expect(tiny, 0)) {
+    if (id >= 0)
+      tgt = neuron ? id
+                   : restart_search<DIAG, DEFER>(A, R, vs, id, 1, W.defer.depth, i, j, li, xi,
+                                                 yi, zi, &lev, c, &deferred, keep);
+    if (DEFER) {
+      const int64_t e = off + j;
+      if (tgt == kDeferred) {
+        W.defer.key[e] = (uint64_t)((uint32_t)deferred >> W.defer.shift);
+        W.defer.cell[e] = deferred;
+        W.defer.src[e] = i;
+        W.defer.elem[e] = j;
+        W.defer.level[e] = (uint8_t)lev;
+        tgt = -1;                               // the second phase overwrites it
+      } else {
+        W.defer.key[e] = W.defer.none;
+      }
+      W.defer.val[e] = (int32_t)e;
+    }
+    A.target[off + j] = tgt;
+    if (DIAG) {
+      if (D.z0) D.z0[off + j] = Z;
+      if (D.levels) D.levels[off + j] = lev;
+      if (D.visits) D.visits[off + j] = c.visits;
+      if (D.opens) D.opens[off + j] = c.opens;
+      if (D.visits0) D.visits0[off + j] = c0.visits;
+      if (D.opens0) D.opens0[off + j] = c0.opens;
+      if (D.entries0) D.entries0[off + j] = c0.entries;
+    }
+  };
+  // (a loop of its own: inside the other one it has every thread spill three more values)
+  if (__builtin_expect(tiny, 0)) {
+    for (int32_t j = first; j < a; j += split) {
+      int32_t id = -1;
+      bool neuron = false;
       int n = 0;
       Z = tiny_sum(A, R, vs, end, i, li, xi, yi, zi, *keep, n);
       if (Z > 0.0) {
@@ -760,7 +792,14 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
           neuron = s.chosen >= 0 ? s.chosen_neuron : s.last_neuron;
         }
       }
-    } else if (Z > 0.0) {
+      finish(j, id, neuron);
+    }
+    return;
+  }
+  for (int32_t j = first; j < a; j += split) {
+    int32_t id = -1;
+    bool neuron = false;
+    if (Z > 0.0) {
       const double T = draw_u(A.seed, i, j, A.step, 0) * Z;
       SelectPass<true> p{A.k2, T};
       Count none;
@@ -804,34 +843,7 @@ __device__ __forceinline__ void draw_slot(const SearchArgs& A, const DiagOut& D,
       id = p.chosen >= 0 ? p.chosen : p.last;
       neuron = p.chosen >= 0 ? p.chosen_neuron : p.last_neuron;
     }
-    if (id >= 0)
-      tgt = neuron ? id
-                   : restart_search<DIAG, DEFER>(A, R, vs, id, 1, W.defer.depth, i, j, li, xi,
-                                                 yi, zi, &lev, c, &deferred, keep);
-    if (DEFER) {
-      const int64_t e = off + j;
-      if (tgt == kDeferred) {
-        W.defer.key[e] = (uint64_t)((uint32_t)deferred >> W.defer.shift);
-        W.defer.cell[e] = deferred;
-        W.defer.src[e] = i;
-        W.defer.elem[e] = j;
-        W.defer.level[e] = (uint8_t)lev;
-        tgt = -1;                               // the second phase overwrites it
-      } else {
-        W.defer.key[e] = W.defer.none;
-      }
-      W.defer.val[e] = (int32_t)e;
-    }
-    A.target[off + j] = tgt;
-    if (DIAG) {
-      if (D.z0) D.z0[off + j] = Z;
-      if (D.levels) D.levels[off + j] = lev;
-      if (D.visits) D.visits[off + j] = c.visits;
-      if (D.opens) D.opens[off + j] = c.opens;
-      if (D.visits0) D.visits0[off + j] = c0.visits;
-      if (D.opens0) D.opens0[off + j] = c0.opens;
-      if (D.entries0) D.entries0[off + j] = c0.entries;
-    }
+    finish(j, id, neuron);
   }
 }
 
