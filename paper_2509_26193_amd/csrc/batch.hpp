@@ -690,11 +690,14 @@ __device__ __forceinline__ void morton_decode(uint64_t k, uint32_t& x, uint32_t&
 
 // Leading bits of the Hilbert index that order the sources of a simulation of n neurons: by
 // n alone, so that its tiles, the cuts of their walks and the last bits of its sums are
-// the same in every batch. 23 bits make 32 cells or more per neuron, cells of 1/200 of the
-// box edge, and three passes of the sort for one simulation.
-constexpr int64_t kFewNeurons = (int64_t)1 << 18;
-
-__host__ __device__ inline int hilbert_bits(int64_t n) { return n <= kFewNeurons ? 23 : 31; }
+// the same in every batch. Six bits more than it takes to number the neurons leave about a
+// neuron per cell where they lie 64 times denser than on average; 20 or more make cells of
+// a hundredth of the box edge. (1 M clustered neurons by 26 bits or by 31: XXX.)
+__host__ __device__ inline int hilbert_bits(int64_t n) {
+  int b = 20;
+  while (b < 31 && ((int64_t)1 << (b - 6)) < n) ++b;
+  return b;
+}
 
 // Sort key of a source: its (simulation, type) group, then its simulation's `own` bits of
 // the Hilbert index in a field of `bits`, those of the launch's largest simulation.
@@ -923,7 +926,8 @@ inline hipError_t enqueue_prep(SearchScratch& S, hipStream_t s) {
   b_tiles_k<<<1, kTilesBlock, 0, s>>>(B, S.counters, S.counters + 2, S.counters + 1, total_n,
                                       S.q.force, S.W.ck_slots, S.W.ck_cap);
   // 64-source tiles in Hilbert order within each (simulation, type) group
-  // (24 bits for one simulation of few neurons, 32 for up to 256 of them or one large one)
+  // (24 bits for one simulation of up to 2^17 neurons or a few small ones, 32 for one of any
+  // size, 64 of up to 2^18 or 2 048 of up to 2^14)
   int gb = 1;
   while ((1ll << gb) < 2ll * B.nsims) ++gb;
   const int bits = hilbert_bits(S.max_n), kb = (gb + bits + 7) / 8 * 8;
