@@ -134,14 +134,6 @@ __global__ void pair_counts_k(const int32_t* __restrict__ vexc, const int32_t* _
   if (i < n) both[i] = make_int2(vexc[i], vinh[i]);
 }
 
-// One block per chunk: its leaves (the caller's vacancy arrays are gathered by id; a bucket
-// leaf is done by its first member's thread, its members in sorted order, which is id order
-// within the finest cell), then its inner nodes by depth, deepest first. Bound by the
-// gathers (a 128-byte line for 8 bytes per neuron) and the records read and written; small
-// trees by the chain over the depths. The whole refresh, against a kernel for the leaves and
-// one per depth: 8M neurons 0.88 ms (1.39), 2M 0.30 (0.37), 4 096 47 us in one launch (41 us
-// in nine, and 22 us for the lists of the depths). A thread's neurons, and its first node of
-// the next depth, are loaded together and ahead: 8M 0.81 -> 0.75 ms for the chunks.
 // A bucket's members are consecutive: every lane forms its neuron's terms, and the wave that has
 // the first member adds them up in order, from lane to lane (8M neurons in cells of 64: 2.90 ->
 // 0.86 ms, where one thread loaded one member after the other; in cells of 2: 5.88
@@ -178,6 +170,14 @@ __device__ __forceinline__ void bucket_add(Acc3& A, Acc3& B, int2 w, const doubl
   }
 }
 
+// One block per chunk: its leaves (the caller's vacancy arrays are gathered by id; a bucket
+// leaf is done by its first member's wave, its members in sorted order, which is id order
+// within the finest cell), then its inner nodes by depth, deepest first. Bound by the
+// gathers (a 128-byte line for 8 bytes per neuron) and the records read and written; small
+// trees by the chain over the depths. The whole refresh, against a kernel for the leaves and
+// one per depth: 8M neurons 0.88 ms (1.39), 2M 0.30 (0.37), 4 096 47 us in one launch (41 us
+// in nine, and 22 us for the lists of the depths). A thread's neurons, and its first node of
+// the next depth, are loaded together and ahead: 8M 0.81 -> 0.75 ms for the chunks.
 template <bool PAIRS, bool ONE>
 __global__ void __launch_bounds__(ONE ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : 6)))
 refresh_chunk_k(
